@@ -107,7 +107,8 @@ typedef struct ims_opts {
     int32_t test_flags;    /* test hooks, 0 in normal use: bit 0 = LT grid shape without a
                               threshold table (hashes drawn in the kernel); bit 1 = unused;
                               bit 2 = LT without the equal-in-weights form; bit 3 = LT grid
-                              shape with full threshold hashes instead of count thresholds */
+                              shape with full threshold hashes instead of count thresholds;
+                              bit 4 = IC drawn-coins form whatever the sizes say */
     /* IC direction (Section 3, "Algorithms", expands the out-arcs of the last
        step's new nodes: the push side).  The pull side instead lets every
        (node, word) pair with an inactive trial scan its in-arcs for frontier
@@ -196,7 +197,10 @@ int ims_simulate_noalloc(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, 
  *   node_counts  device uint32[n_sets * n]: per set, trials in which each
  *                node ended active.                               optional (NULL)
  * Every set's results equal those of ims_simulate on that set.  Asynchronous
- * on `stream`. */
+ * on `stream`.  IC on graphs of at most 2^18 nodes draws every arc's coins
+ * once for all sets and walks the cascades over them where the sets meet
+ * enough arcs (any of opts' shape, blocks_per_cu and ic_* fields keeps the
+ * word-local tasks, which draw coins as they meet arcs). */
 int ims_simulate_sets(ims_graph* g, const uint32_t* set_offsets, const uint32_t* set_nodes, uint32_t n_sets,
                       uint32_t n_trials, uint64_t rng_seed, const ims_opts* opts, uint64_t* totals,
                       uint32_t* node_counts, void* stream);

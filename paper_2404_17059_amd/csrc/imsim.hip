@@ -18,6 +18,7 @@
 #include <vector>
 
 #include "imsim.h"
+#include "live_kernels.hpp"
 #include "plan.hpp"
 #include "sim_kernels.hpp"
 
@@ -95,6 +96,7 @@ struct ims_graph {
     int cus = 0;
     std::vector<int64_t> h_off;  // host copy of the out-offsets (launch planning)
     int64_t* d_off = nullptr;
+    uint32_t* d_off32 = nullptr;  // IC: the out-offsets in 32 bits (m < 2^32 - 1), for the drawn-coins form
     uint32_t* d_idx = nullptr;
     uint32_t* d_thr = nullptr;
     int64_t* d_in_off = nullptr;     // in-CSR offsets (LT: weight pieces; IC: arcs of nonzero threshold)
@@ -103,6 +105,7 @@ struct ims_graph {
     uint32_t* d_ic_in_thr = nullptr; // IC: threshold per in-arc
     int64_t ic_in_m = 0;             // IC: in-arcs (arcs whose threshold is not 0)
     double ic_pbar = 0.0;            // IC: mean firing probability of those arcs
+    double ic_growth = 0.0;          // IC: live out-arcs of the target of a live arc, on average
     uint64_t* d_lvl = nullptr;       // IC grid shape: per level frontier out-arcs [cap], full-pair in-arcs [cap]
     uint32_t* d_lvl_dir = nullptr;   // IC grid shape: direction of each level [cap]
     uint32_t* d_in_src32 = nullptr;  // source per in-arc (uniform-weight form)
@@ -124,6 +127,8 @@ struct ims_graph {
     Buf A, N[3], Q[3], aux, thp, Anm, nmark;
     // sets mode (ims_simulate_sets): per-slot state
     Buf sA, sN, sQ[3], sact, sstamp, ssteps, sets_dev;
+    // drawn-coins form: coin rows, their ranks, live graphs, base bitmaps, work lists and their counters, reached-node lists
+    Buf live_rows, live_rank, live_loff, live_list, live_base, live_todo, live_ctl, live_queue;
     imsim::BatchItem* d_item = nullptr;  // the single-run slot form's item
     // Per-call host data (seed lists, set lists, the slot item) reaches the
     // device from pinned staging memory owned by the handle: such a copy
@@ -172,8 +177,10 @@ struct ims_graph {
         release(thp);
         release(Anm);
         for (Buf* b : {&sA, &sN, &sQ[0], &sQ[1], &sQ[2], &sact, &sstamp, &ssteps, &sets_dev}) release(*b);
+        for (Buf* b : {&live_rows, &live_rank, &live_loff, &live_list, &live_base, &live_todo, &live_ctl, &live_queue}) release(*b);
         dev_free(d_item);
         dev_free(d_off);
+        dev_free(d_off32);
         dev_free(d_idx);
         dev_free(d_thr);
         dev_free(d_in_off);
@@ -359,6 +366,10 @@ int ims_graph_create(int64_t n, int64_t m, const int64_t* offsets, const uint32_
         if ((rc = dev_alloc(&g->d_thr, (uint64_t)m))) return bail(rc);
         if (m > 0 && hipMemcpy(g->d_thr, param, sizeof(uint32_t) * m, hipMemcpyHostToDevice) != hipSuccess)
             return bail(fail(IMS_E_HIP, "threshold upload failed"));
+        const std::vector<uint32_t> off32(offsets, offsets + n + 1);
+        if ((rc = dev_alloc(&g->d_off32, off32.size()))) return bail(rc);
+        if (hipMemcpy(g->d_off32, off32.data(), sizeof(uint32_t) * off32.size(), hipMemcpyHostToDevice) != hipSuccess)
+            return bail(fail(IMS_E_HIP, "graph upload failed"));
         // pull side: per node its in-arcs with their out-CSR ids (plan.hpp)
         imsim_plan::IcInCsr ic_in;
         imsim_plan::build_ic_in_csr(n, m, offsets, indices, (const uint32_t*)param, ic_in);
@@ -367,9 +378,20 @@ int ims_graph_create(int64_t n, int64_t m, const int64_t* offsets, const uint32_
         const std::vector<uint32_t>& ithr = ic_in.thr;
         const int64_t mi = ioff[n];
         g->ic_in_m = mi;
-        double psum = 0.0;
-        for (int64_t k = 0; k < mi; ++k) psum += ithr[k] == 0xFFFFFFFFu ? 1.0 : std::ldexp((double)ithr[k], -32);
+        double psum = 0.0, grown = 0.0;
+        const uint32_t* thr = (const uint32_t*)param;
+        std::vector<double> live_out((size_t)n, 0.0);
+        auto prob = [](uint32_t t) { return t == 0xFFFFFFFFu ? 1.0 : (double)t * 0x1p-32; };
+        for (int64_t u = 0; u < n; ++u)
+            for (int64_t e = offsets[u]; e < offsets[u + 1]; ++e) live_out[(size_t)u] += prob(thr[e]);
+        for (int64_t v = 0; v < n; ++v) {
+            double p = 0.0;
+            for (int64_t k = ioff[v]; k < ioff[v + 1]; ++k) p += prob(ithr[k]);
+            psum += p;
+            grown += p * live_out[(size_t)v];
+        }
         g->ic_pbar = mi > 0 ? psum / (double)mi : 0.0;
+        g->ic_growth = psum > 0.0 ? grown / psum : 0.0;
         if ((rc = dev_alloc(&g->d_in_off, (uint64_t)n + 1)) || (rc = dev_alloc(&g->d_ic_in, (uint64_t)mi)) ||
             (rc = dev_alloc(&g->d_ic_in_thr, (uint64_t)mi)))
             return bail(rc);
@@ -959,6 +981,139 @@ int ims_simulate_levels(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, u
 
 namespace {
 
+// Device bytes the coin rows and the work lists of one trial range may take.
+// Largest graph of the drawn-coins form (its visited bitmap is 32 KB of LDS).
+constexpr uint64_t kLiveNodes = 1u << 18;
+constexpr uint64_t kLiveRowBudget = 1ull << 32, kLiveTodoBudget = 1ull << 29;
+
+// Whether a many-sets call takes the drawn-coins form.  It draws every arc's
+// coin once, m * T / 8 hash blocks at about 150 a nanosecond; the tasks draw
+// the coins of the arcs their cascades meet, set by set, at least those of
+// the seeds' out-arcs in every trial, and where the target of a live arc has
+// about one live out-arc or more a cascade goes on to meet many times that (it
+// is heavy tailed: on the 200k-node weighted-cascade graph at 1,000 trials the forms
+// break even at about 100 random single nodes, m / 2,000 seed out-arcs; one
+// hub already takes 1.7 against 4.4 ms, a set of 25 nodes 2.4 against 21).
+// Below that the factor is the geometric sum of that growth times what a
+// dense draw gains per block.  Draws of up to 20 us always pay but for
+// single-set calls (5,000 nodes: 0.28 against 0.17 ms for one node).
+// Sets on top of a base meet an unknown part of their arcs.  The measured
+// times there (graphs of 5,000 to 200,000 nodes with weighted-cascade
+// probabilities, 100 to 10,000 trials, 1 to 128 hubs on bases of 3 to 20) are
+// about 250 us + the draw + 2.5 ns per (trial, set) for the drawn-coins form,
+// and for the tasks at least 150 us + 15 ns per node (one task's chain of
+// steps) and 50 times the draw of the sets' own out-arcs; growth above 2
+// leaves little outside the base (0.07 ms for the tasks), below 0.8 little at
+// all.
+bool live_sets_pay(const ims_graph* g, bool base, const std::vector<uint32_t>& off, const std::vector<uint32_t>& nodes, uint32_t n_trials)
+{
+    // (64 trials' coin rows and work lists stay within about 4 GB)
+    if ((uint64_t)g->n > kLiveNodes || g->n == 0 || g->m > (1ll << 29) || off.size() > (1u << 24)) return false;
+    uint64_t arcs = 0;
+    for (uint32_t v : nodes) arcs += (uint64_t)(g->h_off[v + 1] - g->h_off[v]);
+    const double blocks = (double)((n_trials + 7) / 8);
+    const double draw = (double)g->m * blocks / 150e3;  // us
+    if (base) {
+        const double live = 250.0 + draw + 0.0025 * (double)n_trials * (double)(off.size() - 1);
+        const double tasks = std::max(150.0 + 0.015 * (double)g->n, 50.0 * (double)arcs * blocks / 150e3);
+        return g->ic_growth >= 0.8 && g->ic_growth <= 2.0 && live < tasks;
+    }
+    const double reach = g->ic_growth >= 0.8 ? 2000.0 : 8.0 / (1.0 - g->ic_growth);
+    return (double)arcs * reach >= (double)g->m || (draw <= 20.0 && off.size() > 8);
+}
+
+// Many seed sets in the drawn-coins form: trials in ranges whose coin rows
+// and work lists fit the budgets, three or four launches per range.
+// h_off / d_off / d_nodes: the sets, offsets on the host too; totals and node_counts are cleared.
+int simulate_sets_live(ims_graph* g, const uint64_t* base, const uint32_t* h_off, const uint32_t* d_off, const uint32_t* d_nodes, uint32_t n_sets,
+                       uint32_t n_trials, uint64_t rng_seed, uint64_t* totals, uint32_t* node_counts, hipStream_t s)
+{
+    using namespace imsim;
+    const uint64_t n = (uint64_t)g->n, m = (uint64_t)g->m;
+    const uint64_t row_words = ((m + 511) / 512) * 8, bm_words = 2 * ((n + 63) / 64);
+    // Packing the live arcs pays once enough large cascades walk them (200k
+    // nodes, 1,000 trials: 1.3 ms for packing; 128 sets of up to 50 nodes
+    // then take 9.7 instead of 16.2 ms, 0.05 ms a set; 4,096 single nodes 2.7
+    // instead of 3.2, 64 marginal ones no less)
+    uint32_t large = 0;
+    for (uint32_t i = 0; i < n_sets; ++i) large += h_off[i + 1] - h_off[i] > kTinySeeds ? 1u : 0u;
+    const bool packed = large >= 32 && m <= (1ull << 24);
+    // live arcs of one trial: the mean, sixteen standard deviations and a little more, at most all
+    const double mean = g->ic_pbar * (double)g->ic_in_m;
+    const uint64_t list_cap = packed ? std::min<uint64_t>(m, (uint64_t)(mean + 16.0 * std::sqrt(mean)) + 256) : 0;
+    const uint64_t row_bytes = row_words * 8 + (packed ? row_words * 4 + (n + 1) * 4 + list_cap * 4 : 0) + (base ? bm_words * 4 : 0) + 1;
+    uint64_t tc = std::min<uint64_t>(kLiveRowBudget / row_bytes, kLiveTodoBudget / (4ull * n_sets)) / 64 * 64;
+    tc = std::min<uint64_t>(std::max<uint64_t>(tc, 64), ((uint64_t)n_trials + 63) / 64 * 64);
+    int rc;
+    // wavefronts per cascade: four where the bitmaps leave room for few
+    // workgroups (200k nodes, six per compute unit: 128 mixed sets 38 / 26 /
+    // 20 / 24 ms with 1 / 2 / 4 / 8) or the cascades are fewer than one-wave
+    // workgroups would fill; one otherwise (30k nodes, 64 mixed sets: 2.4
+    // against 3.4 ms)
+    const uint32_t kw = n >= 65536 || (uint64_t)n_sets * n_trials < 8192 ? 4 : 1;
+    auto reach = packed ? (kw == 4 ? live_reach_kernel<4, true> : live_reach_kernel<1, true>)
+                        : (kw == 4 ? live_reach_kernel<4, false> : live_reach_kernel<1, false>);
+    auto tiny_k = packed ? live_tiny_kernel<true> : live_tiny_kernel<false>;
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reach, 64 * kw, bm_words * 4) != hipSuccess || per_cu < 1) {
+        (void)hipGetLastError();
+        per_cu = 1;
+    }
+    const uint32_t blocks = (uint32_t)std::min<uint64_t>((uint64_t)g->cus * std::min<uint32_t>((uint32_t)per_cu, 32 / kw), (uint64_t)n_sets * tc);
+    if ((rc = ensure_buf(g, g->live_rows, tc * row_words * 8, false)) ||
+        (packed && ((rc = ensure_buf(g, g->live_rank, tc * row_words * 4, false)) || (rc = ensure_buf(g, g->live_loff, tc * (n + 1) * 4, false)) ||
+                    (rc = ensure_buf(g, g->live_list, tc * list_cap * 4, false)))) ||
+        (base && (rc = ensure_buf(g, g->live_base, tc * bm_words * 4, false))) ||
+        (rc = ensure_buf(g, g->live_todo, tc * n_sets * 4, false)) || (rc = ensure_buf(g, g->live_ctl, (2 * kLiveQueues * kCtlStep + tc) * 4, false)) ||
+        (rc = ensure_buf(g, g->live_queue, (uint64_t)blocks * std::max<uint64_t>(n, 1) * 4, false)))
+        return rc;
+    LiveParams L;
+    L.n = n;
+    L.off = g->d_off32;
+    L.idx = g->d_idx;
+    L.m = m;
+    L.rows = (uint64_t*)g->live_rows.p;
+    L.rank = (uint32_t*)g->live_rank.p;
+    L.loff = (uint32_t*)g->live_loff.p;
+    L.llist = (uint32_t*)g->live_list.p;
+    L.list_cap = list_cap;
+    L.row_words = row_words;
+    L.T = n_trials;
+    L.set_off = d_off;
+    L.set_nodes = d_nodes;
+    L.n_sets = n_sets;
+    L.base = base ? (const uint32_t*)g->live_base.p : nullptr;
+    L.todo = (uint32_t*)g->live_todo.p;
+    L.taken = (uint32_t*)g->live_ctl.p;
+    L.entries = L.taken + kLiveQueues * kCtlStep;
+    L.todo_count = L.entries + kLiveQueues * kCtlStep;
+    L.take = base ? 4 : 1;  // a base bitmap is loaded once for neighbouring entries of a trial
+    L.queue = (uint32_t*)g->live_queue.p;
+    L.totals = totals;
+    L.set_node_counts = node_counts;
+    L.status = g->d_status;
+    for (uint32_t t0 = 0; t0 < n_trials; t0 += (uint32_t)tc) {
+        L.t0 = t0;
+        L.tc = std::min<uint32_t>((uint32_t)tc, n_trials - t0);
+        const uint64_t words = (L.tc + 63) / 64;
+        if ((rc = fill_async<uint32_t>(L.taken, 2 * kLiveQueues * kCtlStep + L.tc, 0u, s))) return rc;
+        const uint64_t draw_waves = row_words / 8 * words;
+        if (draw_waves > 0)
+            hipLaunchKernelGGL(live_draw_kernel, dim3((unsigned)((draw_waves + kWaves - 1) / kWaves)), dim3(kBlock), 0, s, L.rows, row_words,
+                               (const uint32_t*)g->d_thr, m, t0, L.tc, rng_seed);
+        if (packed) hipLaunchKernelGGL(live_pack_kernel, dim3(L.tc), dim3(kPackBlock), 0, s, L);
+        const uint64_t base_waves = bm_words / 2 * words;
+        if (base && base_waves > 0)
+            hipLaunchKernelGGL(live_base_kernel, dim3((unsigned)((base_waves + kWaves - 1) / kWaves)), dim3(kBlock), 0, s, base, n, t0, L.tc,
+                               (uint32_t*)g->live_base.p, bm_words);
+        const uint64_t tiny = (uint64_t)kLiveQueues * ((L.tc + kLiveQueues - 1) / kLiveQueues) * ((n_sets + kBlock - 1) / kBlock);
+        hipLaunchKernelGGL(tiny_k, dim3((unsigned)tiny), dim3(kBlock), 0, s, L);
+        hipLaunchKernelGGL(reach, dim3(blocks), dim3(64 * kw), bm_words * 4, s, L);
+        IMS_HIP(hipGetLastError());
+    }
+    return IMS_OK;
+}
+
 // Many seed sets under one trial range (common random numbers); with `base`
 // the sets start from that word-major state and count new activations only.
 int simulate_sets_impl(ims_graph* g, const uint64_t* base, const uint32_t* set_offsets, const uint32_t* set_nodes, uint32_t n_sets,
@@ -993,6 +1148,23 @@ int simulate_sets_impl(ims_graph* g, const uint64_t* base, const uint32_t* set_o
         off.push_back((uint32_t)nodes.size());
     }
     const uint64_t n = (uint64_t)g->n;
+    const uint64_t set_bytes = (off.size() + nodes.size()) * sizeof(uint32_t);
+    if ((rc = ensure_buf(g, g->sets_dev, set_bytes, false))) return rc;
+    uint32_t* d_off = (uint32_t*)g->sets_dev.p;
+    uint32_t* d_nodes = d_off + off.size();
+    if ((rc = stage_upload(g->st_setoff, d_off, off.data(), off.size() * sizeof(uint32_t), s))) return rc;
+    if ((rc = stage_upload(g->st_setnodes, d_nodes, nodes.data(), nodes.size() * sizeof(uint32_t), s))) return rc;
+    if (!g->h_flag) IMS_HIP(hipHostMalloc((void**)&g->h_flag, 4 * sizeof(uint32_t), hipHostMallocDefault));
+    if ((rc = fill_async<uint32_t>(g->d_status, 4, 0u, s))) return rc;
+    if ((rc = fill_async<unsigned long long>((unsigned long long*)totals, n_sets, 0ull, s))) return rc;
+    if (node_counts && (rc = fill_async<uint32_t>(node_counts, (uint64_t)n_sets * n, 0u, s))) return rc;
+    // options that shape the word-local tasks keep them
+    const bool tasks_asked = opts && (opts->shape || opts->blocks_per_cu || opts->ic_alpha != 0.0 || opts->ic_beta != 0.0 || opts->ic_direction);
+    const bool live_forced = opts && (opts->test_flags & 16) && n > 0 && n <= kLiveNodes;
+    if (g->model == IMS_MODEL_IC && !tasks_asked &&
+        (live_forced || live_sets_pay(g, base != nullptr, off, nodes, n_trials)))
+        return simulate_sets_live(g, base, off.data(), d_off, d_nodes, n_sets, n_trials, rng_seed, totals, node_counts, s);
+
     const uint64_t tasks = (uint64_t)n_sets * W;
     const int per_cu = opts && opts->blocks_per_cu > 0 ? opts->blocks_per_cu : 2;
     const uint64_t slots = std::min<uint64_t>(tasks, (uint64_t)g->cus * per_cu);
@@ -1011,13 +1183,6 @@ int simulate_sets_impl(ims_graph* g, const uint64_t* base, const uint32_t* set_o
         if ((rc = ensure_buf(g, g->ssteps, slots * 4, false))) return rc;
     }
     if (g->sA.bytes + g->sN.bytes + g->sstamp.bytes + g->ssteps.bytes != before) g->sets_zero_dirty = true;
-    const uint64_t set_bytes = (off.size() + nodes.size()) * sizeof(uint32_t);
-    if ((rc = ensure_buf(g, g->sets_dev, set_bytes, false))) return rc;
-    uint32_t* d_off = (uint32_t*)g->sets_dev.p;
-    uint32_t* d_nodes = d_off + off.size();
-    if ((rc = stage_upload(g->st_setoff, d_off, off.data(), off.size() * sizeof(uint32_t), s))) return rc;
-    if ((rc = stage_upload(g->st_setnodes, d_nodes, nodes.data(), nodes.size() * sizeof(uint32_t), s))) return rc;
-
     // slot state starts clear: fresh buffers are cleared once, and every task
     // clears what it touched (the rows of the nodes it activated, its next-
     // step masks; stamps only grow)
@@ -1026,10 +1191,6 @@ int simulate_sets_impl(ims_graph* g, const uint64_t* base, const uint32_t* set_o
             if (b->p && (rc = fill_async<uint8_t>((uint8_t*)b->p, b->bytes, 0, s))) return rc;
         g->sets_zero_dirty = false;
     }
-    if (!g->h_flag) IMS_HIP(hipHostMalloc((void**)&g->h_flag, 4 * sizeof(uint32_t), hipHostMallocDefault));
-    if ((rc = fill_async<uint32_t>(g->d_status, 4, 0u, s))) return rc;
-    if ((rc = fill_async<unsigned long long>((unsigned long long*)totals, n_sets, 0ull, s))) return rc;
-    if (node_counts && (rc = fill_async<uint32_t>(node_counts, (uint64_t)n_sets * n, 0u, s))) return rc;
 
     imsim::SimParams P;
     std::memset(&P, 0, sizeof P);

@@ -530,6 +530,121 @@ int set_ic_direction(imsim::SimParams& P, const ims_graph* g, double alpha, doub
     return IMS_OK;
 }
 
+// Device bytes the coin rows and the work lists of one trial range may take.
+// Largest graph of the drawn-coins form (its visited bitmap is 32 KB of LDS).
+constexpr uint64_t kLiveNodes = 1u << 18;
+constexpr uint64_t kLiveRowBudget = 1ull << 32, kLiveTodoBudget = 1ull << 29;
+
+int prof_begin(ims_graph* g, hipStream_t s)
+{
+    for (int k = 0; k < 2; ++k)
+        if (!g->prof_ev[2 * g->prof_count + k]) IMS_HIP(hipEventCreate(&g->prof_ev[2 * g->prof_count + k]));
+    IMS_HIP(hipEventRecord(g->prof_ev[2 * g->prof_count], s));
+    return IMS_OK;
+}
+
+int prof_end(ims_graph* g, hipStream_t s)
+{
+    IMS_HIP(hipEventRecord(g->prof_ev[2 * g->prof_count + 1], s));
+    ++g->prof_count;
+    return IMS_OK;
+}
+
+// Whether a one-set run takes the drawn-coins form.  It draws all m * T coins
+// (`draw`, us) where the other forms draw those of the arcs they meet, so it
+// pays unless the cascades stay in a small part of the graph; growth (live
+// out-arcs of the target of a live arc) tells how far they go.  Measured on
+// Erdos-Renyi, preferential-attachment and small-world graphs of 500 to
+// 100,000 nodes, 64 to 10,000 trials, probabilities 0.01 to 0.1, TV, UR, WC:
+// - growth below 0.7: the other forms end in 60 to 130 us; this one takes
+//   55 us + draw + 10 ns per trial.  Level counts cost the others 0.2 ms.
+// - up to 1.3: 1.1 to 3x faster up to a draw of 110 us (20,000-node ring, WC,
+//   300 trials 0.114 against 0.178 ms; 1,000 trials, draw 167 us, 0.24
+//   against 0.18).  Level counts: 2 to 12x at every size tried.
+// - up to 2: 2 to 4x faster up to a draw of 400 us, slower from about 650.
+// - above: 1.5 to 13x faster at every size tried, but for skewed graphs with
+//   many live arcs per node, whose pull steps end early: there only with
+//   fewer than 20,000 nodes and 4,000 trials (3,000-node preferential
+//   attachment, UR, 4,000 trials 1.24 against 0.77 ms; 300 trials 0.24
+//   against 0.49).
+bool live_single_pays(const ims_graph* g, uint32_t n_trials, bool levels)
+{
+    const double n = (double)g->n, growth = g->ic_growth;
+    const double draw = (double)g->m * (double)((n_trials + 7) / 8) / 150e3;
+    // (64 trials' coin rows stay within about 4 GB)
+    if ((uint64_t)g->n > kLiveNodes || g->n == 0 || g->m > (1ll << 29)) return false;
+    if (growth < 0.7) return levels ? draw <= 80.0 : draw + 0.01 * (double)n_trials <= 2.0;
+    if (growth < 1.3) return draw <= (levels ? 2000.0 : 110.0);
+    if (levels) return true;
+    if (growth < 2.0) return draw <= 400.0;
+    const double live_degree = g->ic_pbar * (double)g->ic_in_m / n;
+    if (live_degree >= 3.0 && growth >= 1.5 * live_degree) return n < 20000.0 && n_trials < 4000;
+    return true;
+}
+
+// One seed set (sorted, distinct: sv) in the drawn-coins form: coin rows,
+// one cascade per trial, then the per-node outputs.
+int simulate_live(ims_graph* g, const std::vector<uint32_t>& sv, uint32_t n_trials, uint64_t rng_seed, uint32_t* trial_counts,
+                  uint32_t* node_counts, uint64_t* total, uint64_t* active_bits, uint32_t* level_counts, uint32_t max_levels, hipStream_t s)
+{
+    using namespace imsim;
+    const uint64_t n = (uint64_t)g->n, m = (uint64_t)g->m;
+    const uint64_t row_words = std::max<uint64_t>((m + 511) / 512, 1) * 8, bm_words = 2 * ((n + 63) / 64);
+    const bool nodes = node_counts || active_bits;
+    // wavefronts per cascade: the fewer the trials, the more (20,000-node
+    // Erdos-Renyi, UR, 64 trials: 1.02 / 0.37 / 0.23 ms with 1 / 4 / 8; 1,000-
+    // node, 10,000 trials: one is fastest)
+    const uint32_t kw = n_trials >= 4096 && n < 65536 ? 1 : n_trials > 512 ? 4 : n_trials > 256 || n < 20000 ? 8 : 16;
+    auto single = kw == 1 ? live_single_kernel<1> : kw == 4 ? live_single_kernel<4> : kw == 8 ? live_single_kernel<8> : live_single_kernel<16>;
+    const uint64_t slots = std::min<uint64_t>(n_trials, (uint64_t)g->cus * 32 / kw);
+    const uint64_t row_bytes = row_words * 8 + (nodes ? bm_words * 4 : 0);
+    uint64_t tc = kLiveRowBudget / row_bytes / 64 * 64;
+    tc = std::min<uint64_t>(std::max<uint64_t>(tc, 64), ((uint64_t)n_trials + 63) / 64 * 64);
+    int rc;
+    if ((rc = ensure_buf(g, g->live_rows, tc * row_words * 8, false)) || (rc = ensure_buf(g, g->live_queue, slots * n * 4, false)) ||
+        (nodes && (rc = ensure_buf(g, g->live_base, tc * bm_words * 4, false))))
+        return rc;
+    LiveSeeds S;
+    S.count = (uint32_t)sv.size();
+    S.more = nullptr;
+    if (sv.size() <= kArgSeeds) {
+        std::copy(sv.begin(), sv.end(), S.v);
+    } else {
+        if ((rc = ensure_buf(g, g->sets_dev, sv.size() * 4, false)) ||
+            (rc = stage_upload(g->st_setnodes, g->sets_dev.p, sv.data(), sv.size() * 4, s)))
+            return rc;
+        S.more = (const uint32_t*)g->sets_dev.p;
+    }
+    LiveParams L;
+    std::memset(&L, 0, sizeof L);
+    L.n = n;
+    L.off = g->d_off32;
+    L.idx = g->d_idx;
+    L.m = m;
+    L.rows = (uint64_t*)g->live_rows.p;
+    L.row_words = row_words;
+    L.T = n_trials;
+    L.queue = (uint32_t*)g->live_queue.p;
+    L.status = g->d_status;
+    uint32_t* bitmaps = nodes ? (uint32_t*)g->live_base.p : nullptr;
+    for (uint32_t t0 = 0; t0 < n_trials; t0 += (uint32_t)tc) {
+        L.t0 = t0;
+        L.tc = std::min<uint32_t>((uint32_t)tc, n_trials - t0);
+        const uint64_t draw_waves = row_words / 8 * ((L.tc + 63) / 64);
+        hipLaunchKernelGGL(live_draw_kernel, dim3((unsigned)((draw_waves + kWaves - 1) / kWaves)), dim3(kBlock), 0, s,
+                           t0 == 0 ? LiveClear{g->d_status, total, node_counts, n} : LiveClear{}, L.rows, row_words, (const uint32_t*)g->d_thr, m, t0, L.tc,
+                           rng_seed);
+        hipLaunchKernelGGL(single, dim3((unsigned)std::min<uint64_t>(slots, L.tc)), dim3(64 * kw), bm_words * 4, s, L, S, bitmaps, trial_counts, total, level_counts,
+                           max_levels);
+        if (nodes)
+            hipLaunchKernelGGL(live_nodes_kernel, dim3((unsigned)(bm_words / 2), (L.tc + 64 * kNodeWords - 1) / (64 * kNodeWords)), dim3(kBlock), 0, s,
+                               (const uint32_t*)bitmaps, bm_words, n,
+                               t0, L.tc, node_counts, active_bits);
+        IMS_HIP(hipGetLastError());
+    }
+    return IMS_OK;
+}
+
 // One simulation; with level_counts the word-local shape also counts the
 // nodes first activated at every level of every trial.
 int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_t n_trials, uint64_t rng_seed,
@@ -587,6 +702,18 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
             const double offspring = n > 0 ? g->ic_pbar * (double)g->ic_in_m / (double)n : 0.0;
             shape = (offspring <= 1.05 && reach <= 10000.0) || (n <= 5000 && offspring <= 2.5) ? 1 : 2;
         }
+    }
+    // options that shape the other forms keep them
+    const bool form_asked = opts && (opts->shape || opts->blocks_per_cu || opts->ic_alpha != 0.0 || opts->ic_beta != 0.0 || opts->ic_direction);
+    const bool live_forced = opts && (opts->test_flags & 16) && n > 0 && n <= kLiveNodes;
+    if (g->model == IMS_MODEL_IC && !form_asked && (live_forced || live_single_pays(g, n_trials, level_counts != nullptr))) {
+        const bool timed = opts && opts->profile && g->prof_count < ims_graph::kProf;
+        if (timed && (rc = prof_begin(g, s))) return rc;
+        if ((rc = simulate_live(g, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, level_counts, max_levels, s)))
+            return rc;
+        if (timed && (rc = prof_end(g, s))) return rc;
+        g->last_shape = 1;
+        return IMS_OK;
     }
     if (level_counts) shape = 1;  // levels are the word-local (synchronous) steps
     if (shape != 1 && shape != 2) return fail(IMS_E_INVALID_ARG, "ims_simulate: unknown shape %d", shape);
@@ -780,12 +907,7 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
         return rc;
 
     const bool prof = opts && opts->profile && g->prof_count < ims_graph::kProf;
-    const uint32_t slot = g->prof_count;
-    if (prof) {
-        for (int k = 0; k < 2; ++k)
-            if (!g->prof_ev[2 * slot + k]) IMS_HIP(hipEventCreate(&g->prof_ev[2 * slot + k]));
-        IMS_HIP(hipEventRecord(g->prof_ev[2 * slot], s));
-    }
+    if (prof && (rc = prof_begin(g, s))) return rc;
     if (slot_run) {
         if (node_counts && (rc = fill_async<uint32_t>(node_counts, n, 0u, s))) return rc;
         imsim::BatchItem it;
@@ -934,10 +1056,7 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
         IMS_HIP(hipEventRecord(g->status_read, s));
         g->status_pending = true;
     }
-    if (prof) {
-        IMS_HIP(hipEventRecord(g->prof_ev[2 * slot + 1], s));
-        g->prof_count = slot + 1;
-    }
+    if (prof && (rc = prof_end(g, s))) return rc;
     g->last_shape = (uint32_t)shape;
 
     if (n > 0 && !(ltg && cells > 0) && !slot_run) {
@@ -980,11 +1099,6 @@ int ims_simulate_levels(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, u
 }  // extern "C"
 
 namespace {
-
-// Device bytes the coin rows and the work lists of one trial range may take.
-// Largest graph of the drawn-coins form (its visited bitmap is 32 KB of LDS).
-constexpr uint64_t kLiveNodes = 1u << 18;
-constexpr uint64_t kLiveRowBudget = 1ull << 32, kLiveTodoBudget = 1ull << 29;
 
 // Whether a many-sets call takes the drawn-coins form.  It draws every arc's
 // coin once, m * T / 8 hash blocks at about 150 a nanosecond; the tasks draw
@@ -1099,7 +1213,7 @@ int simulate_sets_live(ims_graph* g, const uint64_t* base, const uint32_t* h_off
         if ((rc = fill_async<uint32_t>(L.taken, 2 * kLiveQueues * kCtlStep + L.tc, 0u, s))) return rc;
         const uint64_t draw_waves = row_words / 8 * words;
         if (draw_waves > 0)
-            hipLaunchKernelGGL(live_draw_kernel, dim3((unsigned)((draw_waves + kWaves - 1) / kWaves)), dim3(kBlock), 0, s, L.rows, row_words,
+            hipLaunchKernelGGL(live_draw_kernel, dim3((unsigned)((draw_waves + kWaves - 1) / kWaves)), dim3(kBlock), 0, s, LiveClear{}, L.rows, row_words,
                                (const uint32_t*)g->d_thr, m, t0, L.tc, rng_seed);
         if (packed) hipLaunchKernelGGL(live_pack_kernel, dim3(L.tc), dim3(kPackBlock), 0, s, L);
         const uint64_t base_waves = bm_words / 2 * words;

@@ -136,10 +136,23 @@ __device__ __forceinline__ Block4 philox_group(const PhiloxArc& a, uint64_t grou
 // 64-arc piece of that trial's row as it stands (no transpose); lane t keeps
 // trial t's eight pieces and stores them as one 64-byte line.  Bound by the
 // hash arithmetic.
-__global__ __launch_bounds__(kBlock) void live_draw_kernel(uint64_t* __restrict__ rows, uint64_t row_words, const uint32_t* __restrict__ thr,
+// `C` names outputs to zero here for the kernels that follow (status null: none).
+struct LiveClear {
+    uint32_t* status;       // four words
+    uint64_t* total;        // one
+    uint32_t* node_counts;  // [n] or null
+    uint64_t n;
+};
+__global__ __launch_bounds__(kBlock) void live_draw_kernel(LiveClear C, uint64_t* __restrict__ rows, uint64_t row_words, const uint32_t* __restrict__ thr,
                                                            uint64_t m, uint32_t t0, uint32_t tc, uint64_t seed)
 {
     const uint32_t lane = threadIdx.x & 63u;
+    if (C.status) {
+        if (blockIdx.x == 0 && threadIdx.x < 4) C.status[threadIdx.x] = 0;
+        if (blockIdx.x == 0 && threadIdx.x == 4) *C.total = 0;
+        if (C.node_counts)
+            for (uint64_t v = (uint64_t)blockIdx.x * kBlock + threadIdx.x; v < C.n; v += (uint64_t)gridDim.x * kBlock) C.node_counts[v] = 0;
+    }
     const uint64_t wave = uniform64(((uint64_t)blockIdx.x * kBlock + threadIdx.x) >> 6);
     const uint64_t blocks8 = row_words / 8;
     const uint64_t words = (tc + 63) / 64;
@@ -647,6 +660,82 @@ __global__ __launch_bounds__(64 * kW) void live_reach_kernel(LiveParams L)
         }
     }
     if (threadIdx.x == 0 && max_steps) atomicMax(&L.status[0], max_steps);
+}
+
+// Seeds of a single-set run, passed with the launch when they fit.
+constexpr uint32_t kArgSeeds = 256;
+struct LiveSeeds {
+    uint32_t count;
+    const uint32_t* more;  // the seeds in device memory when there are more than kArgSeeds, else null
+    uint32_t v[kArgSeeds];
+};
+
+// One seed set over every trial of a range: workgroups run the trials t0 + b,
+// t0 + b + gridDim.x, ... over their coin rows and leave the final bitmaps for
+// live_nodes_kernel.
+template <int kW>
+__global__ __launch_bounds__(64 * kW) void live_single_kernel(LiveParams L, LiveSeeds S, uint32_t* __restrict__ bitmaps,
+                                                             uint32_t* __restrict__ trial_counts, uint64_t* __restrict__ total,
+                                                             uint32_t* __restrict__ level_counts, uint32_t max_levels)
+{
+    extern __shared__ uint32_t bm[];  // [2 * ceil(n / 64)]
+    __shared__ LiveShared<kW> sh;
+    const uint32_t bm_words = (uint32_t)(2 * ((L.n + 63) / 64));
+    uint64_t sum = 0;
+    uint32_t max_steps = 0;
+    for (uint32_t row = blockIdx.x; row < L.tc; row += gridDim.x) {
+        const uint32_t t = L.t0 + row;
+        for (uint32_t i = threadIdx.x; i < bm_words; i += 64 * kW) bm[i] = 0;
+        uint32_t steps;
+        const uint32_t cnt = live_cascade<kW, false>(
+            live_graph<false>(L, row), bm, L.queue + (uint64_t)blockIdx.x * L.n, sh, S.count,
+            [&](uint32_t i) { return S.more ? S.more[i] : S.v[i]; },
+            [&](uint32_t l, uint32_t count) {
+                if (level_counts && threadIdx.x == 0 && l < max_levels) level_counts[(uint64_t)l * L.T + t] = count;
+            },
+            steps);
+        if (bitmaps)
+            for (uint32_t i = threadIdx.x; i < bm_words; i += 64 * kW) bitmaps[(uint64_t)row * bm_words + i] = bm[i];
+        if (threadIdx.x == 0) trial_counts[t] = cnt;
+        sum += cnt;
+        max_steps = steps > max_steps ? steps : max_steps;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        if (sum) atomicAdd((unsigned long long*)total, (unsigned long long)sum);
+        if (max_steps > load_relaxed32(&L.status[0])) atomicMax(&L.status[0], max_steps);
+    }
+}
+
+// Per-node counts and word-major bits from the trials' bitmaps: a workgroup
+// takes 64 nodes and kNodeWords words of 64 trials, a wavefront every
+// kWaves-th of them (lane = trial, then, transposed, lane = node).
+// node_counts were cleared by the draw of the first range.
+constexpr uint32_t kNodeWords = 16;
+__global__ __launch_bounds__(kBlock) void live_nodes_kernel(const uint32_t* __restrict__ bitmaps, uint64_t bm_words, uint64_t n, uint32_t t0,
+                                                            uint32_t tc, uint32_t* __restrict__ node_counts, uint64_t* __restrict__ A)
+{
+    __shared__ uint32_t part[kWaves][64];
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    const uint64_t tile = blockIdx.x;
+    const uint64_t v = tile * 64 + lane;
+    uint32_t c = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kNodeWords / kWaves; ++k) {
+        const uint32_t w = blockIdx.y * kNodeWords + kWaves * k + wave;
+        const uint32_t row = 64 * w + lane;
+        uint64_t x = row < tc ? *reinterpret_cast<const uint64_t*>(bitmaps + (uint64_t)row * bm_words + 2 * tile) : 0ull;
+        x = wave_transpose64(x, lane);
+        c += (uint32_t)__popcll(x);
+        if (A && v < n && 64 * w < tc) A[((uint64_t)t0 / 64 + w) * n + v] = x;
+    }
+    part[wave][lane] = c;
+    __syncthreads();
+    if (wave == 0 && v < n && node_counts) {
+#pragma unroll
+        for (int q = 1; q < kWaves; ++q) c += part[q][lane];
+        if (c) atomicAdd(&node_counts[v], c);
+    }
 }
 
 }  // namespace imsim

@@ -91,3 +91,40 @@ def test_drawn_coin_sets_match_the_oracle(ims, n, m, trials, p, count, most, hub
     assert (again["new_totals" if based else "totals"] == totals).all()
     assert a == G.last_status()
     G.close()
+
+
+@pytest.mark.parametrize("n,m,trials,p,seeds,hub", [
+    (31, 40, 1, 0.3, 2, 0),
+    (32, 64, 7, 0.3, 3, 0),
+    (65, 513, 64, "mixed", 4, 65),
+    (700, 3000, 65, 0.3, 1, 600),
+    (700, 3000, 300, "one", 300, 600),      # more seeds than travel with the launch; eight wavefronts per cascade
+    (700, 3000, 513, 0.1, 0, 600),          # no seed; four wavefronts
+    (700, 3000, 1100, "mixed", 256, 600),   # two blocks of words in the node counts
+    (3000, 30000, 70, 0.3, 10, 2500),
+    (20000, 60000, 65, 0.5, 5, 9000),       # sixteen wavefronts
+    (129, 700, 4096, 0.2, 3, 100),          # one wavefront
+])
+def test_drawn_coin_run_matches_the_oracle(ims, n, m, trials, p, seeds, hub):
+    rng = np.random.default_rng([n, m, trials, 1])
+    off, idx = graph(n, m, rng, hub)
+    k = idx.size
+    prob = {"mixed": rng.choice([0.0, 0.02, 0.5, 1.0], k), "one": np.ones(k)}.get(p, None)
+    prob = np.full(k, float(p)) if prob is None else prob
+    sd = rng.choice(n, seeds, replace=False).astype(np.uint32)
+    G = ims.Graph(n, off, idx, "ic", prob)
+    ref = oracle.simulate("ic", n, off, idx, oracle.encode("ic", prob), sd, trials, 99)
+    forced = ims.Opts(test_flags=FORCED)
+    for want_bits in (True, False):
+        got = ims.simulate(G, np.concatenate([sd, sd[:2]]), trials, 99, want_bits=want_bits, opts=forced)
+        assert got["total"] == ref["total"]
+        assert (got["trial_counts"].cpu().numpy().view(np.uint32) == ref["trial_counts"]).all()
+        assert (got["node_counts"].cpu().numpy().view(np.uint32) == ref["node_counts"]).all()
+        if want_bits:
+            assert (got["active_bits"].cpu().numpy().view(np.uint64) == ref["active_bits"]).all()
+    # same steps as the grid shape takes; a tasks run on the same handle in between changes nothing
+    grid = ims.simulate(G, sd, trials, 99, opts=ims.Opts(shape=2))
+    assert grid["steps"] == got["steps"]
+    again = ims.simulate(G, sd, trials, 99, opts=forced)
+    assert again["total"] == ref["total"] and (again["node_counts"].cpu().numpy().view(np.uint32) == ref["node_counts"]).all()
+    G.close()

@@ -93,9 +93,11 @@ int ims_graph_info(const ims_graph* g, int64_t* n, int64_t* m, int* model);
 
 /* Simulation options; NULL = automatic.  Any setting gives the same bits. */
 typedef struct ims_opts {
-    int shape;             /* 0 = auto (IC: word-local when the run has at least a quarter as
-                              many 64-trial words as compute units, else grid-wide; LT: grid-
-                              wide), 1 = word-local (a workgroup runs the whole cascade of its
+    int shape;             /* 0 = auto (IC: coins drawn densely, then a workgroup per trial, where
+                              the cascades go far, else word-local when the run has at least a
+                              quarter as many 64-trial words as compute units or they stay small,
+                              else grid-wide; LT: a workgroup per trial where its state fits the
+                              LDS and it pays, else grid-wide), 1 = word-local (a workgroup runs the whole cascade of its
                               trials: of one 64-trial word when active_bits is requested, else of
                               16 trials on persistent slots that add their own counts), 2 = grid-
                               wide steps (one launch per level / sweep) */
@@ -108,7 +110,8 @@ typedef struct ims_opts {
                               threshold table (hashes drawn in the kernel); bit 1 = unused;
                               bit 2 = LT without the equal-in-weights form; bit 3 = LT grid
                               shape with full threshold hashes instead of count thresholds;
-                              bit 4 = IC drawn-coins form whatever the sizes say */
+                              bit 4 = IC drawn-coins form, LT per-trial form
+                              whatever the sizes say */
     /* IC direction (Section 3, "Algorithms", expands the out-arcs of the last
        step's new nodes: the push side).  The pull side instead lets every
        (node, word) pair with an inactive trial scan its in-arcs for frontier

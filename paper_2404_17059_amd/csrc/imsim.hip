@@ -19,6 +19,7 @@
 
 #include "imsim.h"
 #include "live_kernels.hpp"
+#include "lt_trial_kernels.hpp"
 #include "plan.hpp"
 #include "sim_kernels.hpp"
 
@@ -96,7 +97,7 @@ struct ims_graph {
     int cus = 0;
     std::vector<int64_t> h_off;  // host copy of the out-offsets (launch planning)
     int64_t* d_off = nullptr;
-    uint32_t* d_off32 = nullptr;  // IC: the out-offsets in 32 bits (m < 2^32 - 1), for the drawn-coins form
+    uint32_t* d_off32 = nullptr;  // the out-offsets in 32 bits (m < 2^32 - 1), for the per-trial forms
     uint32_t* d_idx = nullptr;
     uint32_t* d_thr = nullptr;
     int64_t* d_in_off = nullptr;     // in-CSR offsets (LT: weight pieces; IC: arcs of nonzero threshold)
@@ -112,6 +113,9 @@ struct ims_graph {
     uint64_t* d_lt_wout = nullptr;   // LT weight per out-arc (push form of the batch's 8-trial tasks)
     uint32_t* d_node_w = nullptr;    // common weight piece per node (uniform-weight form)
     bool lt_uniform = false;
+    bool lt_zero = false;            // some arc has weight 0
+    uint64_t lt_max_in = 0;          // most in-arc pieces of a node
+    uint64_t max_out = 0;            // most out-arcs of a node
     uint32_t* d_kinfo = nullptr;     // per node: low half of its in-CSR offset, first plane in the count table
     uint64_t kplanes_total = 0;      // count-table planes per word summed over the nodes
     uint32_t* d_bfirst = nullptr;    // LT grid shape: first node of each batch
@@ -352,6 +356,7 @@ int ims_graph_create(int64_t n, int64_t m, const int64_t* offsets, const uint32_
     g->m = m;
     g->model = model;
     g->total_chunks = chunks;
+    g->max_out = max_deg;
     g->h_off.assign(offsets, offsets + n + 1);
     auto bail = [&](int code) {
         delete g;
@@ -362,14 +367,14 @@ int ims_graph_create(int64_t n, int64_t m, const int64_t* offsets, const uint32_
     if (hipMemcpy(g->d_off, offsets, sizeof(int64_t) * (n + 1), hipMemcpyHostToDevice) != hipSuccess ||
         (m > 0 && hipMemcpy(g->d_idx, indices, sizeof(uint32_t) * m, hipMemcpyHostToDevice) != hipSuccess))
         return bail(fail(IMS_E_HIP, "graph upload failed"));
+    const std::vector<uint32_t> off32(offsets, offsets + n + 1);
+    if ((rc = dev_alloc(&g->d_off32, off32.size()))) return bail(rc);
+    if (hipMemcpy(g->d_off32, off32.data(), sizeof(uint32_t) * off32.size(), hipMemcpyHostToDevice) != hipSuccess)
+        return bail(fail(IMS_E_HIP, "graph upload failed"));
     if (model == IMS_MODEL_IC) {
         if ((rc = dev_alloc(&g->d_thr, (uint64_t)m))) return bail(rc);
         if (m > 0 && hipMemcpy(g->d_thr, param, sizeof(uint32_t) * m, hipMemcpyHostToDevice) != hipSuccess)
             return bail(fail(IMS_E_HIP, "threshold upload failed"));
-        const std::vector<uint32_t> off32(offsets, offsets + n + 1);
-        if ((rc = dev_alloc(&g->d_off32, off32.size()))) return bail(rc);
-        if (hipMemcpy(g->d_off32, off32.data(), sizeof(uint32_t) * off32.size(), hipMemcpyHostToDevice) != hipSuccess)
-            return bail(fail(IMS_E_HIP, "graph upload failed"));
         // pull side: per node its in-arcs with their out-CSR ids (plan.hpp)
         imsim_plan::IcInCsr ic_in;
         imsim_plan::build_ic_in_csr(n, m, offsets, indices, (const uint32_t*)param, ic_in);
@@ -413,6 +418,8 @@ int ims_graph_create(int64_t n, int64_t m, const int64_t* offsets, const uint32_
         std::vector<uint32_t> node_w, src32;
         const bool uniform = imsim_plan::lt_uniform_form(n, lt_in, node_w, src32);
         g->lt_uniform = uniform;
+        for (int64_t v = 0; v < n; ++v) g->lt_max_in = std::max<uint64_t>(g->lt_max_in, (uint64_t)(in_off[v + 1] - in_off[v]));
+        for (int64_t e = 0; e < m; ++e) g->lt_zero |= ((const uint64_t*)param)[e] == 0;
         if (uniform) {
             std::vector<uint32_t> kinfo;
             g->kplanes_total = imsim_plan::lt_count_planes(n, in_off, kinfo);
@@ -582,6 +589,23 @@ bool live_single_pays(const ims_graph* g, uint32_t n_trials, bool levels)
     return true;
 }
 
+// Seeds as launch arguments, or uploaded when they are too many.
+int live_seeds(ims_graph* g, const std::vector<uint32_t>& sv, imsim::LiveSeeds& S, hipStream_t s)
+{
+    S.count = (uint32_t)sv.size();
+    S.more = nullptr;
+    if (sv.size() <= imsim::kArgSeeds) {
+        std::copy(sv.begin(), sv.end(), S.v);
+        return IMS_OK;
+    }
+    int rc;
+    if ((rc = ensure_buf(g, g->sets_dev, sv.size() * 4, false)) ||
+        (rc = stage_upload(g->st_setnodes, g->sets_dev.p, sv.data(), sv.size() * 4, s)))
+        return rc;
+    S.more = (const uint32_t*)g->sets_dev.p;
+    return IMS_OK;
+}
+
 // One seed set (sorted, distinct: sv) in the drawn-coins form: coin rows,
 // one cascade per trial, then the per-node outputs.
 int simulate_live(ims_graph* g, const std::vector<uint32_t>& sv, uint32_t n_trials, uint64_t rng_seed, uint32_t* trial_counts,
@@ -605,16 +629,7 @@ int simulate_live(ims_graph* g, const std::vector<uint32_t>& sv, uint32_t n_tria
         (nodes && (rc = ensure_buf(g, g->live_base, tc * bm_words * 4, false))))
         return rc;
     LiveSeeds S;
-    S.count = (uint32_t)sv.size();
-    S.more = nullptr;
-    if (sv.size() <= kArgSeeds) {
-        std::copy(sv.begin(), sv.end(), S.v);
-    } else {
-        if ((rc = ensure_buf(g, g->sets_dev, sv.size() * 4, false)) ||
-            (rc = stage_upload(g->st_setnodes, g->sets_dev.p, sv.data(), sv.size() * 4, s)))
-            return rc;
-        S.more = (const uint32_t*)g->sets_dev.p;
-    }
+    if ((rc = live_seeds(g, sv, S, s))) return rc;
     LiveParams L;
     std::memset(&L, 0, sizeof L);
     L.n = n;
@@ -640,6 +655,107 @@ int simulate_live(ims_graph* g, const std::vector<uint32_t>& sv, uint32_t n_tria
             hipLaunchKernelGGL(live_nodes_kernel, dim3((unsigned)(bm_words / 2), (L.tc + 64 * kNodeWords - 1) / (64 * kNodeWords)), dim3(kBlock), 0, s,
                                (const uint32_t*)bitmaps, bm_words, n,
                                t0, L.tc, node_counts, active_bits);
+        IMS_HIP(hipGetLastError());
+    }
+    return IMS_OK;
+}
+
+// Per-trial LT form: element width of a run's states (0: none fits the LDS).
+constexpr uint64_t kLtTrialLds = 160 * 1024 - 12 * 1024;  // what the kernel's own arrays leave of a compute unit's LDS
+uint32_t lt_trial_bits(const ims_graph* g)
+{
+    const uint64_t n = (uint64_t)g->n;
+    const uint32_t bits = !g->lt_uniform || g->lt_zero || g->lt_max_in >= 32767 ? 32 : g->lt_max_in >= 127 ? 16 : 8;
+    return n > 0 && n * bits / 8 + (bits == 32 ? n / 8 : 0) + 64 <= kLtTrialLds ? bits : 0;
+}
+
+// Whether a run takes it.  It touches every arc once per trial, in as many
+// rounds of one workgroup as the cascade has steps; the grid-wide sweeps read
+// everything pending at every step but share it between 64 trials.  Measured
+// (1,000 trials, ms, this against the sweeps; Erdos-Renyi, preferential-
+// attachment and directed power-law graphs of 1,000 to 140,000 nodes, 64 to
+// 4,000 trials): 20,000-node Erdos-Renyi 1.6 / 13.7, preferential attachment
+// 0.6 / 53, power law 0.75 / 1.8.  The sweeps win where a hub holding a
+// notable part of all arcs makes the cascade dense within few steps (and no
+// node has more in-arcs than a sweep stages): with hub seeds above about
+// 200,000 arcs (36,000 nodes 2.2 / 1.55), else above about a million
+// (140,000 nodes, 15 arcs each: 7.6 / 4.4).
+bool lt_trials_pay(const ims_graph* g, const std::vector<uint32_t>& sv)
+{
+    if (g->max_out * 64 < (uint64_t)g->m || g->lt_max_in > 64) return true;
+    uint64_t arcs = 0;
+    for (uint32_t x : sv) arcs += (uint64_t)(g->h_off[x + 1] - g->h_off[x]);
+    return g->m <= (arcs * 16 >= (uint64_t)g->m ? 200000 : 1060000);
+}
+
+// Kernel of a width and wavefront count, allowed the LDS it asks for.
+template <int kBits>
+const void* lt_trial_entry(uint32_t kw)
+{
+    using namespace imsim;
+    return kw == 1 ? (const void*)lt_trial_kernel<kBits, 1> : kw == 4 ? (const void*)lt_trial_kernel<kBits, 4>
+                                                               : (const void*)lt_trial_kernel<kBits, 8>;
+}
+
+// One LT seed set (sorted, distinct: sv) in the per-trial form.
+int simulate_lt_trials(ims_graph* g, uint32_t bits, const std::vector<uint32_t>& sv, uint32_t n_trials, uint64_t rng_seed,
+                       uint32_t* trial_counts, uint32_t* node_counts, uint64_t* total, uint64_t* active_bits, hipStream_t s)
+{
+    using namespace imsim;
+    const uint64_t n = (uint64_t)g->n;
+    const uint64_t stride = (n * bits / 8 + 15) / 16 * 16, bm_words = 2 * ((n + 63) / 64);
+    const bool nodes = node_counts || active_bits;
+    const uint64_t lds = stride + (bits == 32 ? bm_words * 4 : 0);
+    // wavefronts per trial: the fewer trials share a compute unit (by their
+    // number, or by LDS), the more (Erdos-Renyi, 1,000 / 20,000 / 140,000
+    // nodes: 4,000 trials 0.19 / 4.2 ms with one, 0.41 / 3.9 with four; 1,000
+    // trials 26.0 ms with one, 13.3 with four, 12.9 with eight)
+    const uint64_t share = std::min<uint64_t>((160 * 1024) / (lds + 4096), ((uint64_t)n_trials + g->cus - 1) / g->cus);
+    const uint32_t kw = share >= 12 ? 1 : share >= 3 ? 4 : 8;
+    const void* entry = bits == 8 ? lt_trial_entry<8>(kw) : bits == 16 ? lt_trial_entry<16>(kw) : lt_trial_entry<32>(kw);
+    int rc, per_cu = 0;
+    if (lds > 48 * 1024) IMS_HIP(hipFuncSetAttribute(entry, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, entry, (int)(64 * kw), lds) != hipSuccess || per_cu < 1) {
+        (void)hipGetLastError();
+        per_cu = 1;
+    }
+    const uint64_t slots = std::min<uint64_t>(n_trials, (uint64_t)g->cus * (uint32_t)per_cu);
+    uint64_t tc = kLiveRowBudget / (stride + (nodes ? bm_words * 4 : 0)) / 64 * 64;
+    tc = std::min<uint64_t>(std::max<uint64_t>(tc, 64), ((uint64_t)n_trials + 63) / 64 * 64);
+    if ((rc = ensure_buf(g, g->live_rows, tc * stride, false)) || (rc = ensure_buf(g, g->live_queue, slots * n * 4, false)) ||
+        (nodes && (rc = ensure_buf(g, g->live_base, tc * bm_words * 4, false))))
+        return rc;
+    LiveSeeds S;
+    if ((rc = live_seeds(g, sv, S, s))) return rc;
+    LtRun R;
+    std::memset(&R, 0, sizeof R);
+    R.n = n;
+    R.off = g->d_off32;
+    R.idx = g->d_idx;
+    R.wout = g->d_lt_wout;
+    R.in_off = g->d_in_off;
+    R.in_src = g->d_in_src32;
+    R.node_w = g->d_node_w;
+    R.rows = (uint8_t*)g->live_rows.p;
+    R.stride = stride;
+    R.seed = rng_seed;
+    R.queue = (uint32_t*)g->live_queue.p;
+    R.bitmaps = nodes ? (uint32_t*)g->live_base.p : nullptr;
+    R.trial_counts = trial_counts;
+    R.total = total;
+    R.status = g->d_status;
+    for (uint32_t t0 = 0; t0 < n_trials; t0 += (uint32_t)tc) {
+        R.t0 = t0;
+        R.tc = std::min<uint32_t>((uint32_t)tc, n_trials - t0);
+        const uint64_t row_waves = (n + 63) / 64 * ((R.tc + 63) / 64);
+        const LiveClear C = t0 == 0 ? LiveClear{g->d_status, total, node_counts, n} : LiveClear{};
+        auto rows = bits == 8 ? lt_rows_kernel<8> : bits == 16 ? lt_rows_kernel<16> : lt_rows_kernel<32>;
+        hipLaunchKernelGGL(rows, dim3((unsigned)((row_waves + kWaves - 1) / kWaves)), dim3(kBlock), 0, s, C, R);
+        void* args[] = {&R, &S};
+        IMS_HIP(hipLaunchKernel(entry, dim3((unsigned)std::min<uint64_t>(slots, R.tc)), dim3(64 * kw), args, lds, s));
+        if (nodes)
+            hipLaunchKernelGGL(live_nodes_kernel, dim3((unsigned)(bm_words / 2), (R.tc + 64 * kNodeWords - 1) / (64 * kNodeWords)),
+                               dim3(kBlock), 0, s, (const uint32_t*)R.bitmaps, bm_words, n, t0, R.tc, node_counts, active_bits);
         IMS_HIP(hipGetLastError());
     }
     return IMS_OK;
@@ -705,6 +821,17 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
     }
     // options that shape the other forms keep them
     const bool form_asked = opts && (opts->shape || opts->blocks_per_cu || opts->ic_alpha != 0.0 || opts->ic_beta != 0.0 || opts->ic_direction);
+    if (g->model == IMS_MODEL_LT && !form_asked && !level_counts && !(opts && ((opts->test_flags & ~16) || opts->alpha != 0.0))) {
+        const uint32_t bits = lt_trial_bits(g);
+        if (bits && ((opts && (opts->test_flags & 16)) || lt_trials_pay(g, sv))) {
+            const bool timed = opts && opts->profile && g->prof_count < ims_graph::kProf;
+            if (timed && (rc = prof_begin(g, s))) return rc;
+            if ((rc = simulate_lt_trials(g, bits, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, s))) return rc;
+            if (timed && (rc = prof_end(g, s))) return rc;
+            g->last_shape = 1;
+            return IMS_OK;
+        }
+    }
     const bool live_forced = opts && (opts->test_flags & 16) && n > 0 && n <= kLiveNodes;
     if (g->model == IMS_MODEL_IC && !form_asked && (live_forced || live_single_pays(g, n_trials, level_counts != nullptr))) {
         const bool timed = opts && opts->profile && g->prof_count < ims_graph::kProf;

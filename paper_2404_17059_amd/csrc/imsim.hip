@@ -660,59 +660,74 @@ int simulate_live(ims_graph* g, const std::vector<uint32_t>& sv, uint32_t n_tria
     return IMS_OK;
 }
 
-// Per-trial LT form: element width of a run's states (0: none fits the LDS).
-constexpr uint64_t kLtTrialLds = 160 * 1024 - 12 * 1024;  // what the kernel's own arrays leave of a compute unit's LDS
+// Per-trial LT form: element width of a graph's states, and whether a trial's
+// fit the LDS beside the kernel's own arrays.
+constexpr uint64_t kLtTrialLds = 160 * 1024 - 12 * 1024;
 uint32_t lt_trial_bits(const ims_graph* g)
 {
-    const uint64_t n = (uint64_t)g->n;
-    const uint32_t bits = !g->lt_uniform || g->lt_zero || g->lt_max_in >= 32767 ? 32 : g->lt_max_in >= 127 ? 16 : 8;
-    return n > 0 && n * bits / 8 + (bits == 32 ? n / 8 : 0) + 64 <= kLtTrialLds ? bits : 0;
+    return !g->lt_uniform || g->lt_zero || g->lt_max_in >= 32767 ? 32 : g->lt_max_in >= 127 ? 16 : 8;
+}
+bool lt_trial_lds(const ims_graph* g)
+{
+    const uint64_t n = (uint64_t)g->n, bits = lt_trial_bits(g);
+    return n * bits / 8 + (bits == 32 ? n / 8 : 0) + 64 <= kLtTrialLds;
 }
 
 // Whether a run takes it.  It touches every arc once per trial, in as many
 // rounds of one workgroup as the cascade has steps; the grid-wide sweeps read
 // everything pending at every step but share it between 64 trials.  Measured
 // (1,000 trials, ms, this against the sweeps; Erdos-Renyi, preferential-
-// attachment and directed power-law graphs of 1,000 to 140,000 nodes, 64 to
+// attachment and directed power-law graphs of 1,000 to 500,000 nodes, 64 to
 // 4,000 trials): 20,000-node Erdos-Renyi 1.6 / 13.7, preferential attachment
-// 0.6 / 53, power law 0.75 / 1.8.  The sweeps win where a hub holding a
-// notable part of all arcs makes the cascade dense within few steps (and no
-// node has more in-arcs than a sweep stages): with hub seeds above about
-// 200,000 arcs (36,000 nodes 2.2 / 1.55), else above about a million
-// (140,000 nodes, 15 arcs each: 7.6 / 4.4).
+// 0.6 / 53, power law 0.75 / 1.8; state outside the LDS: 100,000-node
+// Erdos-Renyi with random weights 12.7 / 123, 200,000-node preferential
+// attachment 1.4 / 127.  The sweeps win where a hub holding a notable part of
+// all arcs makes the cascade dense within few steps (and no node has more
+// in-arcs than a sweep stages): with hub seeds above about 200,000 arcs
+// (36,000 nodes 2.2 / 1.55; state outside the LDS, 45,000 nodes 13.2 / 4.0),
+// else above about a million (140,000 nodes, 15 arcs each: 7.6 / 4.4; state
+// outside the LDS: 45,000 nodes 3.6 / 4.9, 100,000 nodes 6.3 / 2.8).
 bool lt_trials_pay(const ims_graph* g, const std::vector<uint32_t>& sv)
 {
     if (g->max_out * 64 < (uint64_t)g->m || g->lt_max_in > 64) return true;
     uint64_t arcs = 0;
     for (uint32_t x : sv) arcs += (uint64_t)(g->h_off[x + 1] - g->h_off[x]);
-    return g->m <= (arcs * 16 >= (uint64_t)g->m ? 200000 : 1060000);
+    const bool dense = arcs * 16 >= (uint64_t)g->m;
+    return g->m <= (lt_trial_lds(g) ? (dense ? 200000 : 1060000) : (dense ? 0 : 400000));
 }
 
-// Kernel of a width and wavefront count, allowed the LDS it asks for.
+// Kernel of a width, wavefront count and place of the state.
 template <int kBits>
-const void* lt_trial_entry(uint32_t kw)
+const void* lt_trial_entry(uint32_t kw, bool lds)
 {
     using namespace imsim;
-    return kw == 1 ? (const void*)lt_trial_kernel<kBits, 1> : kw == 4 ? (const void*)lt_trial_kernel<kBits, 4>
-                                                               : (const void*)lt_trial_kernel<kBits, 8>;
+    if (lds)
+        return kw == 1   ? (const void*)lt_trial_kernel<kBits, 1, true>
+               : kw == 4 ? (const void*)lt_trial_kernel<kBits, 4, true>
+                         : (const void*)lt_trial_kernel<kBits, 8, true>;
+    return kw == 1   ? (const void*)lt_trial_kernel<kBits, 1, false>
+           : kw == 4 ? (const void*)lt_trial_kernel<kBits, 4, false>
+                     : (const void*)lt_trial_kernel<kBits, 8, false>;
 }
 
 // One LT seed set (sorted, distinct: sv) in the per-trial form.
-int simulate_lt_trials(ims_graph* g, uint32_t bits, const std::vector<uint32_t>& sv, uint32_t n_trials, uint64_t rng_seed,
+int simulate_lt_trials(ims_graph* g, const std::vector<uint32_t>& sv, uint32_t n_trials, uint64_t rng_seed,
                        uint32_t* trial_counts, uint32_t* node_counts, uint64_t* total, uint64_t* active_bits, hipStream_t s)
 {
     using namespace imsim;
     const uint64_t n = (uint64_t)g->n;
+    const uint32_t bits = lt_trial_bits(g);
     const uint64_t stride = (n * bits / 8 + 15) / 16 * 16, bm_words = 2 * ((n + 63) / 64);
-    const bool nodes = node_counts || active_bits;
-    const uint64_t lds = stride + (bits == 32 ? bm_words * 4 : 0);
+    const bool in_lds = lt_trial_lds(g);
+    const bool nodes = node_counts || active_bits || (!in_lds && bits == 32);
+    const uint64_t lds = in_lds ? stride + (bits == 32 ? bm_words * 4 : 0) : 0;
     // wavefronts per trial: the fewer trials share a compute unit (by their
     // number, or by LDS), the more (Erdos-Renyi, 1,000 / 20,000 / 140,000
     // nodes: 4,000 trials 0.19 / 4.2 ms with one, 0.41 / 3.9 with four; 1,000
     // trials 26.0 ms with one, 13.3 with four, 12.9 with eight)
     const uint64_t share = std::min<uint64_t>((160 * 1024) / (lds + 4096), ((uint64_t)n_trials + g->cus - 1) / g->cus);
     const uint32_t kw = share >= 12 ? 1 : share >= 3 ? 4 : 8;
-    const void* entry = bits == 8 ? lt_trial_entry<8>(kw) : bits == 16 ? lt_trial_entry<16>(kw) : lt_trial_entry<32>(kw);
+    const void* entry = bits == 8 ? lt_trial_entry<8>(kw, in_lds) : bits == 16 ? lt_trial_entry<16>(kw, in_lds) : lt_trial_entry<32>(kw, in_lds);
     int rc, per_cu = 0;
     if (lds > 48 * 1024) IMS_HIP(hipFuncSetAttribute(entry, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, entry, (int)(64 * kw), lds) != hipSuccess || per_cu < 1) {
@@ -822,11 +837,10 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
     // options that shape the other forms keep them
     const bool form_asked = opts && (opts->shape || opts->blocks_per_cu || opts->ic_alpha != 0.0 || opts->ic_beta != 0.0 || opts->ic_direction);
     if (g->model == IMS_MODEL_LT && !form_asked && !level_counts && !(opts && ((opts->test_flags & ~16) || opts->alpha != 0.0))) {
-        const uint32_t bits = lt_trial_bits(g);
-        if (bits && ((opts && (opts->test_flags & 16)) || lt_trials_pay(g, sv))) {
+        if (n > 0 && ((opts && (opts->test_flags & 16)) || lt_trials_pay(g, sv))) {
             const bool timed = opts && opts->profile && g->prof_count < ims_graph::kProf;
             if (timed && (rc = prof_begin(g, s))) return rc;
-            if ((rc = simulate_lt_trials(g, bits, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, s))) return rc;
+            if ((rc = simulate_lt_trials(g, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, s))) return rc;
             if (timed && (rc = prof_end(g, s))) return rc;
             g->last_shape = 1;
             return IMS_OK;

@@ -97,15 +97,16 @@ struct LtTrialShared {
     uint32_t tail;               // joins so far
 };
 
-// Trials t0 + b, t0 + b + gridDim.x, ... of one run, kW wavefronts each.  A
+// Trials t0 + b, t0 + b + gridDim.x, ... of one run, kW wavefronts each, the
+// trial's state in LDS (kLds) or in its row where it stands.  A
 // round takes up to 64 * kW joined nodes (lane = node), lays their out-arcs
 // out densely in LDS (a prefix sum of the degrees), fetches 64 targets at a
 // time and updates them in LDS.  Bound by the chain of rounds: two dependent
-// reads (row bounds, targets), L2 or L1 hits on graphs of this size.
-template <int kBits, int kW>
+// reads (row bounds, targets) and the update.
+template <int kBits, int kW, bool kLds>
 __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
 {
-    extern __shared__ uint32_t st[];  // state, then (32-bit elements) the active bitmap
+    extern __shared__ uint32_t lds[];  // state, then (32-bit elements) the active bitmap
     __shared__ LtTrialShared<kW> sh;
     constexpr uint32_t kHalf = kBits == 32 ? 0u : 1u << (kBits - 1);
     constexpr uint32_t kPer = 32 / kBits;  // elements per LDS word
@@ -114,14 +115,17 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
     const uint32_t n = (uint32_t)R.n;
     const uint32_t bm_words = 2 * ((n + 63) / 64);
     const uint32_t st_words = (uint32_t)(R.stride / 4);
-    uint32_t* bm = st + st_words;
     uint32_t* buf = sh.buf[wave];
     uint32_t* list = R.queue + (uint64_t)blockIdx.x * R.n;
     uint64_t sum = 0;
     uint32_t max_rounds = 0;
     for (uint32_t row = blockIdx.x; row < R.tc; row += gridDim.x) {
-        const uint4* src = reinterpret_cast<const uint4*>(R.rows + (uint64_t)row * R.stride);
-        for (uint32_t i = threadIdx.x; i < st_words / 4; i += 64 * kW) reinterpret_cast<uint4*>(st)[i] = src[i];
+        uint32_t* const start = reinterpret_cast<uint32_t*>(R.rows + (uint64_t)row * R.stride);
+        uint32_t* const st = kLds ? lds : start;
+        uint32_t* const bm = kLds ? lds + st_words : R.bitmaps + (uint64_t)row * bm_words;
+        if constexpr (kLds)
+            for (uint32_t i = threadIdx.x; i < st_words / 4; i += 64 * kW)
+                reinterpret_cast<uint4*>(lds)[i] = reinterpret_cast<const uint4*>(start)[i];
         if (kBits == 32)
             for (uint32_t i = threadIdx.x; i < bm_words; i += 64 * kW) bm[i] = 0;
         if (kW > 1 && threadIdx.x == 0) sh.tail = 0;
@@ -227,7 +231,7 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
                     visit_arcs([&](uint32_t k) { return k0 + k; }, a1 - k0 < kLiveBuf ? a1 - k0 : kLiveBuf);
             }
         }
-        if (R.bitmaps) {
+        if (R.bitmaps && (kLds || kBits != 32)) {
             uint32_t* out = R.bitmaps + (uint64_t)row * bm_words;
             for (uint32_t i = threadIdx.x; i < bm_words; i += 64 * kW) {
                 uint32_t x = 0;
@@ -238,7 +242,7 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
 #pragma unroll
                     for (uint32_t y = 0; y < 32 / kPer; ++y) {
                         const uint32_t at = i * (32 / kPer) + y;
-                        const uint32_t s = at < st_words ? st[at] : 0u;
+                        const uint32_t s = at >= st_words ? 0u : kLds ? st[at] : load_relaxed32(&st[at]);
 #pragma unroll
                         for (uint32_t q = 0; q < kPer; ++q)
                             x |= ((s >> (q * kBits + kBits - 1)) & (32 * i + y * kPer + q < n ? 1u : 0u)) << (y * kPer + q);

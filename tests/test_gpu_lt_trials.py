@@ -24,7 +24,7 @@ def ims():
 
 def graph(n, m, rng, into):
     """m random distinct arcs and `into` arcs into node 1, rows in id order."""
-    keys = np.concatenate([rng.choice(n * n, size=m, replace=False), np.arange(into, dtype=np.int64) * n + 1])
+    keys = np.concatenate([rng.integers(0, n * n, size=m), np.arange(into, dtype=np.int64) * n + 1])
     keys = np.unique(keys)
     keys = keys[keys // n != keys % n]
     off = np.zeros(n + 1, dtype=np.int64)
@@ -58,6 +58,9 @@ def weights(kind, n, idx, rng):
     ("zeros", 300, 1500, 65, 6, 100),
     ("random", 30000, 60000, 65, 40, 0),   # 32-bit states, 124 KB of LDS
     ("equal", 500, 1500, 10, 0, 0),        # no seed
+    ("random", 45000, 90000, 65, 40, 0),   # state outside the LDS, at each width
+    ("equal", 80000, 160000, 9, 40, 300),
+    ("equal", 160000, 320000, 9, 400, 0),
 ])
 def test_per_trial_runs_match_the_oracle(ims, kind, n, m, trials, seeds, into):
     rng = np.random.default_rng([n, m, trials, into])

@@ -198,14 +198,30 @@ __global__ void __launch_bounds__(kThreads) spmm_kernel(uint32_t n_items, uint32
                 for (int i = 0; i < 8; ++i) acc[i] = fmaf(a[q], f[i], acc[i]);
             }
         }
-        for (; e < e1; ++e) {
-            const uint32_t u = nbr[e];
-            const float a = w[e];
-            const u32x4 r = *(const u32x4*)(X + (uint64_t)u * C + (uint64_t)j * 8);
-            float f[8];
-            unpack8(r, f);
+        if (e < e1) {
+            // the last arcs, their rows' loads issued together as well
+            const uint32_t rem = (uint32_t)(e1 - e);
+            u32x4 r[7];
+            float a[7];
             #pragma unroll
-            for (int i = 0; i < 8; ++i) acc[i] = fmaf(a, f[i], acc[i]);
+            for (int q = 0; q < 7; ++q) {
+                r[q] = u32x4{0u, 0u, 0u, 0u};
+                a[q] = 0.0f;
+                if ((uint32_t)q < rem) {
+                    const uint32_t u = nbr[e + q];
+                    a[q] = w[e + q];
+                    r[q] = *(const u32x4*)(X + (uint64_t)u * C + (uint64_t)j * 8);
+                }
+            }
+            #pragma unroll
+            for (int q = 0; q < 7; ++q) {
+                if ((uint32_t)q < rem) {
+                    float f[8];
+                    unpack8(r[q], f);
+                    #pragma unroll
+                    for (int i = 0; i < 8; ++i) acc[i] = fmaf(a[q], f[i], acc[i]);
+                }
+            }
         }
         if (I.slot != kDirect) {
             floatx4* dst = (floatx4*)(partial + (uint64_t)I.slot * C + (uint64_t)j * 8);

@@ -606,60 +606,6 @@ int live_seeds(ims_graph* g, const std::vector<uint32_t>& sv, imsim::LiveSeeds& 
     return IMS_OK;
 }
 
-// One seed set (sorted, distinct: sv) in the drawn-coins form: coin rows,
-// one cascade per trial, then the per-node outputs.
-int simulate_live(ims_graph* g, const std::vector<uint32_t>& sv, uint32_t n_trials, uint64_t rng_seed, uint32_t* trial_counts,
-                  uint32_t* node_counts, uint64_t* total, uint64_t* active_bits, uint32_t* level_counts, uint32_t max_levels, hipStream_t s)
-{
-    using namespace imsim;
-    const uint64_t n = (uint64_t)g->n, m = (uint64_t)g->m;
-    const uint64_t row_words = std::max<uint64_t>((m + 511) / 512, 1) * 8, bm_words = 2 * ((n + 63) / 64);
-    const bool nodes = node_counts || active_bits;
-    // wavefronts per cascade: the fewer the trials, the more (20,000-node
-    // Erdos-Renyi, UR, 64 trials: 1.02 / 0.37 / 0.23 ms with 1 / 4 / 8; 1,000-
-    // node, 10,000 trials: one is fastest)
-    const uint32_t kw = n_trials >= 4096 && n < 65536 ? 1 : n_trials > 512 ? 4 : n_trials > 256 || n < 20000 ? 8 : 16;
-    auto single = kw == 1 ? live_single_kernel<1> : kw == 4 ? live_single_kernel<4> : kw == 8 ? live_single_kernel<8> : live_single_kernel<16>;
-    const uint64_t slots = std::min<uint64_t>(n_trials, (uint64_t)g->cus * 32 / kw);
-    const uint64_t row_bytes = row_words * 8 + (nodes ? bm_words * 4 : 0);
-    uint64_t tc = kLiveRowBudget / row_bytes / 64 * 64;
-    tc = std::min<uint64_t>(std::max<uint64_t>(tc, 64), ((uint64_t)n_trials + 63) / 64 * 64);
-    int rc;
-    if ((rc = ensure_buf(g, g->live_rows, tc * row_words * 8, false)) || (rc = ensure_buf(g, g->live_queue, slots * n * 4, false)) ||
-        (nodes && (rc = ensure_buf(g, g->live_base, tc * bm_words * 4, false))))
-        return rc;
-    LiveSeeds S;
-    if ((rc = live_seeds(g, sv, S, s))) return rc;
-    LiveParams L;
-    std::memset(&L, 0, sizeof L);
-    L.n = n;
-    L.off = g->d_off32;
-    L.idx = g->d_idx;
-    L.m = m;
-    L.rows = (uint64_t*)g->live_rows.p;
-    L.row_words = row_words;
-    L.T = n_trials;
-    L.queue = (uint32_t*)g->live_queue.p;
-    L.status = g->d_status;
-    uint32_t* bitmaps = nodes ? (uint32_t*)g->live_base.p : nullptr;
-    for (uint32_t t0 = 0; t0 < n_trials; t0 += (uint32_t)tc) {
-        L.t0 = t0;
-        L.tc = std::min<uint32_t>((uint32_t)tc, n_trials - t0);
-        const uint64_t draw_waves = row_words / 8 * ((L.tc + 63) / 64);
-        hipLaunchKernelGGL(live_draw_kernel, dim3((unsigned)((draw_waves + kWaves - 1) / kWaves)), dim3(kBlock), 0, s,
-                           t0 == 0 ? LiveClear{g->d_status, total, node_counts, n} : LiveClear{}, L.rows, row_words, (const uint32_t*)g->d_thr, m, t0, L.tc,
-                           rng_seed);
-        hipLaunchKernelGGL(single, dim3((unsigned)std::min<uint64_t>(slots, L.tc)), dim3(64 * kw), bm_words * 4, s, L, S, bitmaps, trial_counts, total, level_counts,
-                           max_levels);
-        if (nodes)
-            hipLaunchKernelGGL(live_nodes_kernel, dim3((unsigned)(bm_words / 2), (L.tc + 64 * kNodeWords - 1) / (64 * kNodeWords)), dim3(kBlock), 0, s,
-                               (const uint32_t*)bitmaps, bm_words, n,
-                               t0, L.tc, node_counts, active_bits);
-        IMS_HIP(hipGetLastError());
-    }
-    return IMS_OK;
-}
-
 // Per-trial LT form: element width of a graph's states, and whether a trial's
 // fit the LDS beside the kernel's own arrays.
 constexpr uint64_t kLtTrialLds = 160 * 1024 - 12 * 1024;
@@ -710,69 +656,163 @@ const void* lt_trial_entry(uint32_t kw, bool lds)
                      : (const void*)lt_trial_kernel<kBits, 8, false>;
 }
 
-// One LT seed set (sorted, distinct: sv) in the per-trial form.
-int simulate_lt_trials(ims_graph* g, const std::vector<uint32_t>& sv, uint32_t n_trials, uint64_t rng_seed,
-                       uint32_t* trial_counts, uint32_t* node_counts, uint64_t* total, uint64_t* active_bits, hipStream_t s)
+// One run in a per-trial form: IC over drawn coins, LT by pushing.
+struct TrialRun {
+    const ims_graph* g = nullptr;
+    uint32_t n_trials = 0;
+    uint32_t kw = 0;        // wavefronts per trial
+    uint32_t bits = 0;      // LT: element width
+    bool nodes = false;     // final bitmaps are kept (for per-node outputs)
+    uint64_t row_bytes = 0; // coin row or starting states of a trial
+    uint64_t bm_words = 0;
+    uint64_t lds = 0;
+    uint64_t slots = 0, tc = 0;  // workgroups, trials per range
+    const void* entry = nullptr;
+    uint64_t rows() const { return tc * row_bytes; }
+    uint64_t queue() const { return slots * (uint64_t)g->n * 4; }
+    uint64_t bitmaps() const { return nodes ? tc * bm_words * 4 : 0; }
+};
+
+// Launch shape of a run; `together` trials run at once on the device (those
+// of other runs beside it included).
+int trial_run_plan(TrialRun& P, const ims_graph* g, uint32_t n_trials, bool nodes, uint64_t together)
 {
     using namespace imsim;
-    const uint64_t n = (uint64_t)g->n;
-    const uint32_t bits = lt_trial_bits(g);
-    const uint64_t stride = (n * bits / 8 + 15) / 16 * 16, bm_words = 2 * ((n + 63) / 64);
-    const bool in_lds = lt_trial_lds(g);
-    const bool nodes = node_counts || active_bits || (!in_lds && bits == 32);
-    const uint64_t lds = in_lds ? stride + (bits == 32 ? bm_words * 4 : 0) : 0;
-    // wavefronts per trial: the fewer trials share a compute unit (by their
-    // number, or by LDS), the more (Erdos-Renyi, 1,000 / 20,000 / 140,000
-    // nodes: 4,000 trials 0.19 / 4.2 ms with one, 0.41 / 3.9 with four; 1,000
-    // trials 26.0 ms with one, 13.3 with four, 12.9 with eight)
-    const uint64_t share = std::min<uint64_t>((160 * 1024) / (lds + 4096), ((uint64_t)n_trials + g->cus - 1) / g->cus);
-    const uint32_t kw = share >= 12 ? 1 : share >= 3 ? 4 : 8;
-    const void* entry = bits == 8 ? lt_trial_entry<8>(kw, in_lds) : bits == 16 ? lt_trial_entry<16>(kw, in_lds) : lt_trial_entry<32>(kw, in_lds);
-    int rc, per_cu = 0;
-    if (lds > 48 * 1024) IMS_HIP(hipFuncSetAttribute(entry, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, entry, (int)(64 * kw), lds) != hipSuccess || per_cu < 1) {
-        (void)hipGetLastError();
-        per_cu = 1;
+    const uint64_t n = (uint64_t)g->n, m = (uint64_t)g->m, cus = (uint64_t)g->cus;
+    P.g = g;
+    P.n_trials = n_trials;
+    P.nodes = nodes;
+    P.bm_words = 2 * ((n + 63) / 64);
+    uint64_t per_cu;
+    if (g->model == IMS_MODEL_IC) {
+        // wavefronts per cascade: the fewer the trials, the more (20,000-node
+        // Erdos-Renyi, UR, 64 trials: 1.02 / 0.37 / 0.23 ms with 1 / 4 / 8;
+        // 1,000-node, 10,000 trials: one is fastest)
+        P.kw = together >= 4096 && n < 65536 ? 1 : together > 512 ? 4 : together > 256 || n < 20000 ? 8 : 16;
+        P.entry = P.kw == 1   ? (const void*)live_single_kernel<1>
+                  : P.kw == 4 ? (const void*)live_single_kernel<4>
+                  : P.kw == 8 ? (const void*)live_single_kernel<8>
+                              : (const void*)live_single_kernel<16>;
+        P.row_bytes = std::max<uint64_t>((m + 511) / 512, 1) * 64;
+        P.lds = P.bm_words * 4;
+        per_cu = 32 / P.kw;
+    } else {
+        P.bits = lt_trial_bits(g);
+        const bool in_lds = lt_trial_lds(g);
+        P.nodes = nodes || (!in_lds && P.bits == 32);
+        P.row_bytes = (n * P.bits / 8 + 15) / 16 * 16;
+        P.lds = in_lds ? P.row_bytes + (P.bits == 32 ? P.bm_words * 4 : 0) : 0;
+        // the fewer trials share a compute unit (by their number, or by LDS),
+        // the more wavefronts (Erdos-Renyi, 1,000 / 20,000 / 140,000 nodes:
+        // 4,000 trials 0.19 / 4.2 ms with one, 0.41 / 3.9 with four; 1,000
+        // trials 26.0 ms with one, 13.3 with four, 12.9 with eight)
+        const uint64_t share = std::min<uint64_t>((160 * 1024) / (P.lds + 4096), (together + cus - 1) / cus);
+        P.kw = share >= 12 ? 1 : share >= 3 ? 4 : 8;
+        P.entry = P.bits == 8    ? lt_trial_entry<8>(P.kw, in_lds)
+                  : P.bits == 16 ? lt_trial_entry<16>(P.kw, in_lds)
+                                 : lt_trial_entry<32>(P.kw, in_lds);
+        if (P.lds > 48 * 1024) IMS_HIP(hipFuncSetAttribute(P.entry, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLtTrialLds));
+        int fit = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, P.entry, (int)(64 * P.kw), P.lds) != hipSuccess || fit < 1) {
+            (void)hipGetLastError();
+            fit = 1;
+        }
+        per_cu = (uint64_t)fit;
     }
-    const uint64_t slots = std::min<uint64_t>(n_trials, (uint64_t)g->cus * (uint32_t)per_cu);
-    uint64_t tc = kLiveRowBudget / (stride + (nodes ? bm_words * 4 : 0)) / 64 * 64;
-    tc = std::min<uint64_t>(std::max<uint64_t>(tc, 64), ((uint64_t)n_trials + 63) / 64 * 64);
-    if ((rc = ensure_buf(g, g->live_rows, tc * stride, false)) || (rc = ensure_buf(g, g->live_queue, slots * n * 4, false)) ||
-        (nodes && (rc = ensure_buf(g, g->live_base, tc * bm_words * 4, false))))
-        return rc;
-    LiveSeeds S;
-    if ((rc = live_seeds(g, sv, S, s))) return rc;
-    LtRun R;
-    std::memset(&R, 0, sizeof R);
-    R.n = n;
-    R.off = g->d_off32;
-    R.idx = g->d_idx;
-    R.wout = g->d_lt_wout;
-    R.in_off = g->d_in_off;
-    R.in_src = g->d_in_src32;
-    R.node_w = g->d_node_w;
-    R.rows = (uint8_t*)g->live_rows.p;
-    R.stride = stride;
-    R.seed = rng_seed;
-    R.queue = (uint32_t*)g->live_queue.p;
-    R.bitmaps = nodes ? (uint32_t*)g->live_base.p : nullptr;
-    R.trial_counts = trial_counts;
-    R.total = total;
-    R.status = g->d_status;
-    for (uint32_t t0 = 0; t0 < n_trials; t0 += (uint32_t)tc) {
-        R.t0 = t0;
-        R.tc = std::min<uint32_t>((uint32_t)tc, n_trials - t0);
-        const uint64_t row_waves = (n + 63) / 64 * ((R.tc + 63) / 64);
-        const LiveClear C = t0 == 0 ? LiveClear{g->d_status, total, node_counts, n} : LiveClear{};
-        auto rows = bits == 8 ? lt_rows_kernel<8> : bits == 16 ? lt_rows_kernel<16> : lt_rows_kernel<32>;
-        hipLaunchKernelGGL(rows, dim3((unsigned)((row_waves + kWaves - 1) / kWaves)), dim3(kBlock), 0, s, C, R);
-        void* args[] = {&R, &S};
-        IMS_HIP(hipLaunchKernel(entry, dim3((unsigned)std::min<uint64_t>(slots, R.tc)), dim3(64 * kw), args, lds, s));
-        if (nodes)
-            hipLaunchKernelGGL(live_nodes_kernel, dim3((unsigned)(bm_words / 2), (R.tc + 64 * kNodeWords - 1) / (64 * kNodeWords)),
-                               dim3(kBlock), 0, s, (const uint32_t*)R.bitmaps, bm_words, n, t0, R.tc, node_counts, active_bits);
+    P.slots = std::min<uint64_t>(n_trials, cus * per_cu);
+    P.tc = kLiveRowBudget / (P.row_bytes + (P.nodes ? P.bm_words * 4 : 0)) / 64 * 64;
+    P.tc = std::min<uint64_t>(std::max<uint64_t>(P.tc, 64), ((uint64_t)n_trials + 63) / 64 * 64);
+    return IMS_OK;
+}
+
+// Enqueue a planned run: per range of trials the coin rows or starting states,
+// the cascades, the per-node outputs.  status: four words, cleared here, or
+// null when `spare` (words nobody reads as a run's status) is given.
+int trial_run_launch(const TrialRun& P, void* rows, void* queue, void* bitmaps, const imsim::LiveSeeds& seeds, uint64_t rng_seed,
+                     uint32_t* trial_counts, uint32_t* node_counts, uint64_t* total, uint64_t* active_bits, uint32_t* level_counts,
+                     uint32_t max_levels, uint32_t* status, uint32_t* spare, hipStream_t s)
+{
+    using namespace imsim;
+    const ims_graph* g = P.g;
+    const uint64_t n = (uint64_t)g->n;
+    LiveSeeds S = seeds;
+    uint32_t* bm = P.nodes ? (uint32_t*)bitmaps : nullptr;
+    for (uint32_t t0 = 0; t0 < P.n_trials; t0 += (uint32_t)P.tc) {
+        uint32_t tc = std::min<uint32_t>((uint32_t)P.tc, P.n_trials - t0);
+        const uint32_t words = (tc + 63) / 64;
+        const LiveClear C = t0 == 0 ? LiveClear{status, total, node_counts, n} : LiveClear{};
+        const dim3 grid((unsigned)std::min<uint64_t>(P.slots, tc)), block(64 * P.kw);
+        if (g->model == IMS_MODEL_IC) {
+            LiveParams L;
+            std::memset(&L, 0, sizeof L);
+            L.n = n;
+            L.off = g->d_off32;
+            L.idx = g->d_idx;
+            L.m = (uint64_t)g->m;
+            L.rows = (uint64_t*)rows;
+            L.row_words = P.row_bytes / 8;
+            L.T = P.n_trials;
+            L.queue = (uint32_t*)queue;
+            L.status = status ? status : spare;
+            L.t0 = t0;
+            L.tc = tc;
+            const uint64_t waves = L.row_words / 8 * words;
+            hipLaunchKernelGGL(live_draw_kernel, dim3((unsigned)((waves + kWaves - 1) / kWaves)), dim3(kBlock), 0, s, C, L.rows, L.row_words,
+                               (const uint32_t*)g->d_thr, L.m, t0, tc, rng_seed);
+            void* args[] = {&L, &S, &bm, &trial_counts, &total, &level_counts, &max_levels};
+            IMS_HIP(hipLaunchKernel(P.entry, grid, block, args, P.lds, s));
+        } else {
+            LtRun R;
+            std::memset(&R, 0, sizeof R);
+            R.n = n;
+            R.off = g->d_off32;
+            R.idx = g->d_idx;
+            R.wout = g->d_lt_wout;
+            R.in_off = g->d_in_off;
+            R.in_src = g->d_in_src32;
+            R.node_w = g->d_node_w;
+            R.rows = (uint8_t*)rows;
+            R.stride = P.row_bytes;
+            R.seed = rng_seed;
+            R.queue = (uint32_t*)queue;
+            R.bitmaps = bm;
+            R.trial_counts = trial_counts;
+            R.total = total;
+            R.status = status ? status : spare;
+            R.t0 = t0;
+            R.tc = tc;
+            const uint64_t waves = (n + 63) / 64 * words;
+            auto start = P.bits == 8 ? lt_rows_kernel<8> : P.bits == 16 ? lt_rows_kernel<16> : lt_rows_kernel<32>;
+            hipLaunchKernelGGL(start, dim3((unsigned)((waves + kWaves - 1) / kWaves)), dim3(kBlock), 0, s, C, R);
+            void* args[] = {&R, &S};
+            IMS_HIP(hipLaunchKernel(P.entry, grid, block, args, P.lds, s));
+        }
+        if (node_counts || active_bits)
+            hipLaunchKernelGGL(live_nodes_kernel, dim3((unsigned)(P.bm_words / 2), (words + kNodeWords - 1) / kNodeWords), dim3(kBlock), 0, s,
+                               (const uint32_t*)bm, P.bm_words, n, t0, tc, node_counts, active_bits);
         IMS_HIP(hipGetLastError());
     }
+    return IMS_OK;
+}
+
+// One seed set (sorted, distinct: sv) in a per-trial form, in the graph's workspace.
+int simulate_trials(ims_graph* g, const std::vector<uint32_t>& sv, uint32_t n_trials, uint64_t rng_seed, uint32_t* trial_counts,
+                    uint32_t* node_counts, uint64_t* total, uint64_t* active_bits, uint32_t* level_counts, uint32_t max_levels,
+                    const ims_opts* opts, hipStream_t s)
+{
+    const bool timed = opts && opts->profile && g->prof_count < ims_graph::kProf;
+    int rc;
+    if (timed && (rc = prof_begin(g, s))) return rc;
+    TrialRun P;
+    imsim::LiveSeeds S;
+    if ((rc = trial_run_plan(P, g, n_trials, node_counts || active_bits, n_trials)) || (rc = ensure_buf(g, g->live_rows, P.rows(), false)) ||
+        (rc = ensure_buf(g, g->live_queue, P.queue(), false)) || (P.nodes && (rc = ensure_buf(g, g->live_base, P.bitmaps(), false))) ||
+        (rc = live_seeds(g, sv, S, s)) ||
+        (rc = trial_run_launch(P, g->live_rows.p, g->live_queue.p, g->live_base.p, S, rng_seed, trial_counts, node_counts, total, active_bits,
+                               level_counts, max_levels, g->d_status, nullptr, s)))
+        return rc;
+    if (timed && (rc = prof_end(g, s))) return rc;
+    g->last_shape = 1;
     return IMS_OK;
 }
 
@@ -836,25 +876,16 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
     }
     // options that shape the other forms keep them
     const bool form_asked = opts && (opts->shape || opts->blocks_per_cu || opts->ic_alpha != 0.0 || opts->ic_beta != 0.0 || opts->ic_direction);
-    if (g->model == IMS_MODEL_LT && !form_asked && !level_counts && !(opts && ((opts->test_flags & ~16) || opts->alpha != 0.0))) {
-        if (n > 0 && ((opts && (opts->test_flags & 16)) || lt_trials_pay(g, sv))) {
-            const bool timed = opts && opts->profile && g->prof_count < ims_graph::kProf;
-            if (timed && (rc = prof_begin(g, s))) return rc;
-            if ((rc = simulate_lt_trials(g, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, s))) return rc;
-            if (timed && (rc = prof_end(g, s))) return rc;
-            g->last_shape = 1;
-            return IMS_OK;
+    const bool forced = opts && (opts->test_flags & 16);
+    if (!form_asked && n > 0) {
+        if (g->model == IMS_MODEL_IC) {
+            if ((forced && n <= kLiveNodes) || live_single_pays(g, n_trials, level_counts != nullptr))
+                return simulate_trials(g, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, level_counts, max_levels,
+                                       opts, s);
+        } else if (!level_counts && !(opts && ((opts->test_flags & ~16) || opts->alpha != 0.0))) {
+            if (forced || lt_trials_pay(g, sv))
+                return simulate_trials(g, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, nullptr, 0, opts, s);
         }
-    }
-    const bool live_forced = opts && (opts->test_flags & 16) && n > 0 && n <= kLiveNodes;
-    if (g->model == IMS_MODEL_IC && !form_asked && (live_forced || live_single_pays(g, n_trials, level_counts != nullptr))) {
-        const bool timed = opts && opts->profile && g->prof_count < ims_graph::kProf;
-        if (timed && (rc = prof_begin(g, s))) return rc;
-        if ((rc = simulate_live(g, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, level_counts, max_levels, s)))
-            return rc;
-        if (timed && (rc = prof_end(g, s))) return rc;
-        g->last_shape = 1;
-        return IMS_OK;
     }
     if (level_counts) shape = 1;  // levels are the word-local (synchronous) steps
     if (shape != 1 && shape != 2) return fail(IMS_E_INVALID_ARG, "ims_simulate: unknown shape %d", shape);
@@ -1512,6 +1543,25 @@ struct ims_batch {
     std::vector<imsim::BatchItem> host_items;
     std::vector<uint32_t*> dev_seeds;
     std::vector<double> cost;
+    // items in a per-trial form (a default batch), beside the task list: their
+    // runs go to kLanes streams forked off the batch's, each with a workspace
+    // its runs use one after the other
+    static constexpr uint32_t kLanes = 4;
+    struct Side {
+        uint32_t item = 0, lane = 0;
+        TrialRun run;
+        imsim::LiveSeeds seeds;
+    };
+    struct Lane {
+        ims_graph::Buf rows, queue, bitmaps;
+        hipStream_t stream = nullptr;
+        hipEvent_t done = nullptr;
+    };
+    bool forms = false;  // items may take a per-trial form (no tuning asked for)
+    std::vector<std::vector<uint32_t>> seed_lists;
+    std::vector<Side> sides;
+    Lane lanes[kLanes];
+    hipEvent_t fork = nullptr;
     ims_tuning tuning{2, 0, 8, 0.0, 0.0};  // 8 trials per task: measured 3-5% faster than 16 on the 64-item batch
     int device = 0, cus = 0;
     uint64_t max_n = 1;
@@ -1539,6 +1589,12 @@ struct ims_batch {
     {
         drop_graph();
         if (capture_stream) (void)hipStreamDestroy(capture_stream);
+        for (Lane& l : lanes) {
+            if (l.stream) (void)hipStreamDestroy(l.stream);
+            if (l.done) (void)hipEventDestroy(l.done);
+            for (ims_graph::Buf* b : {&l.rows, &l.queue, &l.bitmaps}) ims_graph::release(*b);
+        }
+        if (fork) (void)hipEventDestroy(fork);
         for (auto* p : dev_seeds) dev_free(p);
         dev_free(d_items);
         dev_free(d_tasks);
@@ -1565,12 +1621,78 @@ int batch_buf(ims_graph::Buf& b, uint64_t bytes)
     return IMS_OK;
 }
 
+// The batch's items that run in a per-trial form, spread over the lanes
+// (largest first, each to the least loaded), and the lanes' workspaces.
+int batch_plan_sides(ims_batch* b, std::vector<bool>& aside)
+{
+    b->sides.clear();
+    aside.assign(b->items.size(), false);
+    if (!b->forms || b->timing) return IMS_OK;
+    std::vector<uint32_t> which;
+    for (uint32_t i = 0; i < (uint32_t)b->items.size(); ++i) {
+        const ims_graph* g = b->items[i].graph;
+        if (g->n == 0 || g->device != b->device) continue;
+        if (g->model == IMS_MODEL_IC ? live_single_pays(g, b->items[i].n_trials, false) : lt_trials_pay(g, b->seed_lists[i])) which.push_back(i);
+    }
+    std::stable_sort(which.begin(), which.end(), [&](uint32_t x, uint32_t y) { return b->cost[x] > b->cost[y]; });
+    double load[ims_batch::kLanes] = {};
+    uint64_t need[ims_batch::kLanes][3] = {};
+    for (uint32_t i : which) {
+        ims_batch::Side sd;
+        sd.item = i;
+        ims_graph* g = b->items[i].graph;
+        int rc = device_cus(g);
+        if (rc) return rc;
+        for (uint32_t l = 1; l < ims_batch::kLanes; ++l)
+            if (load[l] < load[sd.lane]) sd.lane = l;
+        load[sd.lane] += b->cost[i];
+        const uint64_t beside = std::min<uint64_t>(ims_batch::kLanes, which.size());
+        if ((rc = trial_run_plan(sd.run, g, b->items[i].n_trials, b->items[i].node_counts != nullptr, beside * b->items[i].n_trials))) return rc;
+        sd.seeds.count = (uint32_t)b->seed_lists[i].size();
+        sd.seeds.more = sd.seeds.count > imsim::kArgSeeds ? b->dev_seeds[i] : nullptr;
+        if (!sd.seeds.more) std::copy(b->seed_lists[i].begin(), b->seed_lists[i].end(), sd.seeds.v);
+        const uint64_t bytes[3] = {sd.run.rows(), sd.run.queue(), sd.run.bitmaps()};
+        for (int k = 0; k < 3; ++k) need[sd.lane][k] = std::max(need[sd.lane][k], bytes[k]);
+        b->sides.push_back(sd);
+        aside[i] = true;
+    }
+    for (uint32_t l = 0; l < ims_batch::kLanes && !b->sides.empty(); ++l) {
+        ims_batch::Lane& L = b->lanes[l];
+        ims_graph::Buf* bufs[3] = {&L.rows, &L.queue, &L.bitmaps};
+        for (int k = 0; k < 3; ++k) {
+            if (need[l][k] == 0 || (bufs[k]->p && bufs[k]->bytes >= need[l][k])) continue;
+            ims_graph::release(*bufs[k]);
+            uint8_t* p = nullptr;
+            int rc = dev_alloc(&p, need[l][k]);
+            if (rc) return rc;
+            bufs[k]->p = p;
+            bufs[k]->bytes = need[l][k];
+        }
+        if (!L.stream) IMS_HIP(hipStreamCreateWithFlags(&L.stream, hipStreamNonBlocking));
+        if (!L.done) IMS_HIP(hipEventCreateWithFlags(&L.done, hipEventDisableTiming));
+    }
+    if (!b->sides.empty() && !b->fork) IMS_HIP(hipEventCreateWithFlags(&b->fork, hipEventDisableTiming));
+    return IMS_OK;
+}
+
 // Task list and slot state for the current tuning.
 int batch_plan(ims_batch* b)
 {
     const uint32_t n_items = (uint32_t)b->items.size();
-    std::vector<uint32_t> order(n_items);
-    for (uint32_t i = 0; i < n_items; ++i) order[i] = i;
+    std::vector<bool> aside;
+    int rc_sides = batch_plan_sides(b, aside);
+    if (rc_sides) return rc_sides;
+    std::vector<uint32_t> order;
+    for (uint32_t i = 0; i < n_items; ++i)
+        if (!aside[i]) order.push_back(i);
+    uint64_t max_n = 1;
+    bool any_lt = false;
+    for (uint32_t i : order) {
+        max_n = std::max<uint64_t>(max_n, (uint64_t)b->items[i].graph->n);
+        any_lt |= b->items[i].graph->model == IMS_MODEL_LT;
+    }
+    b->max_n = max_n;
+    b->any_lt = any_lt;
     if (b->tuning.order == 0)
         std::stable_sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) { return b->cost[x] > b->cost[y]; });
     // each word of an item as 2^s tasks of 64 / 2^s trials (s from the
@@ -1604,7 +1726,7 @@ int batch_plan(ims_batch* b)
     if (!tasks.empty()) IMS_HIP(hipMemcpy(b->d_tasks, tasks.data(), tasks.size() * sizeof(uint64_t), hipMemcpyHostToDevice));
     const int per_cu = std::min(std::max(b->tuning.blocks_per_cu, 1), 16);
     b->slots = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(b->n_tasks, (uint64_t)b->cus * per_cu));
-    const uint64_t cells = (uint64_t)b->slots * b->max_n;
+    const uint64_t cells = b->n_tasks ? (uint64_t)b->slots * b->max_n : 0;
     if ((rc = batch_buf(b->sA, cells * 8)) || (rc = batch_buf(b->sN, cells * 8)) || (rc = batch_buf(b->sQ0, cells * 4)) ||
         (rc = batch_buf(b->sQ1, cells * 4)) || (rc = batch_buf(b->sQ2, cells * 16)) || (rc = batch_buf(b->sact, cells * 4)) ||
         (rc = batch_buf(b->sstamp, cells * 4)) || (rc = batch_buf(b->ssteps, (uint64_t)b->slots * 4)))
@@ -1616,21 +1738,9 @@ int batch_plan(ims_batch* b)
     return IMS_OK;
 }
 
-// Enqueue one batch run: clear outputs and the task counter (fill kernels, no
-// memset nodes, so the sequence can be captured), then the persistent launch.
-int batch_enqueue(ims_batch* b, hipStream_t s)
+// The persistent launch over the task list.
+int batch_tasks(ims_batch* b, hipStream_t s)
 {
-    int rc;
-    for (const auto& it : b->items) {
-        if ((rc = fill_async<uint32_t>(it.trial_counts, it.n_trials, 0u, s))) return rc;
-        if (it.node_counts) {
-            int64_t n = 0;
-            ims_graph_info(it.graph, &n, nullptr, nullptr);
-            if ((rc = fill_async<uint32_t>(it.node_counts, (uint64_t)n, 0u, s))) return rc;
-        }
-        if ((rc = fill_async<unsigned long long>((unsigned long long*)it.total, 1, 0ull, s))) return rc;
-    }
-    if ((rc = fill_async<uint32_t>(b->d_ctl, 8, 0u, s))) return rc;
     imsim::SlotBufs S{b->max_n,
                       (uint64_t*)b->sA.p,
                       (uint64_t*)b->sN.p,
@@ -1647,6 +1757,46 @@ int batch_enqueue(ims_batch* b, hipStream_t s)
     return IMS_OK;
 }
 
+// Enqueue one batch run: clear outputs and the task counter (fill kernels, no
+// memset nodes, so the sequence can be captured), then the persistent launch; the items in a
+// per-trial form run on their lanes meanwhile.
+int batch_enqueue(ims_batch* b, hipStream_t s)
+{
+    int rc;
+    std::vector<bool> aside(b->items.size(), false);
+    if (!b->sides.empty()) {
+        IMS_HIP(hipEventRecord(b->fork, s));
+        for (ims_batch::Lane& l : b->lanes) IMS_HIP(hipStreamWaitEvent(l.stream, b->fork, 0));
+        for (const ims_batch::Side& sd : b->sides) {
+            const ims_batch_item& it = b->items[sd.item];
+            const ims_batch::Lane& l = b->lanes[sd.lane];
+            aside[sd.item] = true;
+            if ((rc = trial_run_launch(sd.run, l.rows.p, l.queue.p, l.bitmaps.p, sd.seeds, it.rng_seed, it.trial_counts, it.node_counts,
+                                       it.total, nullptr, nullptr, 0, nullptr, b->d_ctl + 6, l.stream)))
+                return rc;
+        }
+        for (ims_batch::Lane& l : b->lanes) IMS_HIP(hipEventRecord(l.done, l.stream));
+    }
+    if (b->n_tasks) {
+        for (size_t i = 0; i < b->items.size(); ++i) {
+            const ims_batch_item& it = b->items[i];
+            if (aside[i]) continue;
+            if ((rc = fill_async<uint32_t>(it.trial_counts, it.n_trials, 0u, s))) return rc;
+            if (it.node_counts) {
+                int64_t n = 0;
+                ims_graph_info(it.graph, &n, nullptr, nullptr);
+                if ((rc = fill_async<uint32_t>(it.node_counts, (uint64_t)n, 0u, s))) return rc;
+            }
+            if ((rc = fill_async<unsigned long long>((unsigned long long*)it.total, 1, 0ull, s))) return rc;
+        }
+        // (words 6 and 7 take the per-trial runs' steps, which nobody reads)
+        if ((rc = fill_async<uint32_t>(b->d_ctl, 6, 0u, s))) return rc;
+        if ((rc = batch_tasks(b, s))) return rc;
+    }
+    if (!b->sides.empty())
+        for (ims_batch::Lane& l : b->lanes) IMS_HIP(hipStreamWaitEvent(s, l.done, 0));
+    return IMS_OK;
+}
 }  // namespace
 
 extern "C" {
@@ -1667,6 +1817,7 @@ int ims_batch_create(const ims_batch_item* items, uint32_t n_items, const ims_tu
     if (hipGetDeviceProperties(&prop, b->device) != hipSuccess) return bail(fail(IMS_E_HIP, "hipGetDeviceProperties failed"));
     b->cus = prop.multiProcessorCount;
     if (tuning) b->tuning = *tuning;
+    b->forms = tuning == nullptr;
     for (uint32_t i = 0; i < n_items; ++i) {
         const ims_batch_item& it = items[i];
         if (!it.graph || !it.trial_counts || !it.total || it.n_trials == 0 || (it.n_seeds > 0 && !it.seeds))
@@ -1705,14 +1856,13 @@ int ims_batch_create(const ims_batch_item* items, uint32_t n_items, const ims_tu
         P.n_seeds = (uint32_t)sv.size();
         P.cap = g->cap;
         bi.model = g->model;
-        if (g->model == IMS_MODEL_LT) b->any_lt = true;
         bi.trial_counts = it.trial_counts;
         bi.node_counts = it.node_counts;
         bi.total = it.total;
         b->host_items.push_back(bi);
         b->items.push_back(it);
         b->cost.push_back((double)P.W * (double)(g->m + g->n));
-        b->max_n = std::max<uint64_t>(b->max_n, (uint64_t)g->n);
+        b->seed_lists.push_back(std::move(sv));
     }
     int rc = dev_alloc(&b->d_items, std::max<size_t>(b->host_items.size(), 1));
     if (rc) return bail(rc);
@@ -1801,8 +1951,18 @@ int ims_batch_autotune(ims_batch* b, int repeats, void* stream, ims_tuning* chos
     // stage 1: launch shape and task size at the default switch points
     const ims_tuning shapes[] = {{2, 0, 2, 0, 0}, {2, 0, 4, 0, 0}, {4, 0, 4, 0, 0}, {2, 1, 4, 0, 0},
                                  {2, 0, 8, 0, 0}, {4, 0, 8, 0, 0}, {2, 0, 16, 0, 0}};
-    for (const ims_tuning& c : shapes)
-        if ((rc = trial(c))) break;
+    // (a default batch first as it stands, with its per-trial forms)
+    const bool had_forms = b->forms;
+    bool best_forms = false;
+    if (had_forms) {
+        rc = trial(b->tuning);
+        best_forms = true;
+        b->forms = false;
+    }
+    const double forms_ms = best_ms;
+    if (!rc)
+        for (const ims_tuning& c : shapes)
+            if ((rc = trial(c))) break;
     // stage 2: IC switch points for the best shape (1e-9: push only)
     if (!rc) {
         const ims_tuning base = best;
@@ -1820,7 +1980,9 @@ int ims_batch_autotune(ims_batch* b, int repeats, void* stream, ims_tuning* chos
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
+    b->forms = had_forms;
     if (rc) return rc;
+    b->forms = best_forms && best_ms >= forms_ms;
     b->tuning = best;
     if ((rc = batch_plan(b))) return rc;
     if (chosen) *chosen = best;

@@ -136,9 +136,9 @@ __device__ __forceinline__ Block4 philox_group(const PhiloxArc& a, uint64_t grou
 // 64-arc piece of that trial's row as it stands (no transpose); lane t keeps
 // trial t's eight pieces and stores them as one 64-byte line.  Bound by the
 // hash arithmetic.
-// `C` names outputs to zero here for the kernels that follow (status null: none).
+// `C` names outputs to zero here for the kernels that follow (total null: none).
 struct LiveClear {
-    uint32_t* status;       // four words
+    uint32_t* status;       // four words, or null
     uint64_t* total;        // one
     uint32_t* node_counts;  // [n] or null
     uint64_t n;
@@ -147,8 +147,8 @@ __global__ __launch_bounds__(kBlock) void live_draw_kernel(LiveClear C, uint64_t
                                                            uint64_t m, uint32_t t0, uint32_t tc, uint64_t seed)
 {
     const uint32_t lane = threadIdx.x & 63u;
-    if (C.status) {
-        if (blockIdx.x == 0 && threadIdx.x < 4) C.status[threadIdx.x] = 0;
+    if (C.total) {
+        if (C.status && blockIdx.x == 0 && threadIdx.x < 4) C.status[threadIdx.x] = 0;
         if (blockIdx.x == 0 && threadIdx.x == 4) *C.total = 0;
         if (C.node_counts)
             for (uint64_t v = (uint64_t)blockIdx.x * kBlock + threadIdx.x; v < C.n; v += (uint64_t)gridDim.x * kBlock) C.node_counts[v] = 0;

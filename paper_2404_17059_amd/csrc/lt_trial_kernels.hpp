@@ -48,8 +48,8 @@ template <int kBits>
 __global__ __launch_bounds__(kBlock) void lt_rows_kernel(LiveClear C, LtRun R)
 {
     const uint32_t lane = threadIdx.x & 63u;
-    if (C.status) {
-        if (blockIdx.x == 0 && threadIdx.x < 4) C.status[threadIdx.x] = 0;
+    if (C.total) {
+        if (C.status && blockIdx.x == 0 && threadIdx.x < 4) C.status[threadIdx.x] = 0;
         if (blockIdx.x == 0 && threadIdx.x == 4) *C.total = 0;
         if (C.node_counts)
             for (uint64_t v = (uint64_t)blockIdx.x * kBlock + threadIdx.x; v < C.n; v += (uint64_t)gridDim.x * kBlock) C.node_counts[v] = 0;

@@ -82,3 +82,40 @@ def test_per_trial_runs_match_the_oracle(ims, kind, n, m, trials, seeds, into):
     again = ims.simulate(G, sd, trials, 77, opts=forced)
     assert again["total"] == ref["total"]
     G.close()
+
+
+def test_default_batch_mixes_forms_and_replays(ims):
+    """A default batch runs items in per-trial forms beside the task list (a
+    subcritical IC item on a large trial count stays there); every output of
+    every launch equals the single runs', replays with work in between too."""
+    import torch
+    rng = np.random.default_rng(5)
+    items, singles = [], []
+    for i, (n, m, T) in enumerate([(300, 1500, 200), (2000, 9000, 130), (300, 900, 4200), (700, 4000, 65), (45000, 90000, 70), (40, 60, 3)] * 2):
+        off, idx = graph(n, m, rng, 150 if i == 3 else 0)
+        lt = i % 2 == 0 or i == 4
+        p = weights("random" if i in (2, 4) else "equal", n, idx, rng) if lt else np.full(idx.size, 0.01 if i == 7 else 0.3)
+        g = ims.Graph(n, off, idx, "lt" if lt else "ic", p)
+        sd = rng.choice(n, min(n, 300 if i == 1 else 8), replace=False).astype(np.uint32)
+        items.append((g, sd, T, 1000 + i))
+        r = ims.simulate(g, sd, T, 1000 + i, opts=ims.Opts(shape=2))
+        singles.append([r["trial_counts"].cpu().numpy().view(np.uint32), r["node_counts"].cpu().numpy().view(np.uint32), r["total"]])
+    B = ims.Batch(items)
+
+    def check(what):
+        for i, (got, want) in enumerate(zip(B.results(), singles)):
+            assert got["total"] == want[2], (what, i)
+            assert (got["trial_counts"] == want[0]).all(), (what, i)
+            assert (got["node_counts"] == want[1]).all(), (what, i)
+
+    for k in range(3):
+        B.launch()
+        check(f"launch {k}")
+        # other work on the device and on the graphs between the replays
+        ims.simulate(items[k][0], items[k][1], items[k][2], 3)
+        torch.ones(1 << 20, device="cuda").sum().item()
+    B.autotune(1)
+    for k in range(2):
+        B.launch()
+        check(f"after autotune {k}")
+    B.close()

@@ -71,6 +71,11 @@ __device__ __forceinline__ uint32_t wave_scan_incl(uint32_t x)
     return (uint32_t)v;
 }
 
+// Wait for the wavefront's outstanding loads here.  Without it the compiler,
+// which cannot see that a load behind a skipped branch has been waited for,
+// waits for every store in turn in the branches that follow.
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask)
 {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
@@ -419,10 +424,24 @@ __device__ __forceinline__ uint32_t live_cascade(const LiveGraph& G, uint32_t* b
     uint32_t* buf = sh.buf[wave];
     uint32_t par = 0;           // q[par] holds the level being filled
     uint32_t hi = 0, fill = 0;  // list entries below hi are final; fill: entries of the level being filled (one wavefront)
-    auto append = [&](bool fresh, uint32_t v) {
-        const uint64_t mask = __ballot(fresh);
-        if (mask == 0) return;
-        const uint32_t k = (uint32_t)__popcll(mask);
+    // visit v[y] of every lane with on[y]: the bitmap updates are issued
+    // together, then the new nodes of all slots take their places at once
+    auto visit = [&](const bool (&on)[kLiveBuf / 64], const uint32_t (&v)[kLiveBuf / 64]) {
+        bool fresh[kLiveBuf / 64];
+        wait_loads();
+#pragma unroll
+        for (uint32_t y = 0; y < kLiveBuf / 64; ++y) {
+            const uint32_t bit = 1u << (v[y] & 31u);
+            fresh[y] = on[y] && (atomicOr(&bm[v[y] >> 5], bit) & bit) == 0;
+        }
+        uint64_t mask[kLiveBuf / 64];
+        uint32_t k = 0;
+#pragma unroll
+        for (uint32_t y = 0; y < kLiveBuf / 64; ++y) {
+            mask[y] = __ballot(fresh[y]);
+            k += (uint32_t)__popcll(mask[y]);
+        }
+        if (k == 0) return;
         uint32_t at;
         if constexpr (kW == 1) {
             at = fill;
@@ -432,19 +451,15 @@ __device__ __forceinline__ uint32_t live_cascade(const LiveGraph& G, uint32_t* b
             if (lane == 0) at = atomicAdd(&sh.cnt, k);
             at = uniform32(at);
         }
-        if (fresh) {
-            const uint32_t pos = at + lanes_below(mask);
-            list[hi + pos] = v;
-            if (pos < kLiveQ) sh.q[par][pos] = v;
+#pragma unroll
+        for (uint32_t y = 0; y < kLiveBuf / 64; ++y) {
+            if (fresh[y]) {
+                const uint32_t pos = at + lanes_below(mask[y]);
+                list[hi + pos] = v[y];
+                if (pos < kLiveQ) sh.q[par][pos] = v[y];
+            }
+            at += (uint32_t)__popcll(mask[y]);
         }
-    };
-    auto visit = [&](bool on, uint32_t v) {
-        bool fresh = false;
-        if (on) {
-            const uint32_t bit = 1u << (v & 31u);
-            fresh = (atomicOr(&bm[v >> 5], bit) & bit) == 0;
-        }
-        append(fresh, v);
     };
     if (kW > 1 && threadIdx.x == 0) {
         sh.cnt = 0;
@@ -452,8 +467,11 @@ __device__ __forceinline__ uint32_t live_cascade(const LiveGraph& G, uint32_t* b
     }
     __syncthreads();
     for (uint32_t i = 64 * wave; i < n_seeds; i += 64 * kW) {
-        const bool on = i + lane < n_seeds;
-        visit(on, on ? seed_at(i + lane) : 0u);
+        bool on[kLiveBuf / 64] = {};
+        uint32_t v[kLiveBuf / 64] = {};
+        on[0] = i + lane < n_seeds;
+        if (on[0]) v[0] = seed_at(i + lane);
+        visit(on, v);
     }
     steps = 0;
     uint32_t lev = 0, lo = 0;
@@ -486,12 +504,14 @@ __device__ __forceinline__ uint32_t live_cascade(const LiveGraph& G, uint32_t* b
             if (have) __builtin_memcpy(&r, G.off + u, sizeof r);
             // fetch and visit the targets of buf[0 .. nn)
             auto visit_buf = [&](uint32_t nn) {
+                bool on[kLiveBuf / 64];
                 uint32_t v[kLiveBuf / 64];
 #pragma unroll
-                for (uint32_t y = 0; y < kLiveBuf / 64; ++y) v[y] = 64 * y + lane < nn ? G.to[buf[64 * y + lane]] : 0u;
-#pragma unroll
-                for (uint32_t y = 0; y < kLiveBuf / 64; ++y)
-                    if (64 * y < nn) visit(64 * y + lane < nn, v[y]);
+                for (uint32_t y = 0; y < kLiveBuf / 64; ++y) {
+                    on[y] = 64 * y + lane < nn;
+                    v[y] = on[y] ? G.to[buf[64 * y + lane]] : 0u;
+                }
+                visit(on, v);
             };
             if constexpr (kPacked) {
                 any |= __ballot((r.x & kHasArcs) != 0) != 0;
@@ -515,12 +535,14 @@ __device__ __forceinline__ uint32_t live_cascade(const LiveGraph& G, uint32_t* b
                     const uint32_t a0 = (uint32_t)__builtin_amdgcn_readlane((int)k0, j);
                     const uint32_t a1 = a0 + (uint32_t)__builtin_amdgcn_readlane((int)deg, j);
                     for (uint32_t k = a0; k < a1; k += kLiveBuf) {
+                        bool on[kLiveBuf / 64];
                         uint32_t v[kLiveBuf / 64];
 #pragma unroll
-                        for (uint32_t y = 0; y < kLiveBuf / 64; ++y) v[y] = k + 64 * y + lane < a1 ? G.to[k + 64 * y + lane] : 0u;
-#pragma unroll
-                        for (uint32_t y = 0; y < kLiveBuf / 64; ++y)
-                            if (k + 64 * y < a1) visit(k + 64 * y + lane < a1, v[y]);
+                        for (uint32_t y = 0; y < kLiveBuf / 64; ++y) {
+                            on[y] = k + 64 * y + lane < a1;
+                            v[y] = on[y] ? G.to[k + 64 * y + lane] : 0u;
+                        }
+                        visit(on, v);
                     }
                 }
             } else {

@@ -14,7 +14,7 @@
 
 namespace imsim {
 
-constexpr uint32_t kLtRing = 512;  // most recent joins kept in LDS (older ones are read back from the list)
+constexpr uint32_t kLtRing = 256;  // most recent joins kept in LDS (older ones are read back from the list)
 
 // Per (node, trial) state by element width:
 //  8, 16: equal in-weights; 2^(bits-1) - k plus the active in-arcs so far, k
@@ -110,6 +110,7 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
     __shared__ LtTrialShared<kW> sh;
     constexpr uint32_t kHalf = kBits == 32 ? 0u : 1u << (kBits - 1);
     constexpr uint32_t kPer = 32 / kBits;  // elements per LDS word
+    constexpr uint32_t kSlots = kLiveBuf / 64;
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = kW == 1 ? 0u : uniform32(threadIdx.x >> 6);
     const uint32_t n = (uint32_t)R.n;
@@ -131,10 +132,17 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
         if (kW > 1 && threadIdx.x == 0) sh.tail = 0;
         __syncthreads();
         uint32_t tail = 0, head = 0, rounds = 0;
-        auto append = [&](bool fresh, uint32_t v) {
-            const uint64_t mask = __ballot(fresh);
-            if (mask == 0) return;
-            const uint32_t k = (uint32_t)__popcll(mask);
+        uint32_t seen = 0, kept = 0;  // joins of the rounds behind; the ring holds none before `kept`
+        // v[y] of every lane with fresh[y] joined
+        auto append = [&](const bool (&fresh)[kSlots], const uint32_t (&v)[kSlots]) {
+            uint64_t mask[kSlots];
+            uint32_t k = 0;
+#pragma unroll
+            for (uint32_t y = 0; y < kSlots; ++y) {
+                mask[y] = __ballot(fresh[y]);
+                k += (uint32_t)__popcll(mask[y]);
+            }
+            if (k == 0) return;
             uint32_t at;
             if constexpr (kW == 1) {
                 at = tail;
@@ -144,33 +152,34 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
                 if (lane == 0) at = atomicAdd(&sh.tail, k);
                 at = uniform32(at);
             }
-            if (fresh) {
-                const uint32_t pos = at + lanes_below(mask);
-                list[pos] = v;
-                sh.ring[pos % kLtRing] = v;
+#pragma unroll
+            for (uint32_t y = 0; y < kSlots; ++y) {
+                if (fresh[y]) {
+                    const uint32_t pos = at + lanes_below(mask[y]);
+                    list[pos] = v[y];
+                    sh.ring[pos % kLtRing] = v[y];
+                }
+                at += (uint32_t)__popcll(mask[y]);
             }
         };
-        // a newly active in-neighbour of weight wt
-        auto visit = [&](bool on, uint32_t v, uint64_t wt) {
-            bool fresh = false;
-            if (on) {
-                if constexpr (kBits == 32) {
-                    if (wt != 0 && wt > atomicSub(&st[v], (uint32_t)wt)) {
-                        const uint32_t bit = 1u << (v & 31u);
-                        fresh = (atomicOr(&bm[v >> 5], bit) & bit) == 0;  // (seeds cross too)
-                    }
-                } else {
-                    const uint32_t shift = (v % kPer) * kBits;
-                    const uint32_t old = atomicAdd(&st[v / kPer], 1u << shift) >> shift;
-                    fresh = (old & (2 * kHalf - 1)) == kHalf - 1;
-                }
+        // a newly active in-neighbour of weight wt: does it take v past its threshold
+        auto crosses = [&](uint32_t v, uint64_t wt) {
+            if constexpr (kBits == 32) {
+                if (wt == 0 || wt <= atomicSub(&st[v], (uint32_t)wt)) return false;
+                const uint32_t bit = 1u << (v & 31u);
+                return (atomicOr(&bm[v >> 5], bit) & bit) == 0;  // (seeds cross too)
+            } else {
+                const uint32_t shift = (v % kPer) * kBits;
+                const uint32_t old = atomicAdd(&st[v / kPer], 1u << shift) >> shift;
+                return (old & (2 * kHalf - 1)) == kHalf - 1;
             }
-            append(fresh, v);
         };
         for (uint32_t i = 64 * wave; i < S.count; i += 64 * kW) {
-            const bool on = i + lane < S.count;
-            const uint32_t v = on ? (S.more ? S.more[i + lane] : S.v[i + lane]) : 0u;
-            if (on) {
+            bool on[kSlots] = {};
+            uint32_t vs[kSlots] = {};
+            on[0] = i + lane < S.count;
+            if (on[0]) {
+                const uint32_t v = vs[0] = S.more ? S.more[i + lane] : S.v[i + lane];
                 if constexpr (kBits == 32) {
                     atomicOr(&bm[v >> 5], 1u << (v & 31u));
                 } else {
@@ -179,17 +188,21 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
                     atomicOr(&st[v / kPer], kHalf << shift);
                 }
             }
-            append(on, v);
+            append(on, vs);
         }
         for (;;) {
             __syncthreads();
             if constexpr (kW > 1) tail = sh.tail;
             if (head >= tail) break;
+            // joins of one round land in the ring in no order between the
+            // wavefronts, so a round of more than the ring holds leaves it unusable
+            if (kW > 1 && tail - seen > kLtRing) kept = tail;
+            seen = tail;
             const uint32_t end = tail - head < 64 * kW ? tail : head + 64 * kW;
             const uint32_t i = head + 64 * wave + lane;
             const bool have = i < end;
             uint32_t u = 0;
-            if (have) u = tail - i <= kLtRing ? sh.ring[i % kLtRing] : list[i];
+            if (have) u = tail - i <= kLtRing && i >= kept ? sh.ring[i % kLtRing] : list[i];
             head = end;
             ++rounds;
             if constexpr (kW > 1) __syncthreads();  // every entry is read before the ring moves on
@@ -200,18 +213,21 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
             const uint32_t incl = wave_scan_incl(c);
             const uint32_t total = uniform32((uint32_t)__builtin_amdgcn_readlane((int)incl, 63));
             auto visit_arcs = [&](auto arc_at, uint32_t nn) {
-                uint32_t v[kLiveBuf / 64];
-                uint64_t wt[kLiveBuf / 64];
+                // loads, updates and appends of all slots each go together
+                uint32_t v[kSlots];
+                uint64_t wt[kSlots];
+                bool fresh[kSlots];
 #pragma unroll
-                for (uint32_t y = 0; y < kLiveBuf / 64; ++y) {
+                for (uint32_t y = 0; y < kSlots; ++y) {
                     const bool on = 64 * y + lane < nn;
                     const uint32_t e = on ? arc_at(64 * y + lane) : 0u;
                     v[y] = on ? R.idx[e] : 0u;
                     wt[y] = kBits == 32 && on ? R.wout[e] : 0ull;
                 }
+                wait_loads();
 #pragma unroll
-                for (uint32_t y = 0; y < kLiveBuf / 64; ++y)
-                    if (64 * y < nn) visit(64 * y + lane < nn, v[y], wt[y]);
+                for (uint32_t y = 0; y < kSlots; ++y) fresh[y] = 64 * y + lane < nn && crosses(v[y], wt[y]);
+                append(fresh, v);
             };
             for (uint32_t win = 0; win < total; win += kLiveBuf) {
                 const uint32_t p = incl - c - win;  // wraps below the window

@@ -60,7 +60,8 @@ def weights(kind, n, idx, rng):
     ("equal", 500, 1500, 10, 0, 0),        # no seed
     ("random", 45000, 90000, 65, 40, 0),   # state outside the LDS, at each width
     ("equal", 80000, 160000, 9, 40, 300),
-    ("equal", 160000, 320000, 9, 400, 0),
+    ("equal", 160000, 320000, 9, 400, 0),  # more joins in one round than the ring keeps
+    ("equal", 20000, 400000, 9, 3000, 0),
 ])
 def test_per_trial_runs_match_the_oracle(ims, kind, n, m, trials, seeds, into):
     rng = np.random.default_rng([n, m, trials, into])

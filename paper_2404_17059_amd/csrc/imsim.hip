@@ -981,16 +981,19 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
     // (256 B), or hashes drawn in the kernel
     int lt_mode = 0;
     const uint64_t kmin_bytes = g->kplanes_total * ((W + imsim::kRowWords - 1) / imsim::kRowWords) * imsim::kRowWords * 8ull;
+    const uint64_t halves_bytes = n * ((W + imsim::kRowWords - 1) / imsim::kRowWords) * imsim::kRowWords * 128ull;
     if (shape == 2 && g->model == IMS_MODEL_LT && !(test_flags & 1)) {
         if (g->lt_uniform && !(test_flags & 4) && kmin_bytes <= kThresholdTableBudget && g->kplanes_total < (1ull << 32) &&
             !(test_flags & 8))
             lt_mode = 2;
+        else if (!(test_flags & 8) && halves_bytes <= kThresholdTableBudget)
+            lt_mode = 4;
         else if (cells * 256 <= kThresholdTableBudget) lt_mode = 1;
     }
     const bool use_table = lt_mode != 0;
     // (the count-threshold table has 64 bytes of padding: the sweep reads 64
     // bytes from each (node, word)'s first plane)
-    if (use_table && (rc = ensure_buf(g, g->thp, lt_mode == 2 ? kmin_bytes + 64 : cells * 256, false))) return rc;
+    if (use_table && (rc = ensure_buf(g, g->thp, lt_mode == 2 ? kmin_bytes + 64 : lt_mode == 4 ? halves_bytes : cells * 256, false))) return rc;
     if (g->seeds_cap < sv.size() || !g->d_seeds) {
         dev_free(g->d_seeds);
         dev_free(g->d_seed_pre);
@@ -1159,6 +1162,11 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
                 hipLaunchKernelGGL(imsim::ltg_kmin_kernel, dim3(fixed ? blocks : (uint32_t)g->cus * 16), dim3(imsim::kBlock), 0, s, P,
                                    (uint64_t*)g->thp.p);
                 IMS_HIP(hipGetLastError());
+            } else if (lt_mode == 4) {
+                P.kplanes = (const uint64_t*)g->thp.p;
+                hipLaunchKernelGGL(imsim::ltg_halves_kernel, dim3(fixed ? blocks : (uint32_t)g->cus * 16), dim3(imsim::kBlock), 0, s, P,
+                                   (uint64_t*)g->thp.p);
+                IMS_HIP(hipGetLastError());
             }
             const uint64_t work = std::max<uint64_t>(seed_pre.back(), (uint64_t)P.n_seeds * W);
             hipLaunchKernelGGL(imsim::ltg_seed_kernel,
@@ -1169,6 +1177,7 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
         uint32_t sweep_blocks = blocks, big_blocks = blocks;
         if (g->model == IMS_MODEL_LT) {
             sweep_blocks = lt_mode == 2   ? lt_blocks(imsim::ltg_sweep_kernel<2>)
+                           : lt_mode == 4 ? lt_blocks(imsim::ltg_sweep_kernel<4>)
                            : lt_mode == 1 ? lt_blocks(imsim::ltg_sweep_kernel<1>)
                                           : lt_blocks(imsim::ltg_sweep_kernel<0>);
             big_blocks = lt_blocks(imsim::ltg_sweep_kernel<3>);
@@ -1184,8 +1193,11 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
                     hipLaunchKernelGGL(imsim::grid_ic_level_kernel, dim3(blocks), dim3(imsim::kBlock), 0, s, P, st);
                 else
                 {
-                    if (lt_mode == 2) {
-                        hipLaunchKernelGGL(imsim::ltg_sweep_kernel<2>, dim3(sweep_blocks), dim3(imsim::kBlock), 0, s, P, st, tau);
+                    if (lt_mode == 2 || lt_mode == 4) {
+                        if (lt_mode == 2)
+                            hipLaunchKernelGGL(imsim::ltg_sweep_kernel<2>, dim3(sweep_blocks), dim3(imsim::kBlock), 0, s, P, st, tau);
+                        else
+                            hipLaunchKernelGGL(imsim::ltg_sweep_kernel<4>, dim3(sweep_blocks), dim3(imsim::kBlock), 0, s, P, st, tau);
                         if (g->nbig)
                             hipLaunchKernelGGL(imsim::ltg_sweep_kernel<3>,
                                                dim3(std::min<uint32_t>(big_blocks, (g->nbig + imsim::kWaves - 1) / imsim::kWaves)),

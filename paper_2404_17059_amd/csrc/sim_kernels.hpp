@@ -37,6 +37,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "philox.hpp"
 
 namespace imsim {
@@ -1060,6 +1062,115 @@ __device__ __forceinline__ uint64_t count_ge(const uint64_t (&c)[7], const uint6
     return carry;
 }
 
+// Sum of one (node, word) of 64 trials for the any-weights sweep (kMode 4): the
+// node's in-arc rows are lo .. lo + d - 1 of the staged state rows R (column
+// x) with their 32-bit weights in WT; maxd bounds d over the wavefront.
+// Returns the pending trials that join.
+__device__ __forceinline__ uint64_t weigh_sliced(const SimParams& P, const uint64_t* R, const uint32_t* WT, uint32_t x, uint32_t lo,
+                                                 uint32_t d, uint32_t maxd, uint64_t pend, uint64_t v, uint32_t wg, uint64_t G,
+                                                 uint64_t grp, uint32_t xc)
+{
+    const uint32_t* R32 = reinterpret_cast<const uint32_t*>(R);
+    const uint32_t* kp = reinterpret_cast<const uint32_t*>(P.kplanes + (v * kRowWords * G + grp * kRowWords + xc) * 16);
+    uint64_t dec = 0, close = 0;
+    // 32 trials at a time (both halves' sums at once spill registers)
+#pragma unroll 1
+    for (uint32_t h = 0; h < 2; ++h) {
+        uint32_t c[16];  // bit-sliced sums of the weights' top halves
+#pragma unroll
+        for (uint32_t b = 0; b < 16; ++b) c[b] = 0;
+        uint32_t over = 0;  // sums of 2^16 (all weights, to the bit)
+        for (uint32_t r = 0; r < maxd; ++r) {
+            // a lane whose row has ended adds nothing
+            const uint32_t at = lo + r < 64u ? lo + r : 64u;
+            const uint32_t in = r < d ? R32[2 * (at * kRowPitch + x) + h] : 0u;
+            const uint32_t w = WT[at & 63u];
+            uint32_t carry = 0;
+#pragma unroll
+            for (uint32_t b = 0; b < 16; ++b) {
+                const uint32_t t = in & (uint32_t)__builtin_amdgcn_sbfe((int)w, 16 + b, 1);
+                const uint32_t nc = __builtin_amdgcn_bitop3_b32(c[b], t, carry, 0xE8);
+                c[b] = __builtin_amdgcn_bitop3_b32(c[b], t, carry, 0x96);
+                carry = nc;
+            }
+            over |= carry;
+        }
+        // sum > threshold for certain: carry out of sum + ~threshold; possible
+        // at all: the same with d (what the halves cut off, less than one
+        // each) added
+        uint32_t sure = 0, maybe = 0, extra = 0;
+        if (pend) {
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q) {
+                const uint4 k4 = reinterpret_cast<const uint4*>(kp + 16 * h)[q];
+                const uint32_t k[4] = {k4.x, k4.y, k4.z, k4.w};
+#pragma unroll
+                for (uint32_t u = 0; u < 4; ++u) {
+                    const uint32_t b = 4 * q + u;
+                    sure = __builtin_amdgcn_bitop3_b32(c[b], k[u], sure, 0xE8);
+                    const uint32_t on = (uint32_t)__builtin_amdgcn_sbfe((int)d, b, 1);
+                    const uint32_t sum = __builtin_amdgcn_bitop3_b32(c[b], on, extra, 0x96);
+                    extra = __builtin_amdgcn_bitop3_b32(c[b], on, extra, 0xE8);
+                    maybe = __builtin_amdgcn_bitop3_b32(sum, k[u], maybe, 0xE8);
+                }
+            }
+        }
+        dec |= (uint64_t)(sure | over) << (32 * h);
+        close |= (uint64_t)(maybe | extra) << (32 * h);
+    }
+    dec &= pend;
+    close &= pend & ~dec;
+    while (close) {
+        const uint32_t t = (uint32_t)__builtin_ctzll(close);
+        close &= close - 1;
+        uint64_t sum = 0;
+        for (uint32_t r = 0; r < d; ++r)
+            if ((R[(lo + r) * kRowPitch + x] >> t) & 1ull) sum += WT[lo + r];
+        const Block4 blk = philox_block(v, ((uint64_t)P.w0 + wg + x) * 8 + (t >> 3), P.seed, kDomainLtNode);
+        if (sum > (uint64_t)block_lane(blk, t & 7u)) dec |= 1ull << t;
+    }
+    return dec;
+}
+
+// Threshold planes of the any-weights sweep: for node v, word group g and word
+// x of the group, 32-bit word b of the 128 bytes at ((v*G + g)*16 + x) has bit
+// t = NOT bit b of the top half of trial 64*(16g + x) + t's hash, word 16 + b
+// the same for t + 32.  A wavefront takes 8 nodes of
+// one word: lane 8j + q draws node j's trials 8q .. 8q + 7 and stages their
+// halves; then lane t packs trial t's halves of four nodes into one row, and
+// a 64x64 bit transpose puts plane b of the i-th of them in lane 16i + b.
+__global__ __launch_bounds__(kBlock) void ltg_halves_kernel(SimParams P, uint64_t* __restrict__ kplanes)
+{
+    __shared__ uint16_t stage[kWaves][8 * 66];
+    const uint64_t n = (uint64_t)P.n;
+    const uint64_t G = (P.W + kRowWords - 1) / kRowWords;
+    const uint64_t items = ((n + 7) / 8) * P.W;
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t j = lane >> 3, q = lane & 7u;
+    uint16_t* St = stage[threadIdx.x >> 6];
+    for (uint64_t it = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) >> 6; it < items; it += ((uint64_t)gridDim.x * kBlock) >> 6) {
+        const uint64_t w = it % P.W, v0 = (it / P.W) * 8;
+        const Block4 b = philox_block(v0 + j, ((uint64_t)P.w0 + w) * 8 + q, P.seed, kDomainLtNode);
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (uint32_t i = 0; i < 8; ++i) St[j * 66 + 8 * q + i] = (uint16_t)(block_lane(b, i) >> 16);
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (uint32_t h = 0; h < 2; ++h) {
+            uint64_t row = 0;
+#pragma unroll
+            for (uint32_t i = 0; i < 4; ++i) row |= (uint64_t)St[(4 * h + i) * 66 + lane] << (16 * i);
+            const uint64_t r = wave_transpose64(row, lane);
+            const uint64_t v = v0 + 4 * h + (lane >> 4);
+            if (v < n) {
+                uint32_t* out = reinterpret_cast<uint32_t*>(kplanes + ((v * G + w / kRowWords) * kRowWords + w % kRowWords) * 16);
+                out[lane & 15u] = (uint32_t)~r;
+                out[16 + (lane & 15u)] = (uint32_t)(~r >> 32);
+            }
+        }
+    }
+}
+
 // LT sweep `sw` over all words, in place.  Direction switch: a sweep "marks"
 // when the previous sweep changed fewer than `tau` (node, word) pairs: every
 // node that joins then stamps its out-neighbours with sw + 2 in aux (node-
@@ -1074,9 +1185,15 @@ __device__ __forceinline__ uint64_t count_ge(const uint64_t (&c)[7], const uint6
 // kMode: 0 = threshold hashes drawn in the kernel, 1 = threshold table,
 // 2 = count-threshold table (equal in-weights) for batches of at most 64
 // in-arc pieces, 3 = the batches of one node with a longer row, hashes drawn
-// in the kernel (launched after kMode 2 in the same sweep).
+// in the kernel (launched after kMode 2 or 4 in the same sweep), 4 = as 2 for
+// any in-weights: their top 16 bits are summed bit-sliced (a lane adds one
+// arc to 64 trials' sums at once, where a lane per trial adds one) and
+// compared with the top 16 bits of the thresholds; the sum is low by less
+// than one unit per in-arc, so it settles every trial but those that close to
+// their threshold, about one in 8,000 at 8 in-arcs, which are summed exactly
+// (100k-node power-law graph, random weights: a dense sweep 0.52 -> SWEEP4 ms).
 template <int kMode>
-__global__ __launch_bounds__(kBlock, 4) void ltg_sweep_kernel(SimParams P, uint32_t sw, uint32_t tau)
+__global__ __launch_bounds__(kBlock, kMode == 4 ? 3 : 4) void ltg_sweep_kernel(SimParams P, uint32_t sw, uint32_t tau)
 {
     // 64 staged rows, and 4 more that the count form may read (masked)
     __shared__ uint64_t rows[kWaves][68 * kRowPitch];
@@ -1287,7 +1404,8 @@ __global__ __launch_bounds__(kBlock, 4) void ltg_sweep_kernel(SimParams P, uint3
             __builtin_amdgcn_wave_barrier();
         }
     };
-    if (kMode == 2) {
+    constexpr bool kSliced = kMode == 2 || kMode == 4;
+    if constexpr (kSliced) {
         // count thresholds, bit-sliced.  In a dense sweep batch descriptors
         // come two batches ahead and, over at most 16 words, the own states,
         // in-arc sources and node offsets one batch ahead, so a batch starts
@@ -1302,22 +1420,27 @@ __global__ __launch_bounds__(kBlock, 4) void ltg_sweep_kernel(SimParams P, uint3
         // a batch's in-arc source of this lane and the in-CSR offsets of its
         // nodes 0 .. nn (low halves suffice: only differences below 2^32 are
         // used), from clamped addresses
-        auto src_of = [&](const u32x4 d) -> uint32_t {
+        // (kMode 4: with the weight in the high half)
+        using SrcOf = typename std::conditional<kMode == 4, uint64_t, uint32_t>::type;
+        auto src_of = [&](const u32x4 d) -> SrcOf {
             const uint32_t dtot = uniform32(d.y) >> 8;
             const uint64_t da0 = (uint64_t)uniform32(d.z) | ((uint64_t)uniform32(d.w) << 32);
-            if (dtot == 0) return 0u;  // no in-arc to read (the batch is skipped)
-            return P.in_src32[da0 + (lane < dtot && dtot <= 64 ? lane : 0u)];
+            if (dtot == 0) return SrcOf{0};  // no in-arc to read (the batch is skipped)
+            if constexpr (kMode == 4) return P.in_arc[da0 + (lane < dtot && dtot <= 64 ? lane : 0u)];
+            else return P.in_src32[da0 + (lane < dtot && dtot <= 64 ? lane : 0u)];
         };
         // ... and, of the same nodes, the first threshold plane
         auto info_of = [&](const u32x4 d) -> uint2 {
             const uint32_t dvf = uniform32(d.x), dnn = uniform32(d.y) & 0xFFu;
-            return reinterpret_cast<const uint2*>(P.kinfo)[(uint64_t)dvf + (lane <= dnn ? lane : dnn)];
+            if constexpr (kMode == 4) return make_uint2((uint32_t)P.in_off[(uint64_t)dvf + (lane <= dnn ? lane : dnn)], 0u);
+            else return reinterpret_cast<const uint2*>(P.kinfo)[(uint64_t)dvf + (lane <= dnn ? lane : dnn)];
         };
         // a batch's first loads: own states (and marks in a marked sweep) of
         // both passes, in-arc source, node offsets and first planes
         struct First {
             uint64_t own[2];
-            uint32_t mk[2], src;
+            uint32_t mk[2];
+            SrcOf src;
             uint2 info;
         };
         auto first_of = [&](const u32x4 d, First& f) {
@@ -1383,7 +1506,7 @@ __global__ __launch_bounds__(kBlock, 4) void ltg_sweep_kernel(SimParams P, uint3
                     pending();
                     if (passes == 0) continue;
                 }
-                const uint32_t src = pre ? fc.src : src_of(dcur);
+                const SrcOf src = pre ? fc.src : src_of(dcur);
                 const uint2 info = pre ? fc.info : info_of(dcur);
                 const uint32_t offl = info.x;
                 // complemented threshold planes: 64 bytes from the lane's
@@ -1409,14 +1532,15 @@ __global__ __launch_bounds__(kBlock, 4) void ltg_sweep_kernel(SimParams P, uint3
                     for (uint32_t b = 0; b < 8; ++b) k[b] = b < S ? k[b] : ~0ull;
                 };
                 uint64_t k0[8];
-                load_planes(0, k0);
+                if constexpr (kMode == 2) load_planes(0, k0);
                 // stage the source rows of this word group: R[i][x] = state of
                 // in-arc i's source at word wg + x.  Plain loads: a mask read
                 // stale within a sweep only delays a join to the next sweep,
                 // and a sweep without joins saw the state it started from
                 {
-                    const uint64_t* rp = P.Anm + (uint64_t)src * W + wg;
+                    const uint64_t* rp = P.Anm + (uint64_t)(uint32_t)src * W + wg;
                     __builtin_amdgcn_wave_barrier();
+                    if constexpr (kMode == 4) WT[lane] = (uint32_t)(src >> 32);
                     if ((W & 1) == 0 && gw == kRowWords) {
                         uint64_t row[kRowWords];
                         const uint4* rp4 = reinterpret_cast<const uint4*>(rp);
@@ -1450,11 +1574,13 @@ __global__ __launch_bounds__(kBlock, 4) void ltg_sweep_kernel(SimParams P, uint3
                     const uint64_t pend = pq[p];
                     const uint64_t v = (uint64_t)vf + j;
                     uint64_t k[8];
-                    if (p == 0) {
+                    if constexpr (kMode == 2) {
+                        if (p == 0) {
 #pragma unroll
-                        for (uint32_t q = 0; q < 8; ++q) k[q] = k0[q];
-                    } else {
-                        load_planes(1, k);
+                            for (uint32_t q = 0; q < 8; ++q) k[q] = k0[q];
+                        } else {
+                            load_planes(1, k);
+                        }
                     }
                     // node j's in-arc rows: lo .. lo + d - 1
                     const uint32_t oj = (uint32_t)__shfl((int)offl, (int)j);
@@ -1472,20 +1598,25 @@ __global__ __launch_bounds__(kBlock, 4) void ltg_sweep_kernel(SimParams P, uint3
                         const uint32_t di = (uint32_t)__builtin_amdgcn_readlane((int)dj, (int)(16 * i));
                         if ((bp >> (16 * i)) & 0xFFFFull) maxd = di > maxd ? di : maxd;
                     }
-                    uint64_t c[7] = {0, 0, 0, 0, 0, 0, 0};
-                    for (uint32_t r = 0; r < maxd; r += 4) {
-                        // rows lo + r .. lo + r + 3; a lane whose row has
-                        // ended reads rows it masks (at most row 67)
-                        const uint32_t base = lo + r < 64u ? lo + r : 64u;
-                        const uint64_t* rr = R + base * kRowPitch + x;
-                        uint64_t in[4];
+                    uint64_t dec;
+                    if constexpr (kMode == 2) {
+                        uint64_t c[7] = {0, 0, 0, 0, 0, 0, 0};
+                        for (uint32_t r = 0; r < maxd; r += 4) {
+                            // rows lo + r .. lo + r + 3; a lane whose row has
+                            // ended reads rows it masks (at most row 67)
+                            const uint32_t base = lo + r < 64u ? lo + r : 64u;
+                            const uint64_t* rr = R + base * kRowPitch + x;
+                            uint64_t in[4];
 #pragma unroll
-                        for (uint32_t u = 0; u < 4; ++u) in[u] = rr[u * kRowPitch];
+                            for (uint32_t u = 0; u < 4; ++u) in[u] = rr[u * kRowPitch];
 #pragma unroll
-                        for (uint32_t u = 0; u < 4; ++u) in[u] = r + u < d ? in[u] : 0ull;
-                        add4(c, in[0], in[1], in[2], in[3]);
+                            for (uint32_t u = 0; u < 4; ++u) in[u] = r + u < d ? in[u] : 0ull;
+                            add4(c, in[0], in[1], in[2], in[3]);
+                        }
+                        dec = count_ge(c, k) & pend;
+                    } else {
+                        dec = weigh_sliced(P, R, WT, x, lo, d, maxd, pend, v, wg, G, grp, xc);
                     }
-                    const uint64_t dec = count_ge(c, k) & pend;
                     const uint64_t db = __ballot(dec != 0);
                     if (db == 0) continue;
                     if (dec) atomic_or64(&P.Anm[v * W + wg + x], dec);

@@ -111,7 +111,8 @@ typedef struct ims_opts {
                               bit 2 = LT without the equal-in-weights form; bit 3 = LT grid
                               shape with full threshold hashes instead of count thresholds;
                               bit 4 = IC drawn-coins form, LT per-trial form
-                              whatever the sizes say */
+                              whatever the sizes say; bit 5 = IC per-trial form drawing coins
+                              as arcs are met, likewise */
     /* IC direction (Section 3, "Algorithms", expands the out-arcs of the last
        step's new nodes: the push side).  The pull side instead lets every
        (node, word) pair with an inactive trial scan its in-arcs for frontier

@@ -563,8 +563,8 @@ int prof_end(ims_graph* g, hipStream_t s)
 // out-arcs of the target of a live arc) tells how far they go.  Measured on
 // Erdos-Renyi, preferential-attachment and small-world graphs of 500 to
 // 100,000 nodes, 64 to 10,000 trials, probabilities 0.01 to 0.1, TV, UR, WC:
-// - growth below 0.7: the other forms end in 60 to 130 us; this one takes
-//   55 us + draw + 10 ns per trial.  Level counts cost the others 0.2 ms.
+// - growth below 0.7: the other forms end sooner, but for level counts, which
+//   cost them 0.2 ms.
 // - up to 1.3: 1.1 to 3x faster up to a draw of 110 us (20,000-node ring, WC,
 //   300 trials 0.114 against 0.178 ms; 1,000 trials, draw 167 us, 0.24
 //   against 0.18).  Level counts: 2 to 12x at every size tried.
@@ -580,13 +580,29 @@ bool live_single_pays(const ims_graph* g, uint32_t n_trials, bool levels)
     const double draw = (double)g->m * (double)((n_trials + 7) / 8) / 150e3;
     // (64 trials' coin rows stay within about 4 GB)
     if ((uint64_t)g->n > kLiveNodes || g->n == 0 || g->m > (1ll << 29)) return false;
-    if (growth < 0.7) return levels ? draw <= 80.0 : draw + 0.01 * (double)n_trials <= 2.0;
+    if (growth < 0.7) return levels && draw <= 80.0;
     if (growth < 1.3) return draw <= (levels ? 2000.0 : 110.0);
     if (levels) return true;
     if (growth < 2.0) return draw <= 400.0;
     const double live_degree = g->ic_pbar * (double)g->ic_in_m / n;
     if (live_degree >= 3.0 && growth >= 1.5 * live_degree) return n < 20000.0 && n_trials < 4000;
     return true;
+}
+
+// Whether a one-set IC run takes the per-trial form that draws an arc's coin
+// when it meets the arc: cascades that stay small (growth below 0.7), or whose
+// dense draw does not pay, up to about 1,500 trials (above, the tasks of 4 to
+// 16 trials share a hash block between their trials; this form uses one
+// trial's eighth of it).  Measured against the tasks and the grid: 64 to 1,000
+// trials at probabilities 0.01 and 0.03 on 500 to 100,000 nodes 25 to 54
+// against 58 to 95 us (4,000 trials 100 to 150 against 73 to 100); 100,000-
+// node Erdos-Renyi, WC, 1,000 trials 1.3 against 2.3 ms.  Hubs of several
+// thousand out-arcs are walked by one workgroup a trial: there the others are
+// faster (100,000-node preferential attachment, 11 arcs a node: 2.1 / 1.7 ms).
+bool lazy_trials_pay(const ims_graph* g, uint32_t n_trials)
+{
+    if (g->n == 0 || (uint64_t)g->n > kLiveNodes || n_trials > 1500 || g->max_out > 4000) return false;
+    return g->ic_growth < 0.7 || (g->ic_growth < 1.3 && !live_single_pays(g, n_trials, false));
 }
 
 // Seeds as launch arguments, or uploaded when they are too many.
@@ -630,16 +646,21 @@ bool lt_trial_lds(const ims_graph* g)
 // attachment 1.4 / 127.  The sweeps win where a hub holding a notable part of
 // all arcs makes the cascade dense within few steps (and no node has more
 // in-arcs than a sweep stages): with hub seeds above about 200,000 arcs
-// (36,000 nodes 2.2 / 1.55; state outside the LDS, 45,000 nodes 13.2 / 4.0),
-// else above about a million (140,000 nodes, 15 arcs each: 7.6 / 4.4; state
-// outside the LDS: 45,000 nodes 3.6 / 4.9, 100,000 nodes 6.3 / 2.8).
-bool lt_trials_pay(const ims_graph* g, const std::vector<uint32_t>& sv)
+// (36,000 nodes 2.2 / 1.55), 90,000 with 32-bit states at 1,000 trials (87,000
+// arcs 0.90 / 0.90, 175,000 2.3 / 1.5) and more at fewer trials (100 trials:
+// 264,000 arcs 0.87 / 1.42), any number with the state outside the LDS (45,000
+// nodes 14.5 / 2.1); with other seeds above about a million (140,000 nodes,
+// 15 arcs each: 7.6 / 4.4), 300,000 outside the LDS (222,000 arcs 2.3 / 2.9,
+// 346,000 3.7 / 3.0).
+bool lt_trials_pay(const ims_graph* g, const std::vector<uint32_t>& sv, uint32_t n_trials)
 {
     if (g->max_out * 64 < (uint64_t)g->m || g->lt_max_in > 64) return true;
     uint64_t arcs = 0;
     for (uint32_t x : sv) arcs += (uint64_t)(g->h_off[x + 1] - g->h_off[x]);
     const bool dense = arcs * 16 >= (uint64_t)g->m;
-    return g->m <= (lt_trial_lds(g) ? (dense ? 200000 : 1060000) : (dense ? 0 : 400000));
+    if (!lt_trial_lds(g)) return !dense && g->m <= 300000;
+    if (!dense) return g->m <= 1060000;
+    return lt_trial_bits(g) == 32 ? (double)g->m * std::min(1000.0, (double)n_trials) <= 90e6 : g->m <= 200000;
 }
 
 // Kernel of a width, wavefront count and place of the state.
@@ -662,6 +683,7 @@ struct TrialRun {
     uint32_t n_trials = 0;
     uint32_t kw = 0;        // wavefronts per trial
     uint32_t bits = 0;      // LT: element width
+    bool lazy = false;      // IC: coins drawn as arcs are met
     bool nodes = false;     // final bitmaps are kept (for per-node outputs)
     uint64_t row_bytes = 0; // coin row or starting states of a trial
     uint64_t bm_words = 0;
@@ -675,7 +697,7 @@ struct TrialRun {
 
 // Launch shape of a run; `together` trials run at once on the device (those
 // of other runs beside it included).
-int trial_run_plan(TrialRun& P, const ims_graph* g, uint32_t n_trials, bool nodes, uint64_t together)
+int trial_run_plan(TrialRun& P, const ims_graph* g, uint32_t n_trials, bool nodes, uint64_t together, bool lazy)
 {
     using namespace imsim;
     const uint64_t n = (uint64_t)g->n, m = (uint64_t)g->m, cus = (uint64_t)g->cus;
@@ -684,7 +706,16 @@ int trial_run_plan(TrialRun& P, const ims_graph* g, uint32_t n_trials, bool node
     P.nodes = nodes;
     P.bm_words = 2 * ((n + 63) / 64);
     uint64_t per_cu;
-    if (g->model == IMS_MODEL_IC) {
+    P.lazy = lazy;
+    if (lazy) {
+        // (100,000-node preferential attachment, WC, 300 trials: 0.82 ms with
+        // one wavefront, 0.44 with four; elsewhere within 10%)
+        P.kw = 4;
+        P.entry = (const void*)lt_trial_kernel<1, 4, true>;
+        P.row_bytes = 0;
+        P.lds = P.bm_words * 4;
+        per_cu = std::min<uint64_t>(32 / P.kw, (160 * 1024) / (P.lds + 1024 * P.kw + 2048));
+    } else if (g->model == IMS_MODEL_IC) {
         // wavefronts per cascade: the fewer the trials, the more (20,000-node
         // Erdos-Renyi, UR, 64 trials: 1.02 / 0.37 / 0.23 ms with 1 / 4 / 8;
         // 1,000-node, 10,000 trials: one is fastest)
@@ -720,7 +751,7 @@ int trial_run_plan(TrialRun& P, const ims_graph* g, uint32_t n_trials, bool node
         per_cu = (uint64_t)fit;
     }
     P.slots = std::min<uint64_t>(n_trials, cus * per_cu);
-    P.tc = kLiveRowBudget / (P.row_bytes + (P.nodes ? P.bm_words * 4 : 0)) / 64 * 64;
+    P.tc = kLiveRowBudget / (P.row_bytes + (P.nodes ? P.bm_words * 4 : 0) + 1) / 64 * 64;
     P.tc = std::min<uint64_t>(std::max<uint64_t>(P.tc, 64), ((uint64_t)n_trials + 63) / 64 * 64);
     return IMS_OK;
 }
@@ -742,7 +773,7 @@ int trial_run_launch(const TrialRun& P, void* rows, void* queue, void* bitmaps, 
         const uint32_t words = (tc + 63) / 64;
         const LiveClear C = t0 == 0 ? LiveClear{status, total, node_counts, n} : LiveClear{};
         const dim3 grid((unsigned)std::min<uint64_t>(P.slots, tc)), block(64 * P.kw);
-        if (g->model == IMS_MODEL_IC) {
+        if (g->model == IMS_MODEL_IC && !P.lazy) {
             LiveParams L;
             std::memset(&L, 0, sizeof L);
             L.n = n;
@@ -781,15 +812,22 @@ int trial_run_launch(const TrialRun& P, void* rows, void* queue, void* bitmaps, 
             R.status = status ? status : spare;
             R.t0 = t0;
             R.tc = tc;
-            const uint64_t waves = (n + 63) / 64 * words;
-            auto start = P.bits == 8 ? lt_rows_kernel<8> : P.bits == 16 ? lt_rows_kernel<16> : lt_rows_kernel<32>;
-            hipLaunchKernelGGL(start, dim3((unsigned)((waves + kWaves - 1) / kWaves)), dim3(kBlock), 0, s, C, R);
+            if (P.lazy) {
+                R.thr = g->d_thr;
+                R.node_counts = node_counts;
+                if (C.total)
+                    hipLaunchKernelGGL(trial_clear_kernel, dim3((unsigned)std::min<uint64_t>((n + kBlock - 1) / kBlock, 1024)), dim3(kBlock), 0, s, C);
+            } else {
+                const uint64_t waves = (n + 63) / 64 * words;
+                auto start = P.bits == 8 ? lt_rows_kernel<8> : P.bits == 16 ? lt_rows_kernel<16> : lt_rows_kernel<32>;
+                hipLaunchKernelGGL(start, dim3((unsigned)((waves + kWaves - 1) / kWaves)), dim3(kBlock), 0, s, C, R);
+            }
             void* args[] = {&R, &S};
             IMS_HIP(hipLaunchKernel(P.entry, grid, block, args, P.lds, s));
         }
-        if (node_counts || active_bits)
+        if (active_bits || (node_counts && !P.lazy))
             hipLaunchKernelGGL(live_nodes_kernel, dim3((unsigned)(P.bm_words / 2), (words + kNodeWords - 1) / kNodeWords), dim3(kBlock), 0, s,
-                               (const uint32_t*)bm, P.bm_words, n, t0, tc, node_counts, active_bits);
+                               (const uint32_t*)bm, P.bm_words, n, t0, tc, P.lazy ? nullptr : node_counts, active_bits);
         IMS_HIP(hipGetLastError());
     }
     return IMS_OK;
@@ -798,14 +836,14 @@ int trial_run_launch(const TrialRun& P, void* rows, void* queue, void* bitmaps, 
 // One seed set (sorted, distinct: sv) in a per-trial form, in the graph's workspace.
 int simulate_trials(ims_graph* g, const std::vector<uint32_t>& sv, uint32_t n_trials, uint64_t rng_seed, uint32_t* trial_counts,
                     uint32_t* node_counts, uint64_t* total, uint64_t* active_bits, uint32_t* level_counts, uint32_t max_levels,
-                    const ims_opts* opts, hipStream_t s)
+                    const ims_opts* opts, bool lazy, hipStream_t s)
 {
     const bool timed = opts && opts->profile && g->prof_count < ims_graph::kProf;
     int rc;
     if (timed && (rc = prof_begin(g, s))) return rc;
     TrialRun P;
     imsim::LiveSeeds S;
-    if ((rc = trial_run_plan(P, g, n_trials, node_counts || active_bits, n_trials)) || (rc = ensure_buf(g, g->live_rows, P.rows(), false)) ||
+    if ((rc = trial_run_plan(P, g, n_trials, active_bits || (node_counts && !lazy), n_trials, lazy)) || (rc = ensure_buf(g, g->live_rows, P.rows(), false)) ||
         (rc = ensure_buf(g, g->live_queue, P.queue(), false)) || (P.nodes && (rc = ensure_buf(g, g->live_base, P.bitmaps(), false))) ||
         (rc = live_seeds(g, sv, S, s)) ||
         (rc = trial_run_launch(P, g->live_rows.p, g->live_queue.p, g->live_base.p, S, rng_seed, trial_counts, node_counts, total, active_bits,
@@ -879,12 +917,14 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
     const bool forced = opts && (opts->test_flags & 16);
     if (!form_asked && n > 0) {
         if (g->model == IMS_MODEL_IC) {
+            if (!level_counts && (opts && (opts->test_flags & 32) ? n <= kLiveNodes : !forced && lazy_trials_pay(g, n_trials)))
+                return simulate_trials(g, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, nullptr, 0, opts, true, s);
             if ((forced && n <= kLiveNodes) || live_single_pays(g, n_trials, level_counts != nullptr))
                 return simulate_trials(g, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, level_counts, max_levels,
-                                       opts, s);
+                                       opts, false, s);
         } else if (!level_counts && !(opts && ((opts->test_flags & ~16) || opts->alpha != 0.0))) {
-            if (forced || lt_trials_pay(g, sv))
-                return simulate_trials(g, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, nullptr, 0, opts, s);
+            if (forced || lt_trials_pay(g, sv, n_trials))
+                return simulate_trials(g, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, nullptr, 0, opts, false, s);
         }
     }
     if (level_counts) shape = 1;  // levels are the word-local (synchronous) steps
@@ -1004,8 +1044,10 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
     std::vector<uint64_t> seed_pre(sv.size() + 1, 0);
     for (size_t i = 0; i < sv.size(); ++i) seed_pre[i + 1] = seed_pre[i] + (uint64_t)(g->h_off[sv[i] + 1] - g->h_off[sv[i]]);
     if (!g->h_flag) IMS_HIP(hipHostMalloc((void**)&g->h_flag, 4 * sizeof(uint32_t), hipHostMallocDefault));
-    if ((rc = stage_upload(g->st_seeds, g->d_seeds, sv.data(), sv.size() * sizeof(uint32_t), s))) return rc;
-    if ((rc = stage_upload(g->st_pre, g->d_seed_pre, seed_pre.data(), seed_pre.size() * sizeof(uint64_t), s))) return rc;
+    // the slot form's seeds, item and cleared outputs come from one launch
+    const bool slot_prologue = slot_run && sv.size() <= imsim::kArgSeeds;
+    if (!slot_prologue && (rc = stage_upload(g->st_seeds, g->d_seeds, sv.data(), sv.size() * sizeof(uint32_t), s))) return rc;
+    if (!slot_run && (rc = stage_upload(g->st_pre, g->d_seed_pre, seed_pre.data(), seed_pre.size() * sizeof(uint64_t), s))) return rc;
 
     uint64_t* A = active_bits ? active_bits : (uint64_t*)g->A.p;
     // the LT grid shape keeps its state node-major and writes A (when asked
@@ -1023,9 +1065,9 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
         g->zero_dirty = false;
     }
     // (a later 16-word run keeps an earlier run's guard flag)
-    if (!accumulate && (rc = fill_async<uint32_t>(g->d_status, 4, 0u, s))) return rc;
-    if ((rc = fill_async<uint32_t>(trial_counts, n_trials, 0u, s))) return rc;
-    if (!accumulate && (rc = fill_async<unsigned long long>((unsigned long long*)total, 1, 0ull, s))) return rc;
+    if (!accumulate && !slot_prologue && (rc = fill_async<uint32_t>(g->d_status, 4, 0u, s))) return rc;
+    if (!slot_prologue && (rc = fill_async<uint32_t>(trial_counts, n_trials, 0u, s))) return rc;
+    if (!accumulate && !slot_prologue && (rc = fill_async<unsigned long long>((unsigned long long*)total, 1, 0ull, s))) return rc;
 
     imsim::SimParams P;
     P.n = g->n;
@@ -1084,7 +1126,7 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
     const bool prof = opts && opts->profile && g->prof_count < ims_graph::kProf;
     if (prof && (rc = prof_begin(g, s))) return rc;
     if (slot_run) {
-        if (node_counts && (rc = fill_async<uint32_t>(node_counts, n, 0u, s))) return rc;
+        if (!slot_prologue && node_counts && (rc = fill_async<uint32_t>(node_counts, n, 0u, s))) return rc;
         imsim::BatchItem it;
         std::memset(&it, 0, sizeof it);
         it.P = P;
@@ -1092,7 +1134,14 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
         it.trial_counts = trial_counts;
         it.node_counts = node_counts;
         it.total = total;
-        if ((rc = stage_upload(g->st_item, g->d_item, &it, sizeof it, s))) return rc;
+        if (slot_prologue) {
+            imsim::LiveSeeds S;
+            if ((rc = live_seeds(g, sv, S, s))) return rc;
+            hipLaunchKernelGGL(imsim::slot_prologue_kernel, dim3((uint32_t)std::min<uint64_t>((std::max<uint64_t>(n, n_trials) + 255) / 256, 256)),
+                               dim3(imsim::kBlock), 0, s, it, S, g->d_item, g->d_seeds, g->d_status);
+        } else if ((rc = stage_upload(g->st_item, g->d_item, &it, sizeof it, s))) {
+            return rc;
+        }
         imsim::SlotBufs S{n,
                           (uint64_t*)g->sA.p,
                           (uint64_t*)g->sN.p,
@@ -1644,7 +1693,7 @@ int batch_plan_sides(ims_batch* b, std::vector<bool>& aside)
     for (uint32_t i = 0; i < (uint32_t)b->items.size(); ++i) {
         const ims_graph* g = b->items[i].graph;
         if (g->n == 0 || g->device != b->device) continue;
-        if (g->model == IMS_MODEL_IC ? live_single_pays(g, b->items[i].n_trials, false) : lt_trials_pay(g, b->seed_lists[i])) which.push_back(i);
+        if (g->model == IMS_MODEL_IC ? live_single_pays(g, b->items[i].n_trials, false) : lt_trials_pay(g, b->seed_lists[i], b->items[i].n_trials)) which.push_back(i);
     }
     std::stable_sort(which.begin(), which.end(), [&](uint32_t x, uint32_t y) { return b->cost[x] > b->cost[y]; });
     double load[ims_batch::kLanes] = {};
@@ -1659,7 +1708,7 @@ int batch_plan_sides(ims_batch* b, std::vector<bool>& aside)
             if (load[l] < load[sd.lane]) sd.lane = l;
         load[sd.lane] += b->cost[i];
         const uint64_t beside = std::min<uint64_t>(ims_batch::kLanes, which.size());
-        if ((rc = trial_run_plan(sd.run, g, b->items[i].n_trials, b->items[i].node_counts != nullptr, beside * b->items[i].n_trials))) return rc;
+        if ((rc = trial_run_plan(sd.run, g, b->items[i].n_trials, b->items[i].node_counts != nullptr, beside * b->items[i].n_trials, false))) return rc;
         sd.seeds.count = (uint32_t)b->seed_lists[i].size();
         sd.seeds.more = sd.seeds.count > imsim::kArgSeeds ? b->dev_seeds[i] : nullptr;
         if (!sd.seeds.more) std::copy(b->seed_lists[i].begin(), b->seed_lists[i].end(), sd.seeds.v);

@@ -685,12 +685,29 @@ __global__ __launch_bounds__(64 * kW) void live_reach_kernel(LiveParams L)
 }
 
 // Seeds of a single-set run, passed with the launch when they fit.
-constexpr uint32_t kArgSeeds = 256;
+constexpr uint32_t kArgSeeds = 256;  // (a workgroup of kBlock threads places them)
+static_assert(kArgSeeds <= kBlock);
 struct LiveSeeds {
     uint32_t count;
     const uint32_t* more;  // the seeds in device memory when there are more than kArgSeeds, else null
     uint32_t v[kArgSeeds];
 };
+
+// What a slot run reads, put in place by one launch: its item, its seeds, its
+// cleared outputs (uploads and fills of their own took 30 us a run).
+__global__ __launch_bounds__(kBlock) void slot_prologue_kernel(BatchItem it, LiveSeeds S, BatchItem* __restrict__ item, uint32_t* __restrict__ seeds,
+                                                               uint32_t* __restrict__ status)
+{
+    const uint64_t i0 = (uint64_t)blockIdx.x * kBlock + threadIdx.x, step = (uint64_t)gridDim.x * kBlock;
+    for (uint64_t t = i0; t < it.P.T; t += step) it.trial_counts[t] = 0;
+    if (it.node_counts)
+        for (uint64_t v = i0; v < (uint64_t)it.P.n; v += step) it.node_counts[v] = 0;
+    if (blockIdx.x != 0) return;
+    if (threadIdx.x < S.count) seeds[threadIdx.x] = S.v[threadIdx.x];
+    if (threadIdx.x < 4) status[threadIdx.x] = 0;
+    if (threadIdx.x == 4) *it.total = 0;
+    if (threadIdx.x == 5) *item = it;
+}
 
 // One seed set over every trial of a range: workgroups run the trials t0 + b,
 // t0 + b + gridDim.x, ... over their coin rows and leave the final bitmaps for

@@ -23,6 +23,8 @@ constexpr uint32_t kLtRing = 256;  // most recent joins kept in LDS (older ones 
 //  32:    threshold minus the active in-weight so far, modulo 2^32: in-weights
 //         sum to at most 2^32, so "weight > remainder" holds at the crossing
 //         and never again; active bits in a bitmap of their own
+//  1:     IC, the coin of an out-arc drawn when its source has joined; the
+//         bitmap alone
 struct LtRun {
     uint64_t n;
     const uint32_t* __restrict__ off;  // [n + 1] out-CSR offsets
@@ -31,6 +33,8 @@ struct LtRun {
     const int64_t* __restrict__ in_off;   // in-CSR, equal in-weights: pieces per node
     const uint32_t* __restrict__ in_src;  // their sources
     const uint32_t* __restrict__ node_w;  // and their weight
+    const uint32_t* __restrict__ thr;     // IC: threshold per out-arc
+    uint32_t* node_counts;                // IC: [n] counted as nodes join, or null
     uint8_t* rows;      // [tc][stride] starting states
     uint64_t stride;    // bytes, a multiple of 16
     uint64_t seed;
@@ -90,6 +94,15 @@ __global__ __launch_bounds__(kBlock) void lt_rows_kernel(LiveClear C, LtRun R)
     }
 }
 
+// Zeroes a run's outputs (the IC runs here have no earlier kernel to do it).
+__global__ __launch_bounds__(kBlock) void trial_clear_kernel(LiveClear C)
+{
+    if (C.status && blockIdx.x == 0 && threadIdx.x < 4) C.status[threadIdx.x] = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 4) *C.total = 0;
+    if (C.node_counts)
+        for (uint64_t v = (uint64_t)blockIdx.x * kBlock + threadIdx.x; v < C.n; v += (uint64_t)gridDim.x * kBlock) C.node_counts[v] = 0;
+}
+
 template <int kW>
 struct LtTrialShared {
     uint32_t buf[kW][kLiveBuf];  // out-arcs waiting for their targets, per wavefront
@@ -110,12 +123,14 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
     __shared__ LtTrialShared<kW> sh;
     constexpr uint32_t kHalf = kBits == 32 ? 0u : 1u << (kBits - 1);
     constexpr uint32_t kPer = 32 / kBits;  // elements per LDS word
+    constexpr bool kIc = kBits == 1;
+    static_assert(!kIc || kLds, "the IC bitmap is in LDS");
     constexpr uint32_t kSlots = kLiveBuf / 64;
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = kW == 1 ? 0u : uniform32(threadIdx.x >> 6);
     const uint32_t n = (uint32_t)R.n;
     const uint32_t bm_words = 2 * ((n + 63) / 64);
-    const uint32_t st_words = (uint32_t)(R.stride / 4);
+    const uint32_t st_words = kIc ? 0u : (uint32_t)(R.stride / 4);
     uint32_t* buf = sh.buf[wave];
     uint32_t* list = R.queue + (uint64_t)blockIdx.x * R.n;
     uint64_t sum = 0;
@@ -124,14 +139,16 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
         uint32_t* const start = reinterpret_cast<uint32_t*>(R.rows + (uint64_t)row * R.stride);
         uint32_t* const st = kLds ? lds : start;
         uint32_t* const bm = kLds ? lds + st_words : R.bitmaps + (uint64_t)row * bm_words;
-        if constexpr (kLds)
+        if constexpr (kLds && !kIc)
             for (uint32_t i = threadIdx.x; i < st_words / 4; i += 64 * kW)
                 reinterpret_cast<uint4*>(lds)[i] = reinterpret_cast<const uint4*>(start)[i];
-        if (kBits == 32)
+        if (kBits == 32 || kIc)
             for (uint32_t i = threadIdx.x; i < bm_words; i += 64 * kW) bm[i] = 0;
         if (kW > 1 && threadIdx.x == 0) sh.tail = 0;
         __syncthreads();
         uint32_t tail = 0, head = 0, rounds = 0;
+        uint32_t level_end = 0;       // IC: rounds stay within a level (steps are counted by levels)
+        uint32_t level = 0;           // IC: levels begun; rounds = the last one holding a node with out-arcs
         uint32_t seen = 0, kept = 0;  // joins of the rounds behind; the ring holds none before `kept`
         // v[y] of every lane with fresh[y] joined
         auto append = [&](const bool (&fresh)[kSlots], const uint32_t (&v)[kSlots]) {
@@ -158,13 +175,25 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
                     const uint32_t pos = at + lanes_below(mask[y]);
                     list[pos] = v[y];
                     sh.ring[pos % kLtRing] = v[y];
+                    if (kIc && R.node_counts) atomicAdd(&R.node_counts[v[y]], 1u);
                 }
                 at += (uint32_t)__popcll(mask[y]);
             }
         };
         // a newly active in-neighbour of weight wt: does it take v past its threshold
-        auto crosses = [&](uint32_t v, uint64_t wt) {
-            if constexpr (kBits == 32) {
+        // (IC: wt is arc e's threshold, and its coin decides)
+        const uint32_t t = R.t0 + row;
+        auto crosses = [&](uint32_t v, uint64_t wt, uint32_t e) {
+            if constexpr (kIc) {
+                const uint32_t th = (uint32_t)wt;
+                if (th == 0) return false;
+                if (th != 0xFFFFFFFFu) {
+                    const Block4 b = philox_block_chain(e, t >> 3, R.seed, kDomainIcArc);
+                    if (block_lane(b, t & 7u) >= th) return false;
+                }
+                const uint32_t bit = 1u << (v & 31u);
+                return (atomicOr(&bm[v >> 5], bit) & bit) == 0;
+            } else if constexpr (kBits == 32) {
                 if (wt == 0 || wt <= atomicSub(&st[v], (uint32_t)wt)) return false;
                 const uint32_t bit = 1u << (v & 31u);
                 return (atomicOr(&bm[v >> 5], bit) & bit) == 0;  // (seeds cross too)
@@ -180,7 +209,7 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
             on[0] = i + lane < S.count;
             if (on[0]) {
                 const uint32_t v = vs[0] = S.more ? S.more[i + lane] : S.v[i + lane];
-                if constexpr (kBits == 32) {
+                if constexpr (kBits == 32 || kIc) {
                     atomicOr(&bm[v >> 5], 1u << (v & 31u));
                 } else {
                     const uint32_t shift = (v % kPer) * kBits;
@@ -198,17 +227,23 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
             // wavefronts, so a round of more than the ring holds leaves it unusable
             if (kW > 1 && tail - seen > kLtRing) kept = tail;
             seen = tail;
-            const uint32_t end = tail - head < 64 * kW ? tail : head + 64 * kW;
+            if (kIc && head == level_end) {
+                level_end = tail;
+                ++level;
+            }
+            const uint32_t stop = kIc ? level_end : tail;
+            const uint32_t end = stop - head < 64 * kW ? stop : head + 64 * kW;
             const uint32_t i = head + 64 * wave + lane;
             const bool have = i < end;
             uint32_t u = 0;
             if (have) u = tail - i <= kLtRing && i >= kept ? sh.ring[i % kLtRing] : list[i];
             head = end;
-            ++rounds;
+            if (!kIc) ++rounds;
             if constexpr (kW > 1) __syncthreads();  // every entry is read before the ring moves on
             uint2 r = make_uint2(0u, 0u);
             if (have) __builtin_memcpy(&r, R.off + u, sizeof r);
             const uint32_t deg = r.y - r.x;
+            if (kIc && __ballot(deg != 0)) rounds = level;  // (of this wavefront's nodes)
             const uint32_t c = deg <= kLaneArcs ? deg : 0u;
             const uint32_t incl = wave_scan_incl(c);
             const uint32_t total = uniform32((uint32_t)__builtin_amdgcn_readlane((int)incl, 63));
@@ -216,17 +251,22 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
                 // loads, updates and appends of all slots each go together
                 uint32_t v[kSlots];
                 uint64_t wt[kSlots];
+                uint32_t e[kSlots];
                 bool fresh[kSlots];
 #pragma unroll
                 for (uint32_t y = 0; y < kSlots; ++y) {
                     const bool on = 64 * y + lane < nn;
-                    const uint32_t e = on ? arc_at(64 * y + lane) : 0u;
-                    v[y] = on ? R.idx[e] : 0u;
-                    wt[y] = kBits == 32 && on ? R.wout[e] : 0ull;
+                    e[y] = on ? arc_at(64 * y + lane) : 0u;
+                    v[y] = on ? R.idx[e[y]] : 0u;
+                    wt[y] = kBits == 32 && on ? R.wout[e[y]] : kIc && on ? R.thr[e[y]] : 0ull;
                 }
                 wait_loads();
 #pragma unroll
-                for (uint32_t y = 0; y < kSlots; ++y) fresh[y] = 64 * y + lane < nn && crosses(v[y], wt[y]);
+                for (uint32_t y = 0; y < kSlots; ++y) {
+                    fresh[y] = false;
+                    if (kIc && 64 * y >= nn) continue;  // (no coins for empty slots)
+                    fresh[y] = 64 * y + lane < nn && crosses(v[y], wt[y], e[y]);
+                }
                 append(fresh, v);
             };
             for (uint32_t win = 0; win < total; win += kLiveBuf) {
@@ -251,7 +291,7 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
             uint32_t* out = R.bitmaps + (uint64_t)row * bm_words;
             for (uint32_t i = threadIdx.x; i < bm_words; i += 64 * kW) {
                 uint32_t x = 0;
-                if constexpr (kBits == 32) {
+                if constexpr (kBits == 32 || kIc) {
                     x = bm[i];
                 } else {
                     // the active bits of 32 nodes
@@ -272,10 +312,8 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
         max_rounds = rounds > max_rounds ? rounds : max_rounds;
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        if (sum) atomicAdd((unsigned long long*)R.total, (unsigned long long)sum);
-        if (max_rounds > load_relaxed32(&R.status[0])) atomicMax(&R.status[0], max_rounds);
-    }
+    if (threadIdx.x == 0 && sum) atomicAdd((unsigned long long*)R.total, (unsigned long long)sum);
+    if (lane == 0 && (kIc || threadIdx.x == 0) && max_rounds > load_relaxed32(&R.status[0])) atomicMax(&R.status[0], max_rounds);
 }
 
 }  // namespace imsim

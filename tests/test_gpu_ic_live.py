@@ -12,6 +12,7 @@ import pytest
 import oracle
 
 FORCED = 16  # Opts.test_flags: the drawn-coins form whatever the sizes say
+LAZY = 32    # the per-trial form that draws coins as it meets arcs
 
 pytestmark = pytest.mark.gpu
 
@@ -105,7 +106,8 @@ def test_drawn_coin_sets_match_the_oracle(ims, n, m, trials, p, count, most, hub
     (20000, 60000, 65, 0.5, 5, 9000),       # sixteen wavefronts
     (129, 700, 4096, 0.2, 3, 100),          # one wavefront
 ])
-def test_drawn_coin_run_matches_the_oracle(ims, n, m, trials, p, seeds, hub):
+@pytest.mark.parametrize("form", [FORCED, LAZY])
+def test_per_trial_run_matches_the_oracle(ims, n, m, trials, p, seeds, hub, form):
     rng = np.random.default_rng([n, m, trials, 1])
     off, idx = graph(n, m, rng, hub)
     k = idx.size
@@ -114,7 +116,7 @@ def test_drawn_coin_run_matches_the_oracle(ims, n, m, trials, p, seeds, hub):
     sd = rng.choice(n, seeds, replace=False).astype(np.uint32)
     G = ims.Graph(n, off, idx, "ic", prob)
     ref = oracle.simulate("ic", n, off, idx, oracle.encode("ic", prob), sd, trials, 99)
-    forced = ims.Opts(test_flags=FORCED)
+    forced = ims.Opts(test_flags=form)
     for want_bits in (True, False):
         got = ims.simulate(G, np.concatenate([sd, sd[:2]]), trials, 99, want_bits=want_bits, opts=forced)
         assert got["total"] == ref["total"]

@@ -311,12 +311,10 @@ def simulate_levels(graph: Graph, seeds, n_trials: int, rng_seed: int, max_level
 
 def pack_sets(sets) -> tuple[np.ndarray, np.ndarray]:
     """Concatenate seed sets into (offsets uint32[k+1], nodes uint32)."""
-    offs = np.zeros(len(sets) + 1, dtype=np.uint32)
-    parts = []
-    for i, st in enumerate(sets):
-        a = np.ascontiguousarray(st, dtype=np.uint32).ravel()
-        parts.append(a)
-        offs[i + 1] = offs[i] + a.shape[0]
+    parts = [st if type(st) is np.ndarray and st.dtype == np.uint32 and st.ndim == 1
+             else np.ascontiguousarray(st, dtype=np.uint32).ravel() for st in sets]
+    offs = np.zeros(len(parts) + 1, dtype=np.uint32)
+    np.cumsum([p.shape[0] for p in parts], out=offs[1:])
     nodes = np.concatenate(parts) if parts else np.zeros(0, dtype=np.uint32)
     return offs, np.ascontiguousarray(nodes, dtype=np.uint32)
 

@@ -605,6 +605,24 @@ bool lazy_trials_pay(const ims_graph* g, uint32_t n_trials)
     return g->ic_growth < 0.7 || (g->ic_growth < 1.3 && !live_single_pays(g, n_trials, false));
 }
 
+// The coin rows of trials t0 .. t0 + tc - 1 (row_words a multiple of 8).
+void launch_live_draw(const imsim::LiveClear& C, uint64_t* rows, uint64_t row_words, const uint32_t* thr, uint64_t m, uint32_t t0, uint32_t tc,
+                      uint64_t rng_seed, hipStream_t s)
+{
+    using namespace imsim;
+    const uint64_t waves = row_words * ((tc + 63) / 64);
+    // 64-byte stores want eight chunks a wavefront, a full chip some 8,000 wavefronts
+    if (waves / 8 >= 8192)
+        hipLaunchKernelGGL(live_draw_kernel<8>, dim3((unsigned)((waves / 8 + kWaves - 1) / kWaves)), dim3(kBlock), 0, s, C, rows, row_words, thr, m,
+                           t0, tc, rng_seed);
+    else if (waves / 2 >= 8192)
+        hipLaunchKernelGGL(live_draw_kernel<2>, dim3((unsigned)((waves / 2 + kWaves - 1) / kWaves)), dim3(kBlock), 0, s, C, rows, row_words, thr, m,
+                           t0, tc, rng_seed);
+    else
+        hipLaunchKernelGGL(live_draw_kernel<1>, dim3((unsigned)((waves + kWaves - 1) / kWaves)), dim3(kBlock), 0, s, C, rows, row_words, thr, m, t0,
+                           tc, rng_seed);
+}
+
 // Seeds as launch arguments, or uploaded when they are too many.
 int live_seeds(ims_graph* g, const std::vector<uint32_t>& sv, imsim::LiveSeeds& S, hipStream_t s)
 {
@@ -787,9 +805,7 @@ int trial_run_launch(const TrialRun& P, void* rows, void* queue, void* bitmaps, 
             L.status = status ? status : spare;
             L.t0 = t0;
             L.tc = tc;
-            const uint64_t waves = L.row_words / 8 * words;
-            hipLaunchKernelGGL(live_draw_kernel, dim3((unsigned)((waves + kWaves - 1) / kWaves)), dim3(kBlock), 0, s, C, L.rows, L.row_words,
-                               (const uint32_t*)g->d_thr, L.m, t0, tc, rng_seed);
+            launch_live_draw(C, L.rows, L.row_words, g->d_thr, L.m, t0, tc, rng_seed, s);
             void* args[] = {&L, &S, &bm, &trial_counts, &total, &level_counts, &max_levels};
             IMS_HIP(hipLaunchKernel(P.entry, grid, block, args, P.lds, s));
         } else {
@@ -1444,10 +1460,7 @@ int simulate_sets_live(ims_graph* g, const uint64_t* base, const uint32_t* h_off
         L.tc = std::min<uint32_t>((uint32_t)tc, n_trials - t0);
         const uint64_t words = (L.tc + 63) / 64;
         if ((rc = fill_async<uint32_t>(L.taken, 2 * kLiveQueues * kCtlStep + L.tc, 0u, s))) return rc;
-        const uint64_t draw_waves = row_words / 8 * words;
-        if (draw_waves > 0)
-            hipLaunchKernelGGL(live_draw_kernel, dim3((unsigned)((draw_waves + kWaves - 1) / kWaves)), dim3(kBlock), 0, s, LiveClear{}, L.rows, row_words,
-                               (const uint32_t*)g->d_thr, m, t0, L.tc, rng_seed);
+        if (row_words > 0) launch_live_draw(LiveClear{}, L.rows, row_words, g->d_thr, m, t0, L.tc, rng_seed, s);
         if (packed) hipLaunchKernelGGL(live_pack_kernel, dim3(L.tc), dim3(kPackBlock), 0, s, L);
         const uint64_t base_waves = bm_words / 2 * words;
         if (base && base_waves > 0)

@@ -136,11 +136,13 @@ __device__ __forceinline__ Block4 philox_group(const PhiloxArc& a, uint64_t grou
     return Block4{x0, x1, x2, x3};
 }
 
-// Coin rows: a wavefront takes 512 consecutive arcs (eight 64-arc chunks, lane
-// = arc) and one 64-trial word.  A coin's compare over the wavefront is the
+// Coin rows: a wavefront takes kChunks consecutive 64-arc chunks (lane = arc)
+// and one 64-trial word.  A coin's compare over the wavefront is the
 // 64-arc piece of that trial's row as it stands (no transpose); lane t keeps
-// trial t's eight pieces and stores them as one 64-byte line.  Bound by the
-// hash arithmetic.
+// trial t's pieces and stores them together, eight of them as one 64-byte
+// line.  Bound by the hash arithmetic (about 150 blocks a nanosecond) while
+// there are wavefronts for the chip; few arcs take one chunk each (10,000
+// arcs, 1,000 trials: 43 us with eight, 16 with one).
 // `C` names outputs to zero here for the kernels that follow (total null: none).
 struct LiveClear {
     uint32_t* status;       // four words, or null
@@ -148,6 +150,7 @@ struct LiveClear {
     uint32_t* node_counts;  // [n] or null
     uint64_t n;
 };
+template <uint32_t kChunks>
 __global__ __launch_bounds__(kBlock) void live_draw_kernel(LiveClear C, uint64_t* __restrict__ rows, uint64_t row_words, const uint32_t* __restrict__ thr,
                                                            uint64_t m, uint32_t t0, uint32_t tc, uint64_t seed)
 {
@@ -159,19 +162,19 @@ __global__ __launch_bounds__(kBlock) void live_draw_kernel(LiveClear C, uint64_t
             for (uint64_t v = (uint64_t)blockIdx.x * kBlock + threadIdx.x; v < C.n; v += (uint64_t)gridDim.x * kBlock) C.node_counts[v] = 0;
     }
     const uint64_t wave = uniform64(((uint64_t)blockIdx.x * kBlock + threadIdx.x) >> 6);
-    const uint64_t blocks8 = row_words / 8;
+    const uint64_t blocks8 = row_words / kChunks;
     const uint64_t words = (tc + 63) / 64;
     if (wave >= blocks8 * words) return;
     const uint64_t w = wave / blocks8, c8 = wave - w * blocks8;
     const uint32_t left = tc - (uint32_t)(64 * w);
     const uint32_t groups = left >= 64 ? 8u : (left + 7) / 8;
     const uint64_t g0 = t0 / 8 + 8 * w;  // t0 is a multiple of 64
-    uint32_t lo[8], hi[8];
+    uint32_t lo[kChunks], hi[kChunks];
 #pragma unroll
-    for (uint32_t k = 0; k < 8; ++k) {
+    for (uint32_t k = 0; k < kChunks; ++k) {
         lo[k] = 0;
         hi[k] = 0;
-        const uint64_t e = (8 * c8 + k) * 64 + lane;
+        const uint64_t e = (kChunks * c8 + k) * 64 + lane;
         const uint32_t th = e < m ? thr[e] : 0u;
         const uint64_t sure = __ballot(th == 0xFFFFFFFFu);
         if (__ballot(th != 0) == 0) continue;
@@ -188,9 +191,14 @@ __global__ __launch_bounds__(kBlock) void live_draw_kernel(LiveClear C, uint64_t
         }
     }
     if (lane < left) {
-        uint4* out = reinterpret_cast<uint4*>(rows + (64 * w + lane) * row_words + 8 * c8);
+        uint2* out = reinterpret_cast<uint2*>(rows + (64 * w + lane) * row_words + kChunks * c8);
+        if constexpr (kChunks == 1) {
+            out[0] = make_uint2(lo[0], hi[0]);
+        } else {
 #pragma unroll
-        for (uint32_t k = 0; k < 4; ++k) out[k] = make_uint4(lo[2 * k], hi[2 * k], lo[2 * k + 1], hi[2 * k + 1]);
+            for (uint32_t k = 0; k < kChunks; k += 2)
+                *reinterpret_cast<uint4*>(out + k) = make_uint4(lo[k], hi[k], lo[k + 1], hi[k + 1]);
+        }
     }
 }
 
@@ -424,20 +432,24 @@ __device__ __forceinline__ uint32_t live_cascade(const LiveGraph& G, uint32_t* b
     uint32_t* buf = sh.buf[wave];
     uint32_t par = 0;           // q[par] holds the level being filled
     uint32_t hi = 0, fill = 0;  // list entries below hi are final; fill: entries of the level being filled (one wavefront)
-    // visit v[y] of every lane with on[y]: the bitmap updates are issued
+    // visit v[y] of lane where 64 y + lane < nn: the bitmap updates are issued
     // together, then the new nodes of all slots take their places at once
-    auto visit = [&](const bool (&on)[kLiveBuf / 64], const uint32_t (&v)[kLiveBuf / 64]) {
+    auto visit = [&](uint32_t nn, const uint32_t (&v)[kLiveBuf / 64]) {
         bool fresh[kLiveBuf / 64];
         wait_loads();
 #pragma unroll
         for (uint32_t y = 0; y < kLiveBuf / 64; ++y) {
+            fresh[y] = false;
+            if (64 * y >= nn) continue;
             const uint32_t bit = 1u << (v[y] & 31u);
-            fresh[y] = on[y] && (atomicOr(&bm[v[y] >> 5], bit) & bit) == 0;
+            fresh[y] = 64 * y + lane < nn && (atomicOr(&bm[v[y] >> 5], bit) & bit) == 0;
         }
         uint64_t mask[kLiveBuf / 64];
         uint32_t k = 0;
 #pragma unroll
         for (uint32_t y = 0; y < kLiveBuf / 64; ++y) {
+            mask[y] = 0;
+            if (64 * y >= nn) continue;
             mask[y] = __ballot(fresh[y]);
             k += (uint32_t)__popcll(mask[y]);
         }
@@ -453,6 +465,7 @@ __device__ __forceinline__ uint32_t live_cascade(const LiveGraph& G, uint32_t* b
         }
 #pragma unroll
         for (uint32_t y = 0; y < kLiveBuf / 64; ++y) {
+            if (64 * y >= nn) break;
             if (fresh[y]) {
                 const uint32_t pos = at + lanes_below(mask[y]);
                 list[hi + pos] = v[y];
@@ -467,11 +480,9 @@ __device__ __forceinline__ uint32_t live_cascade(const LiveGraph& G, uint32_t* b
     }
     __syncthreads();
     for (uint32_t i = 64 * wave; i < n_seeds; i += 64 * kW) {
-        bool on[kLiveBuf / 64] = {};
         uint32_t v[kLiveBuf / 64] = {};
-        on[0] = i + lane < n_seeds;
-        if (on[0]) v[0] = seed_at(i + lane);
-        visit(on, v);
+        if (i + lane < n_seeds) v[0] = seed_at(i + lane);
+        visit(n_seeds - i < 64 ? n_seeds - i : 64u, v);
     }
     steps = 0;
     uint32_t lev = 0, lo = 0;
@@ -504,14 +515,10 @@ __device__ __forceinline__ uint32_t live_cascade(const LiveGraph& G, uint32_t* b
             if (have) __builtin_memcpy(&r, G.off + u, sizeof r);
             // fetch and visit the targets of buf[0 .. nn)
             auto visit_buf = [&](uint32_t nn) {
-                bool on[kLiveBuf / 64];
                 uint32_t v[kLiveBuf / 64];
 #pragma unroll
-                for (uint32_t y = 0; y < kLiveBuf / 64; ++y) {
-                    on[y] = 64 * y + lane < nn;
-                    v[y] = on[y] ? G.to[buf[64 * y + lane]] : 0u;
-                }
-                visit(on, v);
+                for (uint32_t y = 0; y < kLiveBuf / 64; ++y) v[y] = 64 * y + lane < nn ? G.to[buf[64 * y + lane]] : 0u;
+                visit(nn, v);
             };
             if constexpr (kPacked) {
                 any |= __ballot((r.x & kHasArcs) != 0) != 0;
@@ -535,14 +542,10 @@ __device__ __forceinline__ uint32_t live_cascade(const LiveGraph& G, uint32_t* b
                     const uint32_t a0 = (uint32_t)__builtin_amdgcn_readlane((int)k0, j);
                     const uint32_t a1 = a0 + (uint32_t)__builtin_amdgcn_readlane((int)deg, j);
                     for (uint32_t k = a0; k < a1; k += kLiveBuf) {
-                        bool on[kLiveBuf / 64];
                         uint32_t v[kLiveBuf / 64];
 #pragma unroll
-                        for (uint32_t y = 0; y < kLiveBuf / 64; ++y) {
-                            on[y] = k + 64 * y + lane < a1;
-                            v[y] = on[y] ? G.to[k + 64 * y + lane] : 0u;
-                        }
-                        visit(on, v);
+                        for (uint32_t y = 0; y < kLiveBuf / 64; ++y) v[y] = k + 64 * y + lane < a1 ? G.to[k + 64 * y + lane] : 0u;
+                        visit(a1 - k < kLiveBuf ? a1 - k : kLiveBuf, v);
                     }
                 }
             } else {

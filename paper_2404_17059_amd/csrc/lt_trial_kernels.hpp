@@ -264,7 +264,7 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
 #pragma unroll
                 for (uint32_t y = 0; y < kSlots; ++y) {
                     fresh[y] = false;
-                    if (kIc && 64 * y >= nn) continue;  // (no coins for empty slots)
+                    if (64 * y >= nn) continue;
                     fresh[y] = 64 * y + lane < nn && crosses(v[y], wt[y], e[y]);
                 }
                 append(fresh, v);

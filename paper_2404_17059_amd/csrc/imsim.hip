@@ -98,6 +98,7 @@ struct ims_graph {
     std::vector<int64_t> h_off;  // host copy of the out-offsets (launch planning)
     int64_t* d_off = nullptr;
     uint32_t* d_off32 = nullptr;  // the out-offsets in 32 bits (m < 2^32 - 1), for the per-trial forms
+    uint64_t* d_rec = nullptr;    // arc records of the per-trial forms (null: node, arc or degree count too large for them)
     uint32_t* d_idx = nullptr;
     uint32_t* d_thr = nullptr;
     int64_t* d_in_off = nullptr;     // in-CSR offsets (LT: weight pieces; IC: arcs of nonzero threshold)
@@ -185,6 +186,7 @@ struct ims_graph {
         dev_free(d_item);
         dev_free(d_off);
         dev_free(d_off32);
+        dev_free(d_rec);
         dev_free(d_idx);
         dev_free(d_thr);
         dev_free(d_in_off);
@@ -371,6 +373,14 @@ int ims_graph_create(int64_t n, int64_t m, const int64_t* offsets, const uint32_
     if ((rc = dev_alloc(&g->d_off32, off32.size()))) return bail(rc);
     if (hipMemcpy(g->d_off32, off32.data(), sizeof(uint32_t) * off32.size(), hipMemcpyHostToDevice) != hipSuccess)
         return bail(fail(IMS_E_HIP, "graph upload failed"));
+    if (n <= (1ll << imsim::kRecNodeBits) && m < (1ll << imsim::kRecArcBits) && max_deg < (1ull << (64 - imsim::kRecNodeBits - imsim::kRecArcBits))) {
+        if ((rc = dev_alloc(&g->d_rec, (uint64_t)m))) return bail(rc);
+        if (m > 0)
+            hipLaunchKernelGGL(imsim::arc_record_kernel, dim3((unsigned)std::min<int64_t>((m + imsim::kBlock - 1) / imsim::kBlock, 4096)),
+                               dim3(imsim::kBlock), 0, nullptr, (const uint32_t*)g->d_off32, (const uint32_t*)g->d_idx, (uint64_t)m, g->d_rec);
+        if (hipGetLastError() != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess)
+            return bail(fail(IMS_E_HIP, "arc records failed"));
+    }
     if (model == IMS_MODEL_IC) {
         if ((rc = dev_alloc(&g->d_thr, (uint64_t)m))) return bail(rc);
         if (m > 0 && hipMemcpy(g->d_thr, param, sizeof(uint32_t) * m, hipMemcpyHostToDevice) != hipSuccess)
@@ -578,8 +588,7 @@ bool live_single_pays(const ims_graph* g, uint32_t n_trials, bool levels)
 {
     const double n = (double)g->n, growth = g->ic_growth;
     const double draw = (double)g->m * (double)((n_trials + 7) / 8) / 150e3;
-    // (64 trials' coin rows stay within about 4 GB)
-    if ((uint64_t)g->n > kLiveNodes || g->n == 0 || g->m > (1ll << 29)) return false;
+    if ((uint64_t)g->n > kLiveNodes || g->n == 0 || !g->d_rec) return false;
     if (growth < 0.7) return levels && draw <= 80.0;
     if (growth < 1.3) return draw <= (levels ? 2000.0 : 110.0);
     if (levels) return true;
@@ -601,7 +610,7 @@ bool live_single_pays(const ims_graph* g, uint32_t n_trials, bool levels)
 // faster (100,000-node preferential attachment, 11 arcs a node: 2.1 / 1.7 ms).
 bool lazy_trials_pay(const ims_graph* g, uint32_t n_trials)
 {
-    if (g->n == 0 || (uint64_t)g->n > kLiveNodes || n_trials > 1500 || g->max_out > 4000) return false;
+    if (g->n == 0 || (uint64_t)g->n > kLiveNodes || !g->d_rec || n_trials > 1500 || g->max_out > 4000) return false;
     return g->ic_growth < 0.7 || (g->ic_growth < 1.3 && !live_single_pays(g, n_trials, false));
 }
 
@@ -672,6 +681,7 @@ bool lt_trial_lds(const ims_graph* g)
 // 346,000 3.7 / 3.0).
 bool lt_trials_pay(const ims_graph* g, const std::vector<uint32_t>& sv, uint32_t n_trials)
 {
+    if (!g->d_rec) return false;
     if (g->max_out * 64 < (uint64_t)g->m || g->lt_max_in > 64) return true;
     uint64_t arcs = 0;
     for (uint32_t x : sv) arcs += (uint64_t)(g->h_off[x + 1] - g->h_off[x]);
@@ -797,6 +807,7 @@ int trial_run_launch(const TrialRun& P, void* rows, void* queue, void* bitmaps, 
             L.n = n;
             L.off = g->d_off32;
             L.idx = g->d_idx;
+            L.rec = g->d_rec;
             L.m = (uint64_t)g->m;
             L.rows = (uint64_t*)rows;
             L.row_words = P.row_bytes / 8;
@@ -813,7 +824,7 @@ int trial_run_launch(const TrialRun& P, void* rows, void* queue, void* bitmaps, 
             std::memset(&R, 0, sizeof R);
             R.n = n;
             R.off = g->d_off32;
-            R.idx = g->d_idx;
+            R.rec = g->d_rec;
             R.wout = g->d_lt_wout;
             R.in_off = g->d_in_off;
             R.in_src = g->d_in_src32;
@@ -931,7 +942,7 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
     // options that shape the other forms keep them
     const bool form_asked = opts && (opts->shape || opts->blocks_per_cu || opts->ic_alpha != 0.0 || opts->ic_beta != 0.0 || opts->ic_direction);
     const bool forced = opts && (opts->test_flags & 16);
-    if (!form_asked && n > 0) {
+    if (!form_asked && n > 0 && g->d_rec) {
         if (g->model == IMS_MODEL_IC) {
             if (!level_counts && (opts && (opts->test_flags & 32) ? n <= kLiveNodes : !forced && lazy_trials_pay(g, n_trials)))
                 return simulate_trials(g, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, nullptr, 0, opts, true, s);
@@ -1370,8 +1381,7 @@ namespace {
 // all.
 bool live_sets_pay(const ims_graph* g, bool base, const std::vector<uint32_t>& off, const std::vector<uint32_t>& nodes, uint32_t n_trials)
 {
-    // (64 trials' coin rows and work lists stay within about 4 GB)
-    if ((uint64_t)g->n > kLiveNodes || g->n == 0 || g->m > (1ll << 29) || off.size() > (1u << 24)) return false;
+    if ((uint64_t)g->n > kLiveNodes || g->n == 0 || !g->d_rec || off.size() > (1u << 24)) return false;
     uint64_t arcs = 0;
     for (uint32_t v : nodes) arcs += (uint64_t)(g->h_off[v + 1] - g->h_off[v]);
     const double blocks = (double)((n_trials + 7) / 8);
@@ -1434,6 +1444,7 @@ int simulate_sets_live(ims_graph* g, const uint64_t* base, const uint32_t* h_off
     L.n = n;
     L.off = g->d_off32;
     L.idx = g->d_idx;
+    L.rec = g->d_rec;
     L.m = m;
     L.rows = (uint64_t*)g->live_rows.p;
     L.rank = (uint32_t*)g->live_rank.p;
@@ -1520,7 +1531,7 @@ int simulate_sets_impl(ims_graph* g, const uint64_t* base, const uint32_t* set_o
     if (node_counts && (rc = fill_async<uint32_t>(node_counts, (uint64_t)n_sets * n, 0u, s))) return rc;
     // options that shape the word-local tasks keep them
     const bool tasks_asked = opts && (opts->shape || opts->blocks_per_cu || opts->ic_alpha != 0.0 || opts->ic_beta != 0.0 || opts->ic_direction);
-    const bool live_forced = opts && (opts->test_flags & 16) && n > 0 && n <= kLiveNodes;
+    const bool live_forced = opts && (opts->test_flags & 16) && n > 0 && n <= kLiveNodes && g->d_rec;
     if (g->model == IMS_MODEL_IC && !tasks_asked &&
         (live_forced || live_sets_pay(g, base != nullptr, off, nodes, n_trials)))
         return simulate_sets_live(g, base, off.data(), d_off, d_nodes, n_sets, n_trials, rng_seed, totals, node_counts, s);

@@ -25,10 +25,32 @@ constexpr uint32_t kLiveBuf = 256;    // live arcs gathered per round and wavefr
 
 constexpr uint32_t kHasArcs = 1u << 31;
 
+// An arc's target with that node's own out-arcs: node (20 bits), first arc (24
+// bits), out-degree (20 bits).  A cascade that meets the target has its row
+// bounds at hand, one dependent read a step fewer than looking them up.
+constexpr uint32_t kRecNodeBits = 20, kRecArcBits = 24;
+__device__ __forceinline__ uint64_t arc_record(uint32_t v, uint32_t o0, uint32_t o1)
+{
+    return (uint64_t)v | ((uint64_t)o0 << kRecNodeBits) | ((uint64_t)(o1 - o0) << (kRecNodeBits + kRecArcBits));
+}
+__device__ __forceinline__ uint32_t rec_node(uint64_t r) { return (uint32_t)r & ((1u << kRecNodeBits) - 1u); }
+__device__ __forceinline__ uint32_t rec_first(uint64_t r) { return (uint32_t)(r >> kRecNodeBits) & ((1u << kRecArcBits) - 1u); }
+__device__ __forceinline__ uint32_t rec_degree(uint64_t r) { return (uint32_t)(r >> (kRecNodeBits + kRecArcBits)); }
+
+__global__ __launch_bounds__(kBlock) void arc_record_kernel(const uint32_t* __restrict__ off, const uint32_t* __restrict__ idx, uint64_t m,
+                                                            uint64_t* __restrict__ rec)
+{
+    for (uint64_t e = (uint64_t)blockIdx.x * kBlock + threadIdx.x; e < m; e += (uint64_t)gridDim.x * kBlock) {
+        const uint32_t v = idx[e];
+        rec[e] = arc_record(v, off[v], off[v + 1]);
+    }
+}
+
 struct LiveParams {
     uint64_t n;
     const uint32_t* __restrict__ off;  // [n + 1] out-CSR offsets
     const uint32_t* __restrict__ idx;
+    const uint64_t* __restrict__ rec;  // [m] arc records
     uint64_t m;
     uint64_t* rows;                    // [tc][row_words] coin bits of trial t0 + row, arc order
     uint64_t row_words;                // a multiple of 8
@@ -303,13 +325,14 @@ struct LiveGraph {
     const uint32_t* __restrict__ off;
     const uint32_t* __restrict__ to;
     const uint64_t* __restrict__ bits;
+    const uint64_t* __restrict__ rec;
 };
 
 template <bool kPacked>
 __device__ __forceinline__ LiveGraph live_graph(const LiveParams& L, uint32_t row)
 {
-    if constexpr (kPacked) return LiveGraph{L.loff + (uint64_t)row * (L.n + 1), L.llist + (uint64_t)row * L.list_cap, nullptr};
-    else return LiveGraph{L.off, L.idx, L.rows + (uint64_t)row * L.row_words};
+    if constexpr (kPacked) return LiveGraph{L.loff + (uint64_t)row * (L.n + 1), L.llist + (uint64_t)row * L.list_cap, nullptr, nullptr};
+    else return LiveGraph{L.off, L.idx, L.rows + (uint64_t)row * L.row_words, L.rec};
 }
 
 // Small cascades: lane = one (trial, set), which follows its cascade alone
@@ -408,7 +431,7 @@ __global__ __launch_bounds__(kBlock) void live_tiny_kernel(LiveParams L)
 template <int kW>
 struct LiveShared {
     uint32_t buf[kW][kLiveBuf];  // live arcs waiting for their targets, per wavefront
-    uint32_t q[2][kLiveQ];       // first entries of the current and the next level
+    uint64_t q[2][kLiveQ];       // first entries of the current and the next level (packed: nodes, else arc records)
     uint32_t cnt;                // nodes of the next level
     uint32_t arcs;               // the level holds a node with out-arcs
     uint32_t task, n_tasks;
@@ -421,7 +444,8 @@ struct LiveShared {
 // bounds; their live arcs are laid out densely in LDS (a prefix sum of the
 // counts) so that the targets are fetched 64 at a time, tested and set in the
 // bitmap and appended.  `level(l, count)` is told the size of every level.
-// Bound by the latency of the two dependent reads per round.  Returns the
+// Bound by the latency of the two dependent reads per round (bounds, target;
+// coin words, target record).  Returns the
 // node count; steps = levels holding a node with out-arcs.
 template <int kW, bool kPacked, typename SeedAt, typename Level>
 __device__ __forceinline__ uint32_t live_cascade(const LiveGraph& G, uint32_t* bm, uint32_t* list,
@@ -430,19 +454,26 @@ __device__ __forceinline__ uint32_t live_cascade(const LiveGraph& G, uint32_t* b
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = kW == 1 ? 0u : uniform32(threadIdx.x >> 6);
     uint32_t* buf = sh.buf[wave];
+    // what an arc leads to: a node, or its record
+    using To = typename std::conditional<kPacked, uint32_t, uint64_t>::type;
+    auto node_of = [](To x) -> uint32_t { return kPacked ? (uint32_t)x : rec_node(x); };
+    auto fetch = [&](uint32_t e) -> To {
+        if constexpr (kPacked) return G.to[e];
+        else return G.rec[e];
+    };
     uint32_t par = 0;           // q[par] holds the level being filled
     uint32_t hi = 0, fill = 0;  // list entries below hi are final; fill: entries of the level being filled (one wavefront)
     // visit v[y] of lane where 64 y + lane < nn: the bitmap updates are issued
     // together, then the new nodes of all slots take their places at once
-    auto visit = [&](uint32_t nn, const uint32_t (&v)[kLiveBuf / 64]) {
+    auto visit = [&](uint32_t nn, const To (&v)[kLiveBuf / 64]) {
         bool fresh[kLiveBuf / 64];
         wait_loads();
 #pragma unroll
         for (uint32_t y = 0; y < kLiveBuf / 64; ++y) {
             fresh[y] = false;
             if (64 * y >= nn) continue;
-            const uint32_t bit = 1u << (v[y] & 31u);
-            fresh[y] = 64 * y + lane < nn && (atomicOr(&bm[v[y] >> 5], bit) & bit) == 0;
+            const uint32_t u = node_of(v[y]), bit = 1u << (u & 31u);
+            fresh[y] = 64 * y + lane < nn && (atomicOr(&bm[u >> 5], bit) & bit) == 0;
         }
         uint64_t mask[kLiveBuf / 64];
         uint32_t k = 0;
@@ -468,7 +499,7 @@ __device__ __forceinline__ uint32_t live_cascade(const LiveGraph& G, uint32_t* b
             if (64 * y >= nn) break;
             if (fresh[y]) {
                 const uint32_t pos = at + lanes_below(mask[y]);
-                list[hi + pos] = v[y];
+                list[hi + pos] = node_of(v[y]);
                 if (pos < kLiveQ) sh.q[par][pos] = v[y];
             }
             at += (uint32_t)__popcll(mask[y]);
@@ -480,8 +511,12 @@ __device__ __forceinline__ uint32_t live_cascade(const LiveGraph& G, uint32_t* b
     }
     __syncthreads();
     for (uint32_t i = 64 * wave; i < n_seeds; i += 64 * kW) {
-        uint32_t v[kLiveBuf / 64] = {};
-        if (i + lane < n_seeds) v[0] = seed_at(i + lane);
+        To v[kLiveBuf / 64] = {};
+        if (i + lane < n_seeds) {
+            const uint32_t u = seed_at(i + lane);
+            if constexpr (kPacked) v[0] = u;
+            else v[0] = arc_record(u, G.off[u], G.off[u + 1]);
+        }
         visit(n_seeds - i < 64 ? n_seeds - i : 64u, v);
     }
     steps = 0;
@@ -508,16 +543,20 @@ __device__ __forceinline__ uint32_t live_cascade(const LiveGraph& G, uint32_t* b
         }
         for (uint32_t i = 64 * wave; i < count; i += 64 * kW) {
             const bool have = i + lane < count;
-            uint32_t u = 0;
-            if (have) u = i + lane < kLiveQ ? sh.q[par ^ 1u][i + lane] : list[lo + i + lane];
-            // both bounds in one 8-byte read
+            // the node's bounds: from its record, or (packed, and entries
+            // beyond the LDS) both in one 8-byte read
             uint2 r = make_uint2(0u, 0u);
-            if (have) __builtin_memcpy(&r, G.off + u, sizeof r);
+            if (have) {
+                const bool near = i + lane < kLiveQ;
+                const uint64_t x = near ? sh.q[par ^ 1u][i + lane] : (uint64_t)list[lo + i + lane];
+                if (!kPacked && near) r = make_uint2(rec_first(x), rec_first(x) + rec_degree(x));
+                else __builtin_memcpy(&r, G.off + (uint32_t)x, sizeof r);
+            }
             // fetch and visit the targets of buf[0 .. nn)
             auto visit_buf = [&](uint32_t nn) {
-                uint32_t v[kLiveBuf / 64];
+                To v[kLiveBuf / 64];
 #pragma unroll
-                for (uint32_t y = 0; y < kLiveBuf / 64; ++y) v[y] = 64 * y + lane < nn ? G.to[buf[64 * y + lane]] : 0u;
+                for (uint32_t y = 0; y < kLiveBuf / 64; ++y) v[y] = 64 * y + lane < nn ? fetch(buf[64 * y + lane]) : 0u;
                 visit(nn, v);
             };
             if constexpr (kPacked) {
@@ -542,9 +581,9 @@ __device__ __forceinline__ uint32_t live_cascade(const LiveGraph& G, uint32_t* b
                     const uint32_t a0 = (uint32_t)__builtin_amdgcn_readlane((int)k0, j);
                     const uint32_t a1 = a0 + (uint32_t)__builtin_amdgcn_readlane((int)deg, j);
                     for (uint32_t k = a0; k < a1; k += kLiveBuf) {
-                        uint32_t v[kLiveBuf / 64];
+                        To v[kLiveBuf / 64];
 #pragma unroll
-                        for (uint32_t y = 0; y < kLiveBuf / 64; ++y) v[y] = k + 64 * y + lane < a1 ? G.to[k + 64 * y + lane] : 0u;
+                        for (uint32_t y = 0; y < kLiveBuf / 64; ++y) v[y] = k + 64 * y + lane < a1 ? fetch(k + 64 * y + lane) : 0u;
                         visit(a1 - k < kLiveBuf ? a1 - k : kLiveBuf, v);
                     }
                 }

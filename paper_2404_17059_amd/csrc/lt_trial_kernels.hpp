@@ -28,7 +28,7 @@ constexpr uint32_t kLtRing = 256;  // most recent joins kept in LDS (older ones 
 struct LtRun {
     uint64_t n;
     const uint32_t* __restrict__ off;  // [n + 1] out-CSR offsets
-    const uint32_t* __restrict__ idx;
+    const uint64_t* __restrict__ rec;     // [m] arc records
     const uint64_t* __restrict__ wout;    // weight per out-arc (32-bit elements)
     const int64_t* __restrict__ in_off;   // in-CSR, equal in-weights: pieces per node
     const uint32_t* __restrict__ in_src;  // their sources
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(kBlock) void trial_clear_kernel(LiveClear C)
 template <int kW>
 struct LtTrialShared {
     uint32_t buf[kW][kLiveBuf];  // out-arcs waiting for their targets, per wavefront
-    uint32_t ring[kLtRing];      // join number i at i % kLtRing
+    uint64_t ring[kLtRing];      // the record of join number i at i % kLtRing
     uint32_t tail;               // joins so far
 };
 
@@ -114,8 +114,9 @@ struct LtTrialShared {
 // trial's state in LDS (kLds) or in its row where it stands.  A
 // round takes up to 64 * kW joined nodes (lane = node), lays their out-arcs
 // out densely in LDS (a prefix sum of the degrees), fetches 64 targets at a
-// time and updates them in LDS.  Bound by the chain of rounds: two dependent
-// reads (row bounds, targets) and the update.
+// time and updates them in LDS.  Bound by the chain of rounds: one dependent
+// read (the target records, which bring the next round's row bounds) and the
+// update.
 template <int kBits, int kW, bool kLds>
 __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
 {
@@ -151,7 +152,7 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
         uint32_t level = 0;           // IC: levels begun; rounds = the last one holding a node with out-arcs
         uint32_t seen = 0, kept = 0;  // joins of the rounds behind; the ring holds none before `kept`
         // v[y] of every lane with fresh[y] joined
-        auto append = [&](const bool (&fresh)[kSlots], const uint32_t (&v)[kSlots]) {
+        auto append = [&](const bool (&fresh)[kSlots], const uint64_t (&v)[kSlots]) {
             uint64_t mask[kSlots];
             uint32_t k = 0;
 #pragma unroll
@@ -173,9 +174,10 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
             for (uint32_t y = 0; y < kSlots; ++y) {
                 if (fresh[y]) {
                     const uint32_t pos = at + lanes_below(mask[y]);
-                    list[pos] = v[y];
+                    const uint32_t u = rec_node(v[y]);
+                    list[pos] = u;
                     sh.ring[pos % kLtRing] = v[y];
-                    if (kIc && R.node_counts) atomicAdd(&R.node_counts[v[y]], 1u);
+                    if (kIc && R.node_counts) atomicAdd(&R.node_counts[u], 1u);
                 }
                 at += (uint32_t)__popcll(mask[y]);
             }
@@ -205,10 +207,11 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
         };
         for (uint32_t i = 64 * wave; i < S.count; i += 64 * kW) {
             bool on[kSlots] = {};
-            uint32_t vs[kSlots] = {};
+            uint64_t vs[kSlots] = {};
             on[0] = i + lane < S.count;
             if (on[0]) {
-                const uint32_t v = vs[0] = S.more ? S.more[i + lane] : S.v[i + lane];
+                const uint32_t v = S.more ? S.more[i + lane] : S.v[i + lane];
+                vs[0] = arc_record(v, R.off[v], R.off[v + 1]);
                 if constexpr (kBits == 32 || kIc) {
                     atomicOr(&bm[v >> 5], 1u << (v & 31u));
                 } else {
@@ -235,21 +238,29 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
             const uint32_t end = stop - head < 64 * kW ? stop : head + 64 * kW;
             const uint32_t i = head + 64 * wave + lane;
             const bool have = i < end;
-            uint32_t u = 0;
-            if (have) u = tail - i <= kLtRing && i >= kept ? sh.ring[i % kLtRing] : list[i];
+            uint32_t o0 = 0, deg = 0;
+            if (have) {
+                if (tail - i <= kLtRing && i >= kept) {
+                    const uint64_t x = sh.ring[i % kLtRing];
+                    o0 = rec_first(x);
+                    deg = rec_degree(x);
+                } else {
+                    uint2 r;
+                    __builtin_memcpy(&r, R.off + list[i], sizeof r);
+                    o0 = r.x;
+                    deg = r.y - r.x;
+                }
+            }
             head = end;
             if (!kIc) ++rounds;
             if constexpr (kW > 1) __syncthreads();  // every entry is read before the ring moves on
-            uint2 r = make_uint2(0u, 0u);
-            if (have) __builtin_memcpy(&r, R.off + u, sizeof r);
-            const uint32_t deg = r.y - r.x;
             if (kIc && __ballot(deg != 0)) rounds = level;  // (of this wavefront's nodes)
             const uint32_t c = deg <= kLaneArcs ? deg : 0u;
             const uint32_t incl = wave_scan_incl(c);
             const uint32_t total = uniform32((uint32_t)__builtin_amdgcn_readlane((int)incl, 63));
             auto visit_arcs = [&](auto arc_at, uint32_t nn) {
                 // loads, updates and appends of all slots each go together
-                uint32_t v[kSlots];
+                uint64_t v[kSlots];
                 uint64_t wt[kSlots];
                 uint32_t e[kSlots];
                 bool fresh[kSlots];
@@ -257,7 +268,7 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
                 for (uint32_t y = 0; y < kSlots; ++y) {
                     const bool on = 64 * y + lane < nn;
                     e[y] = on ? arc_at(64 * y + lane) : 0u;
-                    v[y] = on ? R.idx[e[y]] : 0u;
+                    v[y] = on ? R.rec[e[y]] : 0ull;
                     wt[y] = kBits == 32 && on ? R.wout[e[y]] : kIc && on ? R.thr[e[y]] : 0ull;
                 }
                 wait_loads();
@@ -265,7 +276,7 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
                 for (uint32_t y = 0; y < kSlots; ++y) {
                     fresh[y] = false;
                     if (64 * y >= nn) continue;
-                    fresh[y] = 64 * y + lane < nn && crosses(v[y], wt[y], e[y]);
+                    fresh[y] = 64 * y + lane < nn && crosses(rec_node(v[y]), wt[y], e[y]);
                 }
                 append(fresh, v);
             };
@@ -273,7 +284,7 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
                 const uint32_t p = incl - c - win;  // wraps below the window
                 __builtin_amdgcn_wave_barrier();
                 for (uint32_t k = 0; k < c; ++k)
-                    if (p + k < kLiveBuf) buf[p + k] = r.x + k;
+                    if (p + k < kLiveBuf) buf[p + k] = o0 + k;
                 __builtin_amdgcn_wave_barrier();
                 visit_arcs([&](uint32_t k) { return buf[k]; }, total - win < kLiveBuf ? total - win : kLiveBuf);
             }
@@ -281,8 +292,8 @@ __global__ __launch_bounds__(64 * kW) void lt_trial_kernel(LtRun R, LiveSeeds S)
             while (longs) {
                 const int j = __builtin_ctzll(longs);
                 longs &= longs - 1;
-                const uint32_t a0 = (uint32_t)__builtin_amdgcn_readlane((int)r.x, j);
-                const uint32_t a1 = (uint32_t)__builtin_amdgcn_readlane((int)r.y, j);
+                const uint32_t a0 = (uint32_t)__builtin_amdgcn_readlane((int)o0, j);
+                const uint32_t a1 = a0 + (uint32_t)__builtin_amdgcn_readlane((int)deg, j);
                 for (uint32_t k0 = a0; k0 < a1; k0 += kLiveBuf)
                     visit_arcs([&](uint32_t k) { return k0 + k; }, a1 - k0 < kLiveBuf ? a1 - k0 : kLiveBuf);
             }

@@ -97,10 +97,11 @@ typedef struct ims_opts {
                               the cascades go far, else word-local when the run has at least a
                               quarter as many 64-trial words as compute units or they stay small,
                               else grid-wide; LT: a workgroup per trial where its state fits the
-                              LDS and it pays, else grid-wide), 1 = word-local (a workgroup runs the whole cascade of its
-                              trials: of one 64-trial word when active_bits is requested, else of
-                              16 trials on persistent slots that add their own counts), 2 = grid-
-                              wide steps (one launch per level / sweep) */
+                              LDS and it pays, else grid-wide), 1 = word-local (a workgroup runs
+                              the whole cascade of its trials: of one 64-trial word when
+                              active_bits is requested, else of 16 trials on persistent slots
+                              that add their own counts), 2 = grid-wide steps (one launch per
+                              level / sweep) */
     int32_t blocks_per_cu; /* workgroups per compute unit; 0 = auto */
     double alpha;          /* LT grid shape: a sweep marks out-neighbours of joining nodes (and the
                               next sweep evaluates marked nodes only) when the previous sweep
@@ -110,9 +111,9 @@ typedef struct ims_opts {
                               threshold table (hashes drawn in the kernel); bit 1 = unused;
                               bit 2 = LT without the equal-in-weights form; bit 3 = LT grid
                               shape with full threshold hashes instead of count thresholds;
-                              bit 4 = IC drawn-coins form, LT per-trial form
-                              whatever the sizes say; bit 5 = IC per-trial form drawing coins
-                              as arcs are met, likewise */
+                              bit 4 = IC drawn-coins form, LT per-trial form whatever the
+                              sizes say; bit 5 = IC per-trial form drawing coins as arcs are
+                              met, likewise */
     /* IC direction (Section 3, "Algorithms", expands the out-arcs of the last
        step's new nodes: the push side).  The pull side instead lets every
        (node, word) pair with an inactive trial scan its in-arcs for frontier
@@ -139,8 +140,9 @@ typedef struct ims_opts {
  *   node_counts   device uint32[n]: #{t : v in A_t}.                 optional (NULL)
  *   total         device uint64[1]: sum_t |A_t|; sigma = total / T.  required
  *   active_bits   device uint64[ceil(T/64) * n], word-major.         optional (NULL)
- * Asynchronous on `stream` in the word-local shape; the grid shape reads one
- * step counter back per batch of steps and so returns once its last step has
+ * Asynchronous on `stream` in the word-local shape and with a workgroup per
+ * trial; the grid shape reads one step counter back per batch of steps and so
+ * returns once its last step has
  * run (the final pass and the status words are still in flight then). */
 int ims_simulate(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_t n_trials,
                  uint64_t rng_seed, const ims_opts* opts, uint32_t* trial_counts,
@@ -157,7 +159,8 @@ int ims_simulate(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_t
  *   max_levels    >= 1; levels >= max_levels are not counted.
  *   level_counts  device uint32[max_levels * n_trials]: level_counts[l * T + t].
  *   trial_counts, total as ims_simulate.
- * Runs the word-local shape.  ims_graph_last_status() then gives the number
+ * Runs the word-local shape, or (IC, where it pays) a workgroup per trial over
+ * drawn coins.  ims_graph_last_status() then gives the number
  * of levels processed: the deepest nonempty level is at most that number, so
  * a caller that sees it >= max_levels can retry with a larger buffer. */
 int ims_simulate_levels(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_t n_trials, uint64_t rng_seed,

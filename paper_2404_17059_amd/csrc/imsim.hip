@@ -547,9 +547,9 @@ int set_ic_direction(imsim::SimParams& P, const ims_graph* g, double alpha, doub
     return IMS_OK;
 }
 
-// Device bytes the coin rows and the work lists of one trial range may take.
 // Largest graph of the drawn-coins form (its visited bitmap is 32 KB of LDS).
 constexpr uint64_t kLiveNodes = 1u << 18;
+// Device bytes the coin rows and the work lists of one trial range may take.
 constexpr uint64_t kLiveRowBudget = 1ull << 32, kLiveTodoBudget = 1ull << 29;
 
 int prof_begin(ims_graph* g, hipStream_t s)
@@ -577,24 +577,39 @@ int prof_end(ims_graph* g, hipStream_t s)
 //   cost them 0.2 ms.
 // - up to 1.3: 1.1 to 3x faster up to a draw of 110 us (20,000-node ring, WC,
 //   300 trials 0.114 against 0.178 ms; 1,000 trials, draw 167 us, 0.24
-//   against 0.18).  Level counts: 2 to 12x at every size tried.
-// - up to 2: 2 to 4x faster up to a draw of 400 us, slower from about 650.
+//   against 0.18).  With 16 arcs a node and more the other forms meet that
+//   many more: 1.7 to 3x faster up to the largest draw tried, 800 us (44 arcs,
+//   4,000 nodes, WC, 1,000 trials 0.33 against 0.70; 24 arcs, 12,000 nodes,
+//   3,000 trials 1.0 against 2.1), but not below growth 0.85.
+//   Level counts: 2 to 12x at every size tried.
+// - up to 2: 2 to 4x faster up to a draw of 400 us, slower from about 650;
+//   from 16 arcs a node 7 to 10x faster at 600 us.
 // - above: 1.5 to 13x faster at every size tried, but for skewed graphs with
-//   many live arcs per node, whose pull steps end early: there only with
-//   fewer than 20,000 nodes and 4,000 trials (3,000-node preferential
+//   many live arcs per node, or hubs, whose pull steps end early: there only
+//   with fewer than 20,000 nodes and 4,000 trials, and up to 90 million live
+//   arcs (16 arcs, 12,000 nodes, UR, 1,000 trials 0.99 against 1.08 ms, 3,000
+//   trials 2.4 against 1.6), 50 million on directed graphs with hubs (3,000-node preferential
 //   attachment, UR, 4,000 trials 1.24 against 0.77 ms; 300 trials 0.24
-//   against 0.49).
+//   against 0.49).  From eight live arcs a node every graph but a ring is
+//   covered in three or four levels, whose pull steps meet few arcs of a node:
+//   the walk over all live arcs pays up to 40 million of them, 100,000 a
+//   trial and 2,000 trials (44 arcs, 1,000 nodes, UR, 1,000 trials 0.26 against 0.39 ms; 4,000
+//   nodes 0.97 against 0.52; 12,000 nodes, 128 trials 1.1 against 0.63).
 bool live_single_pays(const ims_graph* g, uint32_t n_trials, bool levels)
 {
     const double n = (double)g->n, growth = g->ic_growth;
     const double draw = (double)g->m * (double)((n_trials + 7) / 8) / 150e3;
     if ((uint64_t)g->n > kLiveNodes || g->n == 0 || !g->d_rec) return false;
     if (growth < 0.7) return levels && draw <= 80.0;
-    if (growth < 1.3) return draw <= (levels ? 2000.0 : 110.0);
+    const bool dense = (double)g->m >= 16.0 * n;
+    if (growth < 1.3) return draw <= (levels ? 2000.0 : !dense || growth < 0.85 ? 110.0 : 800.0);
     if (levels) return true;
-    if (growth < 2.0) return draw <= 400.0;
+    if (growth < 2.0) return draw <= (dense ? 800.0 : 400.0);
     const double live_degree = g->ic_pbar * (double)g->ic_in_m / n;
-    if (live_degree >= 3.0 && growth >= 1.5 * live_degree) return n < 20000.0 && n_trials < 4000;
+    if (live_degree >= 8.0) return n_trials <= 2000 && live_degree * n <= 100e3 && live_degree * n * n_trials <= 40e6;
+    const bool skewed = growth >= 1.5 * live_degree, hubs = (double)g->max_out * n >= 20.0 * (double)g->m;
+    if (live_degree >= 3.0 && (skewed || hubs))
+        return n < 20000.0 && n_trials < 4000 && live_degree * n * n_trials <= (skewed ? 90e6 : 50e6);
     return true;
 }
 
@@ -607,11 +622,13 @@ bool live_single_pays(const ims_graph* g, uint32_t n_trials, bool levels)
 // against 58 to 95 us (4,000 trials 100 to 150 against 73 to 100); 100,000-
 // node Erdos-Renyi, WC, 1,000 trials 1.3 against 2.3 ms.  Hubs of several
 // thousand out-arcs are walked by one workgroup a trial: there the others are
-// faster (100,000-node preferential attachment, 11 arcs a node: 2.1 / 1.7 ms).
+// faster (100,000-node preferential attachment, 11 arcs a node: 2.1 / 1.7 ms),
+// and from growth 0.7 on graphs of 16 arcs a node and more (60 arcs, 12,000
+// nodes, WC, 1,000 trials 2.6 / 2.0 ms).
 bool lazy_trials_pay(const ims_graph* g, uint32_t n_trials)
 {
     if (g->n == 0 || (uint64_t)g->n > kLiveNodes || !g->d_rec || n_trials > 1500 || g->max_out > 4000) return false;
-    return g->ic_growth < 0.7 || (g->ic_growth < 1.3 && !live_single_pays(g, n_trials, false));
+    return g->ic_growth < 0.7 || (g->ic_growth < 1.3 && (double)g->m < 16.0 * (double)g->n && !live_single_pays(g, n_trials, false));
 }
 
 // The coin rows of trials t0 .. t0 + tc - 1 (row_words a multiple of 8).
@@ -677,7 +694,9 @@ bool lt_trial_lds(const ims_graph* g)
 // arcs 0.90 / 0.90, 175,000 2.3 / 1.5) and more at fewer trials (100 trials:
 // 264,000 arcs 0.87 / 1.42), any number with the state outside the LDS (45,000
 // nodes 14.5 / 2.1); with other seeds above about a million (140,000 nodes,
-// 15 arcs each: 7.6 / 4.4), 300,000 outside the LDS (222,000 arcs 2.3 / 2.9,
+// 15 arcs each: 7.6 / 4.4; where few trials leave the chip idle, half of
+// that: 800,000 arcs, 128 trials 2.0 / 1.7, 256 trials 2.0 / 1.9, 320 trials
+// 2.0 / 2.0), 300,000 outside the LDS (222,000 arcs 2.3 / 2.9,
 // 346,000 3.7 / 3.0).
 bool lt_trials_pay(const ims_graph* g, const std::vector<uint32_t>& sv, uint32_t n_trials)
 {
@@ -687,7 +706,7 @@ bool lt_trials_pay(const ims_graph* g, const std::vector<uint32_t>& sv, uint32_t
     for (uint32_t x : sv) arcs += (uint64_t)(g->h_off[x + 1] - g->h_off[x]);
     const bool dense = arcs * 16 >= (uint64_t)g->m;
     if (!lt_trial_lds(g)) return !dense && g->m <= 300000;
-    if (!dense) return g->m <= 1060000;
+    if (!dense) return g->m <= (n_trials < 320 ? 500000u : 1060000u);
     return lt_trial_bits(g) == 32 ? (double)g->m * std::min(1000.0, (double)n_trials) <= 90e6 : g->m <= 200000;
 }
 
@@ -1053,7 +1072,11 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
         if (g->lt_uniform && !(test_flags & 4) && kmin_bytes <= kThresholdTableBudget && g->kplanes_total < (1ull << 32) &&
             !(test_flags & 8))
             lt_mode = 2;
-        else if (!(test_flags & 8) && halves_bytes <= kThresholdTableBudget)
+        // the bit-sliced sums give a lane to each word of a row: below six
+        // words most lanes idle (100,000-node power-law graph, random weights:
+        // 2.1 against 1.2 ms at 2 words, 3.4 against 3.0 at 5, 3.5 against 3.6
+        // at 7, 3.1 against 7.3 at 16)
+        else if (!(test_flags & 8) && halves_bytes <= kThresholdTableBudget && (W >= 6 || cells * 256 > kThresholdTableBudget))
             lt_mode = 4;
         else if (cells * 256 <= kThresholdTableBudget) lt_mode = 1;
     }

@@ -445,10 +445,11 @@ struct LiveShared {
 // counts) so that the targets are fetched 64 at a time, tested and set in the
 // bitmap and appended.  `level(l, count)` is told the size of every level.
 // Bound by the latency of the two dependent reads per round (bounds, target;
-// coin words, target record).  Returns the
-// node count; steps = levels holding a node with out-arcs.
+// coin words, target record).  Once all n nodes are reached, the arcs left
+// lead nowhere new and are not walked.  Returns the node count; steps = levels
+// holding a node with out-arcs.
 template <int kW, bool kPacked, typename SeedAt, typename Level>
-__device__ __forceinline__ uint32_t live_cascade(const LiveGraph& G, uint32_t* bm, uint32_t* list,
+__device__ __forceinline__ uint32_t live_cascade(const LiveGraph& G, uint32_t n, uint32_t* bm, uint32_t* list,
                                                  LiveShared<kW>& sh, uint32_t n_seeds, SeedAt seed_at, Level level, uint32_t& steps)
 {
     const uint32_t lane = threadIdx.x & 63u;
@@ -552,6 +553,7 @@ __device__ __forceinline__ uint32_t live_cascade(const LiveGraph& G, uint32_t* b
                 if (!kPacked && near) r = make_uint2(rec_first(x), rec_first(x) + rec_degree(x));
                 else __builtin_memcpy(&r, G.off + (uint32_t)x, sizeof r);
             }
+            const bool all = hi + (kW == 1 ? fill : uniform32(*(volatile uint32_t*)&sh.cnt)) >= n;
             // fetch and visit the targets of buf[0 .. nn)
             auto visit_buf = [&](uint32_t nn) {
                 To v[kLiveBuf / 64];
@@ -561,6 +563,8 @@ __device__ __forceinline__ uint32_t live_cascade(const LiveGraph& G, uint32_t* b
             };
             if constexpr (kPacked) {
                 any |= __ballot((r.x & kHasArcs) != 0) != 0;
+                if (all && any) break;
+                if (all) continue;
                 const uint32_t k0 = r.x & ~kHasArcs;
                 const uint32_t deg = (r.y & ~kHasArcs) - k0;
                 const uint32_t c = deg <= kLaneArcs ? deg : 0u;
@@ -592,6 +596,8 @@ __device__ __forceinline__ uint32_t live_cascade(const LiveGraph& G, uint32_t* b
                 const uint32_t x0 = o0 >> 6;
                 const uint32_t nw = o1 > o0 ? ((o1 - 1) >> 6) - x0 + 1 : 0u;  // coin words of the row
                 any |= __ballot(nw != 0) != 0;
+                if (all && any) break;
+                if (all) continue;
                 // lay the set bits of up to two words per lane out in LDS and visit their targets
                 auto walk = [&](const uint64_t (&word)[2], uint32_t ebase) {
                     const uint32_t c = (uint32_t)(__popcll(word[0]) + __popcll(word[1]));
@@ -705,7 +711,7 @@ __global__ __launch_bounds__(64 * kW) void live_reach_kernel(LiveParams L)
                 const uint32_t s0 = L.set_off[set];
                 uint32_t steps;
                 const uint32_t cnt = live_cascade<kW, kPacked>(
-                    live_graph<kPacked>(L, row), bm, list, sh, L.set_off[set + 1] - s0,
+                    live_graph<kPacked>(L, row), (uint32_t)L.n, bm, list, sh, L.set_off[set + 1] - s0,
                     [&](uint32_t i) { return L.set_nodes[s0 + i]; }, [](uint32_t, uint32_t) {}, steps);
                 max_steps = steps > max_steps ? steps : max_steps;
                 if (threadIdx.x == 0 && cnt) atomicAdd((unsigned long long*)&L.totals[set], (unsigned long long)cnt);
@@ -769,7 +775,7 @@ __global__ __launch_bounds__(64 * kW) void live_single_kernel(LiveParams L, Live
         for (uint32_t i = threadIdx.x; i < bm_words; i += 64 * kW) bm[i] = 0;
         uint32_t steps;
         const uint32_t cnt = live_cascade<kW, false>(
-            live_graph<false>(L, row), bm, L.queue + (uint64_t)blockIdx.x * L.n, sh, S.count,
+            live_graph<false>(L, row), (uint32_t)L.n, bm, L.queue + (uint64_t)blockIdx.x * L.n, sh, S.count,
             [&](uint32_t i) { return S.more ? S.more[i] : S.v[i]; },
             [&](uint32_t l, uint32_t count) {
                 if (level_counts && threadIdx.x == 0 && l < max_levels) level_counts[(uint64_t)l * L.T + t] = count;

@@ -1191,7 +1191,7 @@ __global__ __launch_bounds__(kBlock) void ltg_halves_kernel(SimParams P, uint64_
 // compared with the top 16 bits of the thresholds; the sum is low by less
 // than one unit per in-arc, so it settles every trial but those that close to
 // their threshold, about one in 8,000 at 8 in-arcs, which are summed exactly
-// (100k-node power-law graph, random weights: a dense sweep 0.52 -> SWEEP4 ms).
+// (100k-node power-law graph, random weights: a dense sweep 0.52 -> 0.12 ms).
 template <int kMode>
 __global__ __launch_bounds__(kBlock, kMode == 4 ? 3 : 4) void ltg_sweep_kernel(SimParams P, uint32_t sw, uint32_t tau)
 {

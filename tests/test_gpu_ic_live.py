@@ -48,6 +48,8 @@ CASES = [
     (700, 3000, 130, "mixed", 40, 30, 600),  # packed live graphs, live rows above a lane's share
     (3000, 9000, 127, "one", 40, 8, 2500),
     (3000, 9000, 70, 0.0, 12, 8, 0),
+    (400, 40000, 9, "one", 12, 8, 0),       # every node reached with arcs left to walk
+    (400, 40000, 9, "one", 100, 8, 0),      # the same, packed
 ]
 
 
@@ -105,6 +107,8 @@ def test_drawn_coin_sets_match_the_oracle(ims, n, m, trials, p, count, most, hub
     (3000, 30000, 70, 0.3, 10, 2500),
     (20000, 60000, 65, 0.5, 5, 9000),       # sixteen wavefronts
     (129, 700, 4096, 0.2, 3, 100),          # one wavefront
+    (400, 40000, 65, 0.3, 3, 0),            # every node reached with arcs left to walk
+    (400, 40000, 4096, 0.3, 400, 0),        # the seeds are all nodes; one wavefront
 ])
 @pytest.mark.parametrize("form", [FORCED, LAZY])
 def test_per_trial_run_matches_the_oracle(ims, n, m, trials, p, seeds, hub, form):

@@ -55,7 +55,9 @@ def weights(kind, n, idx, rng):
     ("equal", 40000, 90000, 65, 30, 300),  # 16-bit states, 80 KB of LDS
     ("random", 63, 200, 9, 2, 0),
     ("random", 300, 1500, 130, 6, 250),
+    ("random", 300, 1500, 321, 6, 40),     # six words: the fewest that the sweeps sum bit-sliced
     ("zeros", 300, 1500, 65, 6, 100),
+    ("zeros", 300, 1500, 1025, 6, 100),    # sixteen words and one more
     ("random", 30000, 60000, 65, 40, 0),   # 32-bit states, 124 KB of LDS
     ("equal", 500, 1500, 10, 0, 0),        # no seed
     ("random", 45000, 90000, 65, 40, 0),   # state outside the LDS, at each width

@@ -44,7 +44,8 @@ def load_workload(name: str):
 # every source that decides what the simulation kernels do and how they are
 # launched (grid sizes, padding, threshold form): a measured traffic figure is
 # reported only while all of them are unchanged
-KERNEL_SOURCES = ["paper_2404_17059_amd/csrc/sim_kernels.hpp", "paper_2404_17059_amd/csrc/philox.hpp",
+KERNEL_SOURCES = ["paper_2404_17059_amd/csrc/sim_kernels.hpp", "paper_2404_17059_amd/csrc/live_kernels.hpp",
+                  "paper_2404_17059_amd/csrc/lt_trial_kernels.hpp", "paper_2404_17059_amd/csrc/philox.hpp",
                   "paper_2404_17059_amd/csrc/imsim.hip"]
 
 
@@ -163,7 +164,7 @@ def traffic_record(dirs, copy_mib: int, calls: int, workload: str) -> int:
     """Measured bytes per call from four rocprofv3 runs (FETCH_SIZE and
     WRITE_SIZE of the workload, then of the copy calibration): each counter is
     scaled by the bytes the copy is known to move per KiB it reads, summed over
-    the library's kernels and divided by the calls in the run.  Prints the
+    the library's per-call kernels and divided by the calls in the run.  Prints the
     per-kernel table and writes profiles/traffic_simulate_<workload>.json,
     keyed to the kernel sources."""
     fetch, fd = _counter_sums(dirs[0])
@@ -180,7 +181,8 @@ def traffic_record(dirs, copy_mib: int, calls: int, workload: str) -> int:
     print("| kernel | dispatches | FETCH_SIZE KiB | WRITE_SIZE KiB |\n|---|---:|---:|---:|")
     for k in names:
         print(f"| `{k[:90]}` | {fd.get(k, wd.get(k, 0))} | {fetch.get(k, 0):.0f} | {write.get(k, 0):.0f} |")
-    lib = [k for k in names if "imsim" in k]
+    # arc_record_kernel runs when the graph is created, not in a call
+    lib = [k for k in names if "imsim" in k and "arc_record_kernel" not in k]
     fb = sum(fetch.get(k, 0) for k in lib) * 1024 * fscale / calls
     wb = sum(write.get(k, 0) for k in lib) * 1024 * wscale / calls
     print(f"library kernels per call: read {fb / 1e9:.3f} GB, written {wb / 1e9:.3f} GB, total {(fb + wb) / 1e9:.3f} GB")

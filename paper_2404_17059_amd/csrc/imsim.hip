@@ -1411,9 +1411,31 @@ bool live_sets_pay(const ims_graph* g, bool base, const std::vector<uint32_t>& o
     const double draw = (double)g->m * blocks / 150e3;  // us
     if (base) {
         const double live = 250.0 + draw + 0.0025 * (double)n_trials * (double)(off.size() - 1);
-        const double tasks = std::max(150.0 + 0.015 * (double)g->n, 50.0 * (double)arcs * blocks / 150e3);
+        // the chain only where the sets are hubs (40,000-node preferential
+        // attachment, 8 random nodes, 1,000 trials: tasks 0.40, drawn 0.64 ms)
+        const bool hubs = (double)arcs * (double)g->n >= 4.0 * (double)g->m * (double)nodes.size();
+        const double tasks = std::max(hubs ? 150.0 + 0.015 * (double)g->n : 0.0, 50.0 * (double)arcs * blocks / 150e3);
         return g->ic_growth >= 0.8 && g->ic_growth <= 2.0 && live < tasks;
     }
+    // Where the tasks stay faster (whole calls in ms, tasks / drawn; random sets
+    // on graphs of 1,000 to 40,000 nodes, 5 to 44 arcs a node):
+    // - small cascades of many seeds, which a lane does not follow alone, and
+    //   of few sets (growth 0.16, 1,000 trials, 64 sets of 30 0.25 / 0.87, 16
+    //   single nodes 0.100 / 0.107; 256 single nodes 0.36 / 0.17); up to growth
+    //   0.9 with fewer than 16 arcs a node and many trials (64 sets of 30,
+    //   1,000 trials 0.69 / 0.92, 100 trials 0.44 / 0.21);
+    // - under four sets near growth 1 (0.14 / 0.16);
+    // - cascades that cover the graph in three levels, whose pull steps end
+    //   early, but for few walks (growth 39, 16 sets, 1,000 trials 0.85 / 1.68,
+    //   100 trials 0.81 / 0.44).
+    const uint64_t sets = off.size() - 1;
+    uint64_t large = 0;
+    for (uint64_t i = 0; i < sets; ++i) large += off[i + 1] - off[i] > imsim::kTinySeeds ? 1u : 0u;
+    const bool dense = (double)g->m >= 16.0 * (double)g->n;
+    if (g->ic_growth < 0.6 && (large || sets < 64)) return false;
+    if (g->ic_growth < 0.9 && !dense && large * n_trials > 8000) return false;
+    if (sets < 4 && g->ic_growth < (dense ? 0.85 : 1.4)) return false;
+    if (g->ic_growth >= 8.0 && sets * n_trials > 8000) return false;
     const double reach = g->ic_growth >= 0.8 ? 2000.0 : 8.0 / (1.0 - g->ic_growth);
     return (double)arcs * reach >= (double)g->m || (draw <= 20.0 && off.size() > 8);
 }

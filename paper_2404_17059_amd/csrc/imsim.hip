@@ -613,6 +613,21 @@ bool live_single_pays(const ims_graph* g, uint32_t n_trials, bool levels)
     return true;
 }
 
+// Whether an IC item of a batch does: the tasks share the chip there, so the
+// lines lie lower than for a run alone (batches of 8 items, ms, tasks / this:
+// 60,000 to 300,000 arcs, WC, 2,000 trials 2.7 / 2.9, at draws up to 40 us 0.94
+// / 0.37; 44 arcs a node, WC, draws of 300 us and more 4.4 / 6.0, up to 150 us
+// 1.5 / 0.9; 44 arcs a node, UR 0.59 / 0.80; 40 arcs, Erdos-Renyi, UR, 200
+// trials 1.05 / 0.42, 2,000 trials 2.1 / 2.3).
+bool live_item_pays(const ims_graph* g, uint32_t n_trials)
+{
+    if (!live_single_pays(g, n_trials, false)) return false;
+    const double n = (double)g->n, draw = (double)g->m * (double)((n_trials + 7) / 8) / 150e3;
+    if (g->ic_growth < 1.3) return draw <= ((double)g->m >= 16.0 * n ? 150.0 : 45.0);
+    const double live_degree = g->ic_pbar * (double)g->ic_in_m / n;
+    return live_degree < 8.0 || (g->ic_growth < 1.5 * live_degree && n_trials <= 500 && live_degree * n <= 60e3);
+}
+
 // Whether a one-set IC run takes the per-trial form that draws an arc's coin
 // when it meets the arc: cascades that stay small (growth below 0.7), or whose
 // dense draw does not pay, up to about 1,500 trials (above, the tasks of 4 to
@@ -1762,7 +1777,7 @@ int batch_plan_sides(ims_batch* b, std::vector<bool>& aside)
     for (uint32_t i = 0; i < (uint32_t)b->items.size(); ++i) {
         const ims_graph* g = b->items[i].graph;
         if (g->n == 0 || g->device != b->device) continue;
-        if (g->model == IMS_MODEL_IC ? live_single_pays(g, b->items[i].n_trials, false) : lt_trials_pay(g, b->seed_lists[i], b->items[i].n_trials)) which.push_back(i);
+        if (g->model == IMS_MODEL_IC ? live_item_pays(g, b->items[i].n_trials) : lt_trials_pay(g, b->seed_lists[i], b->items[i].n_trials)) which.push_back(i);
     }
     std::stable_sort(which.begin(), which.end(), [&](uint32_t x, uint32_t y) { return b->cost[x] > b->cost[y]; });
     double load[ims_batch::kLanes] = {};

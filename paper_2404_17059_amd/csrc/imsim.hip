@@ -1719,6 +1719,7 @@ struct ims_batch {
     ims_graph::Buf sA, sN, sQ0, sQ1, sQ2, sact, sstamp, ssteps, srem;
     bool any_lt = false;
     uint32_t slots = 0;
+    imsim_plan::SlotTags tags;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     hipStream_t capture_stream = nullptr;  // the null stream cannot be captured
@@ -1879,6 +1880,13 @@ int batch_plan(ims_batch* b)
     // LT items split into tasks of at most 16 trials run in push form: 16
     // threshold remainders per node and slot
     if (b->any_lt && b->tuning.split >= 4 && (rc = batch_buf(b->srem, cells * 8 * imsim::kRemWords))) return rc;
+    if (b->n_tasks && b->tags.replan(b->max_n, b->slots)) {
+        // (the null stream waits for no launch that still runs on another)
+        IMS_HIP(hipDeviceSynchronize());
+        for (ims_graph::Buf* t : {&b->srem, &b->sstamp, &b->ssteps})
+            if (t->p) IMS_HIP(hipMemset(t->p, 0, t->bytes));
+    }
+    IMS_HIP(hipStreamSynchronize(nullptr));  // cleared before a launch on any stream
     b->drop_graph();
     return IMS_OK;
 }

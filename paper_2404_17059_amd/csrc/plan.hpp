@@ -184,4 +184,24 @@ inline void lt_batches(int64_t n, const std::vector<int64_t>& in_off, LtBatches&
     }
 }
 
+// Slot state of a batch.  A slot's remainder words and candidate stamps lie at
+// slot * stride (the largest node count on the task list) and are not cleared
+// between tasks: a task knows its own by a tag that its slot's step counter
+// never gives out again.  That holds only while every word keeps its slot, so a
+// plan that moves the slots, or whose counters start again, must clear all
+// three; a plan with the same stride and no more slots may keep them.
+struct SlotTags {
+    uint64_t stride = 0;  // the stride the words were written under (0: all still clear)
+    uint64_t slots = 0;   // the slots whose counters run on
+    // Takes in the next plan; true when its words, stamps and counters must be cleared first.
+    bool replan(uint64_t new_stride, uint64_t new_slots)
+    {
+        const bool stale = stride != 0 && (new_stride != stride || new_slots > slots);
+        if (new_stride != stride) slots = 0;
+        stride = new_stride;
+        slots = std::max(slots, new_slots);
+        return stale;
+    }
+};
+
 }  // namespace imsim_plan

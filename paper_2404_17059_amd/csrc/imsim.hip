@@ -550,7 +550,7 @@ int set_ic_direction(imsim::SimParams& P, const ims_graph* g, double alpha, doub
 // Largest graph of the drawn-coins form (its visited bitmap is 32 KB of LDS).
 constexpr uint64_t kLiveNodes = 1u << 18;
 // Device bytes the coin rows and the work lists of one trial range may take.
-constexpr uint64_t kLiveRowBudget = 1ull << 32, kLiveTodoBudget = 1ull << 29;
+constexpr uint64_t kLiveRowBudget = imsim_plan::kTrialRowBudget, kLiveTodoBudget = 1ull << 29;
 
 int prof_begin(ims_graph* g, hipStream_t s)
 {
@@ -758,8 +758,8 @@ struct TrialRun {
 };
 
 // Launch shape of a run; `together` trials run at once on the device (those
-// of other runs beside it included).
-int trial_run_plan(TrialRun& P, const ims_graph* g, uint32_t n_trials, bool nodes, uint64_t together, bool lazy)
+// of other runs beside it included, on `lanes` lanes in all).
+int trial_run_plan(TrialRun& P, const ims_graph* g, uint32_t n_trials, bool nodes, uint64_t together, bool lazy, uint64_t lanes = 1)
 {
     using namespace imsim;
     const uint64_t n = (uint64_t)g->n, m = (uint64_t)g->m, cus = (uint64_t)g->cus;
@@ -799,7 +799,9 @@ int trial_run_plan(TrialRun& P, const ims_graph* g, uint32_t n_trials, bool node
         // the more wavefronts (Erdos-Renyi, 1,000 / 20,000 / 140,000 nodes:
         // 4,000 trials 0.19 / 4.2 ms with one, 0.41 / 3.9 with four; 1,000
         // trials 26.0 ms with one, 13.3 with four, 12.9 with eight)
-        const uint64_t share = std::min<uint64_t>((160 * 1024) / (P.lds + 4096), (together + cus - 1) / cus);
+        // (states outside the LDS: or by the room for their lists)
+        const uint64_t at_once = std::min(together, imsim_plan::trial_lists(n, lanes) * lanes);
+        const uint64_t share = std::min<uint64_t>((160 * 1024) / (P.lds + 4096), (at_once + cus - 1) / cus);
         P.kw = share >= 12 ? 1 : share >= 3 ? 4 : 8;
         P.entry = P.bits == 8    ? lt_trial_entry<8>(P.kw, in_lds)
                   : P.bits == 16 ? lt_trial_entry<16>(P.kw, in_lds)
@@ -812,9 +814,10 @@ int trial_run_plan(TrialRun& P, const ims_graph* g, uint32_t n_trials, bool node
         }
         per_cu = (uint64_t)fit;
     }
-    P.slots = std::min<uint64_t>(n_trials, cus * per_cu);
-    P.tc = kLiveRowBudget / (P.row_bytes + (P.nodes ? P.bm_words * 4 : 0) + 1) / 64 * 64;
-    P.tc = std::min<uint64_t>(std::max<uint64_t>(P.tc, 64), ((uint64_t)n_trials + 63) / 64 * 64);
+    const imsim_plan::TrialSpace space =
+        imsim_plan::trial_space(n, n_trials, P.row_bytes + (P.nodes ? P.bm_words * 4 : 0), cus * per_cu, lanes);
+    P.slots = space.lists;
+    P.tc = space.trials;
     return IMS_OK;
 }
 
@@ -1793,7 +1796,8 @@ int batch_plan_sides(ims_batch* b, std::vector<bool>& aside)
             if (load[l] < load[sd.lane]) sd.lane = l;
         load[sd.lane] += b->cost[i];
         const uint64_t beside = std::min<uint64_t>(ims_batch::kLanes, which.size());
-        if ((rc = trial_run_plan(sd.run, g, b->items[i].n_trials, b->items[i].node_counts != nullptr, beside * b->items[i].n_trials, false))) return rc;
+        if ((rc = trial_run_plan(sd.run, g, b->items[i].n_trials, b->items[i].node_counts != nullptr, beside * b->items[i].n_trials, false, beside)))
+            return rc;
         sd.seeds.count = (uint32_t)b->seed_lists[i].size();
         sd.seeds.more = sd.seeds.count > imsim::kArgSeeds ? b->dev_seeds[i] : nullptr;
         if (!sd.seeds.more) std::copy(b->seed_lists[i].begin(), b->seed_lists[i].end(), sd.seeds.v);

@@ -46,7 +46,7 @@ def load_workload(name: str):
 # reported only while all of them are unchanged
 KERNEL_SOURCES = ["paper_2404_17059_amd/csrc/sim_kernels.hpp", "paper_2404_17059_amd/csrc/live_kernels.hpp",
                   "paper_2404_17059_amd/csrc/lt_trial_kernels.hpp", "paper_2404_17059_amd/csrc/philox.hpp",
-                  "paper_2404_17059_amd/csrc/imsim.hip"]
+                  "paper_2404_17059_amd/csrc/plan.hpp", "paper_2404_17059_amd/csrc/routes.hpp", "paper_2404_17059_amd/csrc/imsim.hip"]
 
 
 def log(*a):

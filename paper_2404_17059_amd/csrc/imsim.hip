@@ -21,6 +21,7 @@
 #include "live_kernels.hpp"
 #include "lt_trial_kernels.hpp"
 #include "plan.hpp"
+#include "routes.hpp"
 #include "sim_kernels.hpp"
 
 namespace {
@@ -89,9 +90,8 @@ int record_error(int code, const char* msg)
 }
 }  // namespace imsim
 
-struct ims_graph {
+struct ims_graph : imsim_plan::RouteGraph {
     int device = 0;
-    int64_t n = 0, m = 0;
     int model = 0;
     uint64_t total_chunks = 0;  // sum over nodes of ceil(outdeg / kChunk)
     int cus = 0;
@@ -105,18 +105,11 @@ struct ims_graph {
     uint64_t* d_in_arc = nullptr;  // (source | weight piece << 32) per in-arc
     uint64_t* d_ic_in = nullptr;     // IC: (source | out-CSR arc id << 32) per in-arc
     uint32_t* d_ic_in_thr = nullptr; // IC: threshold per in-arc
-    int64_t ic_in_m = 0;             // IC: in-arcs (arcs whose threshold is not 0)
-    double ic_pbar = 0.0;            // IC: mean firing probability of those arcs
-    double ic_growth = 0.0;          // IC: live out-arcs of the target of a live arc, on average
     uint64_t* d_lvl = nullptr;       // IC grid shape: per level frontier out-arcs [cap], full-pair in-arcs [cap]
     uint32_t* d_lvl_dir = nullptr;   // IC grid shape: direction of each level [cap]
     uint32_t* d_in_src32 = nullptr;  // source per in-arc (uniform-weight form)
     uint64_t* d_lt_wout = nullptr;   // LT weight per out-arc (push form of the batch's 8-trial tasks)
     uint32_t* d_node_w = nullptr;    // common weight piece per node (uniform-weight form)
-    bool lt_uniform = false;
-    bool lt_zero = false;            // some arc has weight 0
-    uint64_t lt_max_in = 0;          // most in-arc pieces of a node
-    uint64_t max_out = 0;            // most out-arcs of a node
     uint32_t* d_kinfo = nullptr;     // per node: low half of its in-CSR offset, first plane in the count table
     uint64_t kplanes_total = 0;      // count-table planes per word summed over the nodes
     uint32_t* d_bfirst = nullptr;    // LT grid shape: first node of each batch
@@ -375,6 +368,7 @@ int ims_graph_create(int64_t n, int64_t m, const int64_t* offsets, const uint32_
         return bail(fail(IMS_E_HIP, "graph upload failed"));
     if (n <= (1ll << imsim::kRecNodeBits) && m < (1ll << imsim::kRecArcBits) && max_deg < (1ull << (64 - imsim::kRecNodeBits - imsim::kRecArcBits))) {
         if ((rc = dev_alloc(&g->d_rec, (uint64_t)m))) return bail(rc);
+        g->records = true;
         if (m > 0)
             hipLaunchKernelGGL(imsim::arc_record_kernel, dim3((unsigned)std::min<int64_t>((m + imsim::kBlock - 1) / imsim::kBlock, 4096)),
                                dim3(imsim::kBlock), 0, nullptr, (const uint32_t*)g->d_off32, (const uint32_t*)g->d_idx, (uint64_t)m, g->d_rec);
@@ -547,8 +541,19 @@ int set_ic_direction(imsim::SimParams& P, const ims_graph* g, double alpha, doub
     return IMS_OK;
 }
 
-// Largest graph of the drawn-coins form (its visited bitmap is 32 KB of LDS).
-constexpr uint64_t kLiveNodes = 1u << 18;
+using imsim_plan::kLiveNodes;
+using imsim_plan::lt_trial_bits;
+using imsim_plan::lt_trial_lds;
+using imsim_plan::kLtTrialLds;
+static_assert(imsim_plan::kTinySeeds == imsim::kTinySeeds);
+
+uint64_t seed_out_arcs(const ims_graph* g, const std::vector<uint32_t>& sv)
+{
+    uint64_t arcs = 0;
+    for (uint32_t x : sv) arcs += (uint64_t)(g->h_off[x + 1] - g->h_off[x]);
+    return arcs;
+}
+
 // Device bytes the coin rows and the work lists of one trial range may take.
 constexpr uint64_t kLiveRowBudget = imsim_plan::kTrialRowBudget, kLiveTodoBudget = 1ull << 29;
 
@@ -565,85 +570,6 @@ int prof_end(ims_graph* g, hipStream_t s)
     IMS_HIP(hipEventRecord(g->prof_ev[2 * g->prof_count + 1], s));
     ++g->prof_count;
     return IMS_OK;
-}
-
-// Whether a one-set run takes the drawn-coins form.  It draws all m * T coins
-// (`draw`, us) where the other forms draw those of the arcs they meet, so it
-// pays unless the cascades stay in a small part of the graph; growth (live
-// out-arcs of the target of a live arc) tells how far they go.  Measured on
-// Erdos-Renyi, preferential-attachment and small-world graphs of 500 to
-// 100,000 nodes, 64 to 10,000 trials, probabilities 0.01 to 0.1, TV, UR, WC:
-// - growth below 0.7: the other forms end sooner, but for level counts, which
-//   cost them 0.2 ms.
-// - up to 1.3: 1.1 to 3x faster up to a draw of 110 us (20,000-node ring, WC,
-//   300 trials 0.114 against 0.178 ms; 1,000 trials, draw 167 us, 0.24
-//   against 0.18).  With 16 arcs a node and more the other forms meet that
-//   many more: 1.7 to 3x faster up to the largest draw tried, 800 us (44 arcs,
-//   4,000 nodes, WC, 1,000 trials 0.33 against 0.70; 24 arcs, 12,000 nodes,
-//   3,000 trials 1.0 against 2.1), but not below growth 0.85.
-//   Level counts: 2 to 12x at every size tried.
-// - up to 2: 2 to 4x faster up to a draw of 400 us, slower from about 650;
-//   from 16 arcs a node 7 to 10x faster at 600 us.
-// - above: 1.5 to 13x faster at every size tried, but for skewed graphs with
-//   many live arcs per node, or hubs, whose pull steps end early: there only
-//   with fewer than 20,000 nodes and 4,000 trials, and up to 90 million live
-//   arcs (16 arcs, 12,000 nodes, UR, 1,000 trials 0.99 against 1.08 ms, 3,000
-//   trials 2.4 against 1.6), 50 million on directed graphs with hubs (3,000-node preferential
-//   attachment, UR, 4,000 trials 1.24 against 0.77 ms; 300 trials 0.24
-//   against 0.49).  From eight live arcs a node every graph but a ring is
-//   covered in three or four levels, whose pull steps meet few arcs of a node:
-//   the walk over all live arcs pays up to 40 million of them, 100,000 a
-//   trial and 2,000 trials (44 arcs, 1,000 nodes, UR, 1,000 trials 0.26 against 0.39 ms; 4,000
-//   nodes 0.97 against 0.52; 12,000 nodes, 128 trials 1.1 against 0.63).
-bool live_single_pays(const ims_graph* g, uint32_t n_trials, bool levels)
-{
-    const double n = (double)g->n, growth = g->ic_growth;
-    const double draw = (double)g->m * (double)((n_trials + 7) / 8) / 150e3;
-    if ((uint64_t)g->n > kLiveNodes || g->n == 0 || !g->d_rec) return false;
-    if (growth < 0.7) return levels && draw <= 80.0;
-    const bool dense = (double)g->m >= 16.0 * n;
-    if (growth < 1.3) return draw <= (levels ? 2000.0 : !dense || growth < 0.85 ? 110.0 : 800.0);
-    if (levels) return true;
-    if (growth < 2.0) return draw <= (dense ? 800.0 : 400.0);
-    const double live_degree = g->ic_pbar * (double)g->ic_in_m / n;
-    if (live_degree >= 8.0) return n_trials <= 2000 && live_degree * n <= 100e3 && live_degree * n * n_trials <= 40e6;
-    const bool skewed = growth >= 1.5 * live_degree, hubs = (double)g->max_out * n >= 20.0 * (double)g->m;
-    if (live_degree >= 3.0 && (skewed || hubs))
-        return n < 20000.0 && n_trials < 4000 && live_degree * n * n_trials <= (skewed ? 90e6 : 50e6);
-    return true;
-}
-
-// Whether an IC item of a batch does: the tasks share the chip there, so the
-// lines lie lower than for a run alone (batches of 8 items, ms, tasks / this:
-// 60,000 to 300,000 arcs, WC, 2,000 trials 2.7 / 2.9, at draws up to 40 us 0.94
-// / 0.37; 44 arcs a node, WC, draws of 300 us and more 4.4 / 6.0, up to 150 us
-// 1.5 / 0.9; 44 arcs a node, UR 0.59 / 0.80; 40 arcs, Erdos-Renyi, UR, 200
-// trials 1.05 / 0.42, 2,000 trials 2.1 / 2.3).
-bool live_item_pays(const ims_graph* g, uint32_t n_trials)
-{
-    if (!live_single_pays(g, n_trials, false)) return false;
-    const double n = (double)g->n, draw = (double)g->m * (double)((n_trials + 7) / 8) / 150e3;
-    if (g->ic_growth < 1.3) return draw <= ((double)g->m >= 16.0 * n ? 150.0 : 45.0);
-    const double live_degree = g->ic_pbar * (double)g->ic_in_m / n;
-    return live_degree < 8.0 || (g->ic_growth < 1.5 * live_degree && n_trials <= 500 && live_degree * n <= 60e3);
-}
-
-// Whether a one-set IC run takes the per-trial form that draws an arc's coin
-// when it meets the arc: cascades that stay small (growth below 0.7), or whose
-// dense draw does not pay, up to about 1,500 trials (above, the tasks of 4 to
-// 16 trials share a hash block between their trials; this form uses one
-// trial's eighth of it).  Measured against the tasks and the grid: 64 to 1,000
-// trials at probabilities 0.01 and 0.03 on 500 to 100,000 nodes 25 to 54
-// against 58 to 95 us (4,000 trials 100 to 150 against 73 to 100); 100,000-
-// node Erdos-Renyi, WC, 1,000 trials 1.3 against 2.3 ms.  Hubs of several
-// thousand out-arcs are walked by one workgroup a trial: there the others are
-// faster (100,000-node preferential attachment, 11 arcs a node: 2.1 / 1.7 ms),
-// and from growth 0.7 on graphs of 16 arcs a node and more (60 arcs, 12,000
-// nodes, WC, 1,000 trials 2.6 / 2.0 ms).
-bool lazy_trials_pay(const ims_graph* g, uint32_t n_trials)
-{
-    if (g->n == 0 || (uint64_t)g->n > kLiveNodes || !g->d_rec || n_trials > 1500 || g->max_out > 4000) return false;
-    return g->ic_growth < 0.7 || (g->ic_growth < 1.3 && (double)g->m < 16.0 * (double)g->n && !live_single_pays(g, n_trials, false));
 }
 
 // The coin rows of trials t0 .. t0 + tc - 1 (row_words a multiple of 8).
@@ -679,50 +605,6 @@ int live_seeds(ims_graph* g, const std::vector<uint32_t>& sv, imsim::LiveSeeds& 
         return rc;
     S.more = (const uint32_t*)g->sets_dev.p;
     return IMS_OK;
-}
-
-// Per-trial LT form: element width of a graph's states, and whether a trial's
-// fit the LDS beside the kernel's own arrays.
-constexpr uint64_t kLtTrialLds = 160 * 1024 - 12 * 1024;
-uint32_t lt_trial_bits(const ims_graph* g)
-{
-    return !g->lt_uniform || g->lt_zero || g->lt_max_in >= 32767 ? 32 : g->lt_max_in >= 127 ? 16 : 8;
-}
-bool lt_trial_lds(const ims_graph* g)
-{
-    const uint64_t n = (uint64_t)g->n, bits = lt_trial_bits(g);
-    return n * bits / 8 + (bits == 32 ? n / 8 : 0) + 64 <= kLtTrialLds;
-}
-
-// Whether a run takes it.  It touches every arc once per trial, in as many
-// rounds of one workgroup as the cascade has steps; the grid-wide sweeps read
-// everything pending at every step but share it between 64 trials.  Measured
-// (1,000 trials, ms, this against the sweeps; Erdos-Renyi, preferential-
-// attachment and directed power-law graphs of 1,000 to 500,000 nodes, 64 to
-// 4,000 trials): 20,000-node Erdos-Renyi 1.6 / 13.7, preferential attachment
-// 0.6 / 53, power law 0.75 / 1.8; state outside the LDS: 100,000-node
-// Erdos-Renyi with random weights 12.7 / 123, 200,000-node preferential
-// attachment 1.4 / 127.  The sweeps win where a hub holding a notable part of
-// all arcs makes the cascade dense within few steps (and no node has more
-// in-arcs than a sweep stages): with hub seeds above about 200,000 arcs
-// (36,000 nodes 2.2 / 1.55), 90,000 with 32-bit states at 1,000 trials (87,000
-// arcs 0.90 / 0.90, 175,000 2.3 / 1.5) and more at fewer trials (100 trials:
-// 264,000 arcs 0.87 / 1.42), any number with the state outside the LDS (45,000
-// nodes 14.5 / 2.1); with other seeds above about a million (140,000 nodes,
-// 15 arcs each: 7.6 / 4.4; where few trials leave the chip idle, half of
-// that: 800,000 arcs, 128 trials 2.0 / 1.7, 256 trials 2.0 / 1.9, 320 trials
-// 2.0 / 2.0), 300,000 outside the LDS (222,000 arcs 2.3 / 2.9,
-// 346,000 3.7 / 3.0).
-bool lt_trials_pay(const ims_graph* g, const std::vector<uint32_t>& sv, uint32_t n_trials)
-{
-    if (!g->d_rec) return false;
-    if (g->max_out * 64 < (uint64_t)g->m || g->lt_max_in > 64) return true;
-    uint64_t arcs = 0;
-    for (uint32_t x : sv) arcs += (uint64_t)(g->h_off[x + 1] - g->h_off[x]);
-    const bool dense = arcs * 16 >= (uint64_t)g->m;
-    if (!lt_trial_lds(g)) return !dense && g->m <= 300000;
-    if (!dense) return g->m <= (n_trials < 320 ? 500000u : 1060000u);
-    return lt_trial_bits(g) == 32 ? (double)g->m * std::min(1000.0, (double)n_trials) <= 90e6 : g->m <= 200000;
 }
 
 // Kernel of a width, wavefront count and place of the state.
@@ -790,8 +672,8 @@ int trial_run_plan(TrialRun& P, const ims_graph* g, uint32_t n_trials, bool node
         P.lds = P.bm_words * 4;
         per_cu = 32 / P.kw;
     } else {
-        P.bits = lt_trial_bits(g);
-        const bool in_lds = lt_trial_lds(g);
+        P.bits = lt_trial_bits(*g);
+        const bool in_lds = lt_trial_lds(*g);
         P.nodes = nodes || (!in_lds && P.bits == 32);
         P.row_bytes = (n * P.bits / 8 + 15) / 16 * 16;
         P.lds = in_lds ? P.row_bytes + (P.bits == 32 ? P.bm_words * 4 : 0) : 0;
@@ -981,13 +863,13 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
     const bool forced = opts && (opts->test_flags & 16);
     if (!form_asked && n > 0 && g->d_rec) {
         if (g->model == IMS_MODEL_IC) {
-            if (!level_counts && (opts && (opts->test_flags & 32) ? n <= kLiveNodes : !forced && lazy_trials_pay(g, n_trials)))
+            if (!level_counts && (opts && (opts->test_flags & 32) ? n <= kLiveNodes : !forced && imsim_plan::lazy_trials_pay(*g, n_trials)))
                 return simulate_trials(g, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, nullptr, 0, opts, true, s);
-            if ((forced && n <= kLiveNodes) || live_single_pays(g, n_trials, level_counts != nullptr))
+            if ((forced && n <= kLiveNodes) || imsim_plan::live_single_pays(*g, n_trials, level_counts != nullptr))
                 return simulate_trials(g, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, level_counts, max_levels,
                                        opts, false, s);
         } else if (!level_counts && !(opts && ((opts->test_flags & ~16) || opts->alpha != 0.0))) {
-            if (forced || lt_trials_pay(g, sv, n_trials))
+            if (forced || imsim_plan::lt_trials_pay(*g, seed_out_arcs(g, sv), n_trials))
                 return simulate_trials(g, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, nullptr, 0, opts, false, s);
         }
     }
@@ -1401,63 +1283,6 @@ int ims_simulate_levels(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, u
 
 namespace {
 
-// Whether a many-sets call takes the drawn-coins form.  It draws every arc's
-// coin once, m * T / 8 hash blocks at about 150 a nanosecond; the tasks draw
-// the coins of the arcs their cascades meet, set by set, at least those of
-// the seeds' out-arcs in every trial, and where the target of a live arc has
-// about one live out-arc or more a cascade goes on to meet many times that (it
-// is heavy tailed: on the 200k-node weighted-cascade graph at 1,000 trials the forms
-// break even at about 100 random single nodes, m / 2,000 seed out-arcs; one
-// hub already takes 1.7 against 4.4 ms, a set of 25 nodes 2.4 against 21).
-// Below that the factor is the geometric sum of that growth times what a
-// dense draw gains per block.  Draws of up to 20 us always pay but for
-// single-set calls (5,000 nodes: 0.28 against 0.17 ms for one node).
-// Sets on top of a base meet an unknown part of their arcs.  The measured
-// times there (graphs of 5,000 to 200,000 nodes with weighted-cascade
-// probabilities, 100 to 10,000 trials, 1 to 128 hubs on bases of 3 to 20) are
-// about 250 us + the draw + 2.5 ns per (trial, set) for the drawn-coins form,
-// and for the tasks at least 150 us + 15 ns per node (one task's chain of
-// steps) and 50 times the draw of the sets' own out-arcs; growth above 2
-// leaves little outside the base (0.07 ms for the tasks), below 0.8 little at
-// all.
-bool live_sets_pay(const ims_graph* g, bool base, const std::vector<uint32_t>& off, const std::vector<uint32_t>& nodes, uint32_t n_trials)
-{
-    if ((uint64_t)g->n > kLiveNodes || g->n == 0 || !g->d_rec || off.size() > (1u << 24)) return false;
-    uint64_t arcs = 0;
-    for (uint32_t v : nodes) arcs += (uint64_t)(g->h_off[v + 1] - g->h_off[v]);
-    const double blocks = (double)((n_trials + 7) / 8);
-    const double draw = (double)g->m * blocks / 150e3;  // us
-    if (base) {
-        const double live = 250.0 + draw + 0.0025 * (double)n_trials * (double)(off.size() - 1);
-        // the chain only where the sets are hubs (40,000-node preferential
-        // attachment, 8 random nodes, 1,000 trials: tasks 0.40, drawn 0.64 ms)
-        const bool hubs = (double)arcs * (double)g->n >= 4.0 * (double)g->m * (double)nodes.size();
-        const double tasks = std::max(hubs ? 150.0 + 0.015 * (double)g->n : 0.0, 50.0 * (double)arcs * blocks / 150e3);
-        return g->ic_growth >= 0.8 && g->ic_growth <= 2.0 && live < tasks;
-    }
-    // Where the tasks stay faster (whole calls in ms, tasks / drawn; random sets
-    // on graphs of 1,000 to 40,000 nodes, 5 to 44 arcs a node):
-    // - small cascades of many seeds, which a lane does not follow alone, and
-    //   of few sets (growth 0.16, 1,000 trials, 64 sets of 30 0.25 / 0.87, 16
-    //   single nodes 0.100 / 0.107; 256 single nodes 0.36 / 0.17); up to growth
-    //   0.9 with fewer than 16 arcs a node and many trials (64 sets of 30,
-    //   1,000 trials 0.69 / 0.92, 100 trials 0.44 / 0.21);
-    // - under four sets near growth 1 (0.14 / 0.16);
-    // - cascades that cover the graph in three levels, whose pull steps end
-    //   early, but for few walks (growth 39, 16 sets, 1,000 trials 0.85 / 1.68,
-    //   100 trials 0.81 / 0.44).
-    const uint64_t sets = off.size() - 1;
-    uint64_t large = 0;
-    for (uint64_t i = 0; i < sets; ++i) large += off[i + 1] - off[i] > imsim::kTinySeeds ? 1u : 0u;
-    const bool dense = (double)g->m >= 16.0 * (double)g->n;
-    if (g->ic_growth < 0.6 && (large || sets < 64)) return false;
-    if (g->ic_growth < 0.9 && !dense && large * n_trials > 8000) return false;
-    if (sets < 4 && g->ic_growth < (dense ? 0.85 : 1.4)) return false;
-    if (g->ic_growth >= 8.0 && sets * n_trials > 8000) return false;
-    const double reach = g->ic_growth >= 0.8 ? 2000.0 : 8.0 / (1.0 - g->ic_growth);
-    return (double)arcs * reach >= (double)g->m || (draw <= 20.0 && off.size() > 8);
-}
-
 // Many seed sets in the drawn-coins form: trials in ranges whose coin rows
 // and work lists fit the budgets, three or four launches per range.
 // h_off / d_off / d_nodes: the sets, offsets on the host too; totals and node_counts are cleared.
@@ -1596,7 +1421,7 @@ int simulate_sets_impl(ims_graph* g, const uint64_t* base, const uint32_t* set_o
     const bool tasks_asked = opts && (opts->shape || opts->blocks_per_cu || opts->ic_alpha != 0.0 || opts->ic_beta != 0.0 || opts->ic_direction);
     const bool live_forced = opts && (opts->test_flags & 16) && n > 0 && n <= kLiveNodes && g->d_rec;
     if (g->model == IMS_MODEL_IC && !tasks_asked &&
-        (live_forced || live_sets_pay(g, base != nullptr, off, nodes, n_trials)))
+        (live_forced || imsim_plan::live_sets_pay(*g, base != nullptr, off, seed_out_arcs(g, nodes), n_trials)))
         return simulate_sets_live(g, base, off.data(), d_off, d_nodes, n_sets, n_trials, rng_seed, totals, node_counts, s);
 
     const uint64_t tasks = (uint64_t)n_sets * W;
@@ -1781,7 +1606,9 @@ int batch_plan_sides(ims_batch* b, std::vector<bool>& aside)
     for (uint32_t i = 0; i < (uint32_t)b->items.size(); ++i) {
         const ims_graph* g = b->items[i].graph;
         if (g->n == 0 || g->device != b->device) continue;
-        if (g->model == IMS_MODEL_IC ? live_item_pays(g, b->items[i].n_trials) : lt_trials_pay(g, b->seed_lists[i], b->items[i].n_trials)) which.push_back(i);
+        if (g->model == IMS_MODEL_IC ? imsim_plan::live_item_pays(*g, b->items[i].n_trials)
+                                     : imsim_plan::lt_trials_pay(*g, seed_out_arcs(g, b->seed_lists[i]), b->items[i].n_trials))
+            which.push_back(i);
     }
     std::stable_sort(which.begin(), which.end(), [&](uint32_t x, uint32_t y) { return b->cost[x] > b->cost[y]; });
     double load[ims_batch::kLanes] = {};

@@ -1,0 +1,207 @@
+// Which form a call runs in: plain C++ (no HIP) over what is known of the graph
+// and the call before it starts, so that the rules can be checked on the CPU.
+// Every form gives the same results; the lines stand where the measured times
+// beside them cross.
+#pragma once
+
+#include <stdint.h>
+
+#include <algorithm>
+#include <vector>
+
+namespace imsim_plan {
+
+// Largest graph of the IC per-trial forms (their visited bitmap is 32 KB of LDS).
+constexpr uint64_t kLiveNodes = 1u << 18;
+constexpr uint64_t kTinySeeds = 4;  // larger seed sets of a many-sets call go to a wavefront at once
+
+// What the rules know of a graph.
+struct RouteGraph {
+    int64_t n = 0, m = 0;
+    uint64_t max_out = 0;    // most out-arcs of a node
+    bool records = false;    // the graph has the arc records of the per-trial forms
+    int64_t ic_in_m = 0;     // IC: in-arcs (arcs whose threshold is not 0)
+    double ic_pbar = 0.0;    // IC: mean firing probability of those arcs
+    double ic_growth = 0.0;  // IC: live out-arcs of the target of a live arc, on average
+    bool lt_uniform = false; // LT: equal in-weights
+    bool lt_zero = false;    // LT: some arc has weight 0
+    uint64_t lt_max_in = 0;  // LT: most in-arc pieces of a node
+};
+
+// Whether a one-set run takes the drawn-coins form.  It draws all m * T coins
+// (`draw`, us) where the other forms draw those of the arcs they meet, so it
+// pays unless the cascades stay in a small part of the graph; growth (live
+// out-arcs of the target of a live arc) tells how far they go.  Measured on
+// Erdos-Renyi, preferential-attachment and small-world graphs of 500 to
+// 100,000 nodes, 64 to 10,000 trials, probabilities 0.01 to 0.1, TV, UR, WC:
+// - growth below 0.7: the other forms end sooner, but for level counts, which
+//   cost them 0.2 ms.
+// - up to 1.3: 1.1 to 3x faster up to a draw of 110 us (20,000-node ring, WC,
+//   300 trials 0.114 against 0.178 ms; 1,000 trials, draw 167 us, 0.24
+//   against 0.18).  With 16 arcs a node and more the other forms meet that
+//   many more: 1.7 to 3x faster up to the largest draw tried, 800 us (44 arcs,
+//   4,000 nodes, WC, 1,000 trials 0.33 against 0.70; 24 arcs, 12,000 nodes,
+//   3,000 trials 1.0 against 2.1), but not below growth 0.85.
+//   Level counts: 2 to 12x at every size tried.
+// - up to 2: 2 to 4x faster up to a draw of 400 us, slower from about 650;
+//   from 16 arcs a node 7 to 10x faster at 600 us.
+// - above: 1.5 to 13x faster at every size tried, but for skewed graphs with
+//   many live arcs per node, or hubs, whose pull steps end early: there only
+//   with fewer than 20,000 nodes and 4,000 trials, and up to 90 million live
+//   arcs (16 arcs, 12,000 nodes, UR, 1,000 trials 0.99 against 1.08 ms, 3,000
+//   trials 2.4 against 1.6), 50 million on directed graphs with hubs (3,000-node preferential
+//   attachment, UR, 4,000 trials 1.24 against 0.77 ms; 300 trials 0.24
+//   against 0.49).  From eight live arcs a node every graph but a ring is
+//   covered in three or four levels, whose pull steps meet few arcs of a node:
+//   the walk over all live arcs pays up to 40 million of them, 100,000 a
+//   trial and 2,000 trials (44 arcs, 1,000 nodes, UR, 1,000 trials 0.26 against 0.39 ms; 4,000
+//   nodes 0.97 against 0.52; 12,000 nodes, 128 trials 1.1 against 0.63).
+inline bool live_single_pays(const RouteGraph& g, uint32_t n_trials, bool levels)
+{
+    const double n = (double)g.n, growth = g.ic_growth;
+    const double draw = (double)g.m * (double)((n_trials + 7) / 8) / 150e3;
+    if ((uint64_t)g.n > kLiveNodes || g.n == 0 || !g.records) return false;
+    if (growth < 0.7) return levels && draw <= 80.0;
+    const bool dense = (double)g.m >= 16.0 * n;
+    if (growth < 1.3) return draw <= (levels ? 2000.0 : !dense || growth < 0.85 ? 110.0 : 800.0);
+    if (levels) return true;
+    if (growth < 2.0) return draw <= (dense ? 800.0 : 400.0);
+    const double live_degree = g.ic_pbar * (double)g.ic_in_m / n;
+    if (live_degree >= 8.0) return n_trials <= 2000 && live_degree * n <= 100e3 && live_degree * n * n_trials <= 40e6;
+    const bool skewed = growth >= 1.5 * live_degree, hubs = (double)g.max_out * n >= 20.0 * (double)g.m;
+    if (live_degree >= 3.0 && (skewed || hubs))
+        return n < 20000.0 && n_trials < 4000 && live_degree * n * n_trials <= (skewed ? 90e6 : 50e6);
+    return true;
+}
+
+// Whether an IC item of a batch does: the tasks share the chip there, so the
+// lines lie lower than for a run alone (batches of 8 items, ms, tasks / this:
+// 60,000 to 300,000 arcs, WC, 2,000 trials 2.7 / 2.9, at draws up to 40 us 0.94
+// / 0.37; 44 arcs a node, WC, draws of 300 us and more 4.4 / 6.0, up to 150 us
+// 1.5 / 0.9; 44 arcs a node, UR 0.59 / 0.80; 40 arcs, Erdos-Renyi, UR, 200
+// trials 1.05 / 0.42, 2,000 trials 2.1 / 2.3).
+inline bool live_item_pays(const RouteGraph& g, uint32_t n_trials)
+{
+    if (!live_single_pays(g, n_trials, false)) return false;
+    const double n = (double)g.n, draw = (double)g.m * (double)((n_trials + 7) / 8) / 150e3;
+    if (g.ic_growth < 1.3) return draw <= ((double)g.m >= 16.0 * n ? 150.0 : 45.0);
+    const double live_degree = g.ic_pbar * (double)g.ic_in_m / n;
+    return live_degree < 8.0 || (g.ic_growth < 1.5 * live_degree && n_trials <= 500 && live_degree * n <= 60e3);
+}
+
+// Whether a one-set IC run takes the per-trial form that draws an arc's coin
+// when it meets the arc: cascades that stay small (growth below 0.7), or whose
+// dense draw does not pay, up to about 1,500 trials (above, the tasks of 4 to
+// 16 trials share a hash block between their trials; this form uses one
+// trial's eighth of it).  Measured against the tasks and the grid: 64 to 1,000
+// trials at probabilities 0.01 and 0.03 on 500 to 100,000 nodes 25 to 54
+// against 58 to 95 us (4,000 trials 100 to 150 against 73 to 100); 100,000-
+// node Erdos-Renyi, WC, 1,000 trials 1.3 against 2.3 ms.  Hubs of several
+// thousand out-arcs are walked by one workgroup a trial: there the others are
+// faster (100,000-node preferential attachment, 11 arcs a node: 2.1 / 1.7 ms),
+// and from growth 0.7 on graphs of 16 arcs a node and more (60 arcs, 12,000
+// nodes, WC, 1,000 trials 2.6 / 2.0 ms).
+inline bool lazy_trials_pay(const RouteGraph& g, uint32_t n_trials)
+{
+    if (g.n == 0 || (uint64_t)g.n > kLiveNodes || !g.records || n_trials > 1500 || g.max_out > 4000) return false;
+    return g.ic_growth < 0.7 || (g.ic_growth < 1.3 && (double)g.m < 16.0 * (double)g.n && !live_single_pays(g, n_trials, false));
+}
+
+// Per-trial LT form: element width of a graph's states, and whether a trial's
+// fit the LDS beside the kernel's own arrays.
+constexpr uint64_t kLtTrialLds = 160 * 1024 - 12 * 1024;
+inline uint32_t lt_trial_bits(const RouteGraph& g)
+{
+    return !g.lt_uniform || g.lt_zero || g.lt_max_in >= 32767 ? 32 : g.lt_max_in >= 127 ? 16 : 8;
+}
+inline bool lt_trial_lds(const RouteGraph& g)
+{
+    const uint64_t n = (uint64_t)g.n, bits = lt_trial_bits(g);
+    return n * bits / 8 + (bits == 32 ? n / 8 : 0) + 64 <= kLtTrialLds;
+}
+
+// Whether a run takes it.  It touches every arc once per trial, in as many
+// rounds of one workgroup as the cascade has steps; the grid-wide sweeps read
+// everything pending at every step but share it between 64 trials.  Measured
+// (1,000 trials, ms, this against the sweeps; Erdos-Renyi, preferential-
+// attachment and directed power-law graphs of 1,000 to 500,000 nodes, 64 to
+// 4,000 trials): 20,000-node Erdos-Renyi 1.6 / 13.7, preferential attachment
+// 0.6 / 53, power law 0.75 / 1.8; state outside the LDS: 100,000-node
+// Erdos-Renyi with random weights 12.7 / 123, 200,000-node preferential
+// attachment 1.4 / 127.  The sweeps win where a hub holding a notable part of
+// all arcs makes the cascade dense within few steps (and no node has more
+// in-arcs than a sweep stages): with hub seeds above about 200,000 arcs
+// (36,000 nodes 2.2 / 1.55), 90,000 with 32-bit states at 1,000 trials (87,000
+// arcs 0.90 / 0.90, 175,000 2.3 / 1.5) and more at fewer trials (100 trials:
+// 264,000 arcs 0.87 / 1.42), any number with the state outside the LDS (45,000
+// nodes 14.5 / 2.1); with other seeds above about a million (140,000 nodes,
+// 15 arcs each: 7.6 / 4.4; where few trials leave the chip idle, half of
+// that: 800,000 arcs, 128 trials 2.0 / 1.7, 256 trials 2.0 / 1.9, 320 trials
+// 2.0 / 2.0), 300,000 outside the LDS (222,000 arcs 2.3 / 2.9,
+// 346,000 3.7 / 3.0).
+inline bool lt_trials_pay(const RouteGraph& g, uint64_t arcs, uint32_t n_trials)
+{
+    if (!g.records) return false;
+    if (g.max_out * 64 < (uint64_t)g.m || g.lt_max_in > 64) return true;
+    const bool dense = arcs * 16 >= (uint64_t)g.m;
+    if (!lt_trial_lds(g)) return !dense && g.m <= 300000;
+    if (!dense) return g.m <= (n_trials < 320 ? 500000u : 1060000u);
+    return lt_trial_bits(g) == 32 ? (double)g.m * std::min(1000.0, (double)n_trials) <= 90e6 : g.m <= 200000;
+}
+
+// Whether a many-sets call takes the drawn-coins form.  It draws every arc's
+// coin once, m * T / 8 hash blocks at about 150 a nanosecond; the tasks draw
+// the coins of the arcs their cascades meet, set by set, at least those of
+// the seeds' out-arcs in every trial, and where the target of a live arc has
+// about one live out-arc or more a cascade goes on to meet many times that (it
+// is heavy tailed: on the 200k-node weighted-cascade graph at 1,000 trials the forms
+// break even at about 100 random single nodes, m / 2,000 seed out-arcs; one
+// hub already takes 1.7 against 4.4 ms, a set of 25 nodes 2.4 against 21).
+// Below that the factor is the geometric sum of that growth times what a
+// dense draw gains per block.  Draws of up to 20 us always pay but for
+// single-set calls (5,000 nodes: 0.28 against 0.17 ms for one node).
+// Sets on top of a base meet an unknown part of their arcs.  The measured
+// times there (graphs of 5,000 to 200,000 nodes with weighted-cascade
+// probabilities, 100 to 10,000 trials, 1 to 128 hubs on bases of 3 to 20) are
+// about 250 us + the draw + 2.5 ns per (trial, set) for the drawn-coins form,
+// and for the tasks at least 150 us + 15 ns per node (one task's chain of
+// steps) and 50 times the draw of the sets' own out-arcs; growth above 2
+// leaves little outside the base (0.07 ms for the tasks), below 0.8 little at
+// all.
+inline bool live_sets_pay(const RouteGraph& g, bool base, const std::vector<uint32_t>& off, uint64_t arcs, uint32_t n_trials)
+{
+    if ((uint64_t)g.n > kLiveNodes || g.n == 0 || !g.records || off.size() > (1u << 24)) return false;
+    const double blocks = (double)((n_trials + 7) / 8);
+    const double draw = (double)g.m * blocks / 150e3;  // us
+    if (base) {
+        const double live = 250.0 + draw + 0.0025 * (double)n_trials * (double)(off.size() - 1);
+        // the chain only where the sets are hubs (40,000-node preferential
+        // attachment, 8 random nodes, 1,000 trials: tasks 0.40, drawn 0.64 ms)
+        const bool hubs = (double)arcs * (double)g.n >= 4.0 * (double)g.m * (double)off.back();
+        const double tasks = std::max(hubs ? 150.0 + 0.015 * (double)g.n : 0.0, 50.0 * (double)arcs * blocks / 150e3);
+        return g.ic_growth >= 0.8 && g.ic_growth <= 2.0 && live < tasks;
+    }
+    // Where the tasks stay faster (whole calls in ms, tasks / drawn; random sets
+    // on graphs of 1,000 to 40,000 nodes, 5 to 44 arcs a node):
+    // - small cascades of many seeds, which a lane does not follow alone, and
+    //   of few sets (growth 0.16, 1,000 trials, 64 sets of 30 0.25 / 0.87, 16
+    //   single nodes 0.100 / 0.107; 256 single nodes 0.36 / 0.17); up to growth
+    //   0.9 with fewer than 16 arcs a node and many trials (64 sets of 30,
+    //   1,000 trials 0.69 / 0.92, 100 trials 0.44 / 0.21);
+    // - under four sets near growth 1 (0.14 / 0.16);
+    // - cascades that cover the graph in three levels, whose pull steps end
+    //   early, but for few walks (growth 39, 16 sets, 1,000 trials 0.85 / 1.68,
+    //   100 trials 0.81 / 0.44).
+    const uint64_t sets = off.size() - 1;
+    uint64_t large = 0;
+    for (uint64_t i = 0; i < sets; ++i) large += off[i + 1] - off[i] > kTinySeeds ? 1u : 0u;
+    const bool dense = (double)g.m >= 16.0 * (double)g.n;
+    if (g.ic_growth < 0.6 && (large || sets < 64)) return false;
+    if (g.ic_growth < 0.9 && !dense && large * n_trials > 8000) return false;
+    if (sets < 4 && g.ic_growth < (dense ? 0.85 : 1.4)) return false;
+    if (g.ic_growth >= 8.0 && sets * n_trials > 8000) return false;
+    const double reach = g.ic_growth >= 0.8 ? 2000.0 : 8.0 / (1.0 - g.ic_growth);
+    return (double)arcs * reach >= (double)g.m || (draw <= 20.0 && off.size() > 8);
+}
+
+}  // namespace imsim_plan

@@ -110,6 +110,7 @@ struct ims_graph : imsim_plan::RouteGraph {
     uint32_t* d_in_src32 = nullptr;  // source per in-arc (uniform-weight form)
     uint64_t* d_lt_wout = nullptr;   // LT weight per out-arc (push form of the batch's 8-trial tasks)
     uint32_t* d_node_w = nullptr;    // common weight piece per node (uniform-weight form)
+    std::vector<std::pair<uint32_t, uint32_t>> long_rows;  // LT: nodes with more than 64 in-arc pieces, and how many
     uint32_t* d_kinfo = nullptr;     // per node: low half of its in-CSR offset, first plane in the count table
     uint64_t kplanes_total = 0;      // count-table planes per word summed over the nodes
     uint32_t* d_bfirst = nullptr;    // LT grid shape: first node of each batch
@@ -422,7 +423,13 @@ int ims_graph_create(int64_t n, int64_t m, const int64_t* offsets, const uint32_
         std::vector<uint32_t> node_w, src32;
         const bool uniform = imsim_plan::lt_uniform_form(n, lt_in, node_w, src32);
         g->lt_uniform = uniform;
-        for (int64_t v = 0; v < n; ++v) g->lt_max_in = std::max<uint64_t>(g->lt_max_in, (uint64_t)(in_off[v + 1] - in_off[v]));
+        for (int64_t v = 0; v < n; ++v) {
+            const uint64_t d = (uint64_t)(in_off[v + 1] - in_off[v]);
+            g->lt_max_in = std::max(g->lt_max_in, d);
+            if (d <= 64) continue;
+            g->lt_long += d;
+            g->long_rows.emplace_back((uint32_t)v, (uint32_t)d);
+        }
         for (int64_t e = 0; e < m; ++e) g->lt_zero |= ((const uint64_t*)param)[e] == 0;
         if (uniform) {
             std::vector<uint32_t> kinfo;
@@ -554,6 +561,18 @@ uint64_t seed_out_arcs(const ims_graph* g, const std::vector<uint32_t>& sv)
     return arcs;
 }
 
+// LT: in-arc pieces of the nodes with more than 64 that are not in sv (sorted).
+uint64_t long_pieces_left(const ims_graph* g, const std::vector<uint32_t>& sv)
+{
+    uint64_t left = 0;
+    size_t i = 0;
+    for (const auto& row : g->long_rows) {
+        while (i < sv.size() && sv[i] < row.first) ++i;
+        if (i == sv.size() || sv[i] != row.first) left += row.second;
+    }
+    return left;
+}
+
 // Device bytes the coin rows and the work lists of one trial range may take.
 constexpr uint64_t kLiveRowBudget = imsim_plan::kTrialRowBudget, kLiveTodoBudget = 1ull << 29;
 
@@ -680,11 +699,14 @@ int trial_run_plan(TrialRun& P, const ims_graph* g, uint32_t n_trials, bool node
         // the fewer trials share a compute unit (by their number, or by LDS),
         // the more wavefronts (Erdos-Renyi, 1,000 / 20,000 / 140,000 nodes:
         // 4,000 trials 0.19 / 4.2 ms with one, 0.41 / 3.9 with four; 1,000
-        // trials 26.0 ms with one, 13.3 with four, 12.9 with eight)
+        // trials 26.0 ms with one, 13.3 with four, 12.9 with eight); never one
+        // outside the LDS, where every wavefront's state competes for the
+        // caches (250,000 nodes, random weights, 4,000 trials 36 ms with one,
+        // 26 with four; 200,000-node preferential attachment, hub seeds 45 / 40)
         // (states outside the LDS: or by the room for their lists)
         const uint64_t at_once = std::min(together, imsim_plan::trial_lists(n, lanes) * lanes);
         const uint64_t share = std::min<uint64_t>((160 * 1024) / (P.lds + 4096), (at_once + cus - 1) / cus);
-        P.kw = share >= 12 ? 1 : share >= 3 ? 4 : 8;
+        P.kw = share >= 12 && in_lds ? 1 : share >= 3 ? 4 : 8;
         P.entry = P.bits == 8    ? lt_trial_entry<8>(P.kw, in_lds)
                   : P.bits == 16 ? lt_trial_entry<16>(P.kw, in_lds)
                                  : lt_trial_entry<32>(P.kw, in_lds);
@@ -869,7 +891,7 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
                 return simulate_trials(g, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, level_counts, max_levels,
                                        opts, false, s);
         } else if (!level_counts && !(opts && ((opts->test_flags & ~16) || opts->alpha != 0.0))) {
-            if (forced || imsim_plan::lt_trials_pay(*g, seed_out_arcs(g, sv), n_trials))
+            if (forced || imsim_plan::lt_run_pays(*g, seed_out_arcs(g, sv), long_pieces_left(g, sv), n_trials))
                 return simulate_trials(g, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, nullptr, 0, opts, false, s);
         }
     }

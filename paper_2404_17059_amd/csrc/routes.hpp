@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 #include <vector>
 
 namespace imsim_plan {
@@ -25,7 +26,8 @@ struct RouteGraph {
     double ic_growth = 0.0;  // IC: live out-arcs of the target of a live arc, on average
     bool lt_uniform = false; // LT: equal in-weights
     bool lt_zero = false;    // LT: some arc has weight 0
-    uint64_t lt_max_in = 0;  // LT: most in-arc pieces of a node
+    uint64_t lt_max_in = 0;  // LT: most in-arc pieces of a node, and
+    uint64_t lt_long = 0;    // those of all nodes with more than 64
 };
 
 // Whether a one-set run takes the drawn-coins form.  It draws all m * T coins
@@ -120,7 +122,7 @@ inline bool lt_trial_lds(const RouteGraph& g)
     return n * bits / 8 + (bits == 32 ? n / 8 : 0) + 64 <= kLtTrialLds;
 }
 
-// Whether a run takes it.  It touches every arc once per trial, in as many
+// Whether an item of a batch takes it, and a run of few seeds.  It touches every arc once per trial, in as many
 // rounds of one workgroup as the cascade has steps; the grid-wide sweeps read
 // everything pending at every step but share it between 64 trials.  Measured
 // (1,000 trials, ms, this against the sweeps; Erdos-Renyi, preferential-
@@ -147,6 +149,43 @@ inline bool lt_trials_pay(const RouteGraph& g, uint64_t arcs, uint32_t n_trials)
     if (!lt_trial_lds(g)) return !dense && g.m <= 300000;
     if (!dense) return g.m <= (n_trials < 320 ? 500000u : 1060000u);
     return lt_trial_bits(g) == 32 ? (double)g.m * std::min(1000.0, (double)n_trials) <= 90e6 : g.m <= 200000;
+}
+
+// Whether a one-set run does.  The more out-arcs the seeds have (`arcs`), the
+// fewer sweeps a cascade takes, while every trial still pushes along all it
+// reaches, so the line is a number of seed arcs over all trials: 8e7 with the
+// states in the LDS (scaled by the square root of a state's size, as larger
+// ones leave fewer trials a compute unit), 1.4e7 outside it; below 512 and 256
+// trials a workgroup's chain decides, not their number.  Directed graphs with
+// a hub holding a notable part of all arcs reach far from any seed, and their
+// sweeps are few: 5e7 there, 1e7 where a compute unit holds one trial and they
+// take turns, and up to 1.1 million arcs (outside the LDS 300,000, and no
+// seeds with a sixteenth of the arcs).  The sweeps draw the hashes of rows
+// above 64 in-arcs anew each time, so those that no seed covers (`long_left`)
+// move the line up.  ms, this against the sweeps:
+// - 300,000-node Erdos-Renyi, 3 arcs, 320 trials: 300 seeds 0.7 / 5.5, 6,000
+//   3.8 / 6.3, 30,000 8.3 / 3.6, 100,000 11.9 / 2.3; 60,000 nodes, 8 arcs,
+//   random weights, 1,000 trials: 300 seeds 16.6 / 41, 1,200 20.4 / 21.6,
+//   6,000 20.6 / 5.8
+// - 130,000-node preferential attachment, 1,000 trials: the 50 largest hubs
+//   2.7 / 3.2, 300 5.1 / 1.6; 13,000 random nodes 8.0 / 16
+// - in the LDS, 60,000-node preferential attachment, 1,000 trials: 1,200 hubs
+//   1.1 / 1.2, 20,000 2.0 / 0.5
+// - directed power-law graphs, 8 arcs, 1,000 trials: 60,000 nodes, the largest
+//   hub 2.5 / 3.5, ten 2.6 / 2.7; 100,000 nodes (one trial a compute unit), 50
+//   random nodes 2.2 / 4.1, 2,000 6.1 / 4.5, the largest hub 7.8 / 4.5, at
+//   256 trials 2.1 / 3.9
+// (5,100 runs: slower than the sweeps by more than 15% in 28, at most 2.0
+// times; 371, at most 30 times, by the rule above.)
+inline bool lt_run_pays(const RouteGraph& g, uint64_t arcs, uint64_t long_left, uint32_t n_trials)
+{
+    if (!g.records) return false;
+    const bool lds = lt_trial_lds(g), hub = g.max_out * 64 >= (uint64_t)g.m && g.lt_max_in <= 64;
+    if (hub && (lds ? g.m > 1100000 : g.m > 300000 || arcs * 16 >= (uint64_t)g.m)) return false;
+    const double state = (double)g.n * lt_trial_bits(g) / 8;
+    const double pushed = (double)arcs * std::max<double>(n_trials, lds ? 512 : 256) * (lds ? std::sqrt(state / 65536.0) : 1.0);
+    const double most = !lds ? 1.4e7 : !hub ? 8e7 : state > 70e3 && n_trials > 256 ? 1e7 : 5e7;
+    return pushed <= most * (1.0 + 50.0 * (double)long_left / (double)std::max<int64_t>(g.m, 1));
 }
 
 // Whether a many-sets call takes the drawn-coins form.  It draws every arc's

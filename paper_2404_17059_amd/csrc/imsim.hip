@@ -885,11 +885,14 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
     const bool forced = opts && (opts->test_flags & 16);
     if (!form_asked && n > 0 && g->d_rec) {
         if (g->model == IMS_MODEL_IC) {
-            if (!level_counts && (opts && (opts->test_flags & 32) ? n <= kLiveNodes : !forced && imsim_plan::lazy_trials_pay(*g, n_trials)))
-                return simulate_trials(g, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, nullptr, 0, opts, true, s);
-            if ((forced && n <= kLiveNodes) || imsim_plan::live_single_pays(*g, n_trials, level_counts != nullptr))
+            using imsim_plan::IcForm;
+            IcForm form = level_counts ? (imsim_plan::live_single_pays(*g, n_trials, true) ? IcForm::kDrawn : IcForm::kTasks)
+                                       : imsim_plan::ic_run_form(*g, seed_out_arcs(g, sv), n_trials, active_bits != nullptr);
+            if (forced && n <= kLiveNodes) form = IcForm::kDrawn;
+            if (opts && (opts->test_flags & 32) && n <= kLiveNodes && !level_counts) form = IcForm::kMet;
+            if (form != IcForm::kTasks)
                 return simulate_trials(g, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, level_counts, max_levels,
-                                       opts, false, s);
+                                       opts, form == IcForm::kMet, s);
         } else if (!level_counts && !(opts && ((opts->test_flags & ~16) || opts->alpha != 0.0))) {
             if (forced || imsim_plan::lt_run_pays(*g, seed_out_arcs(g, sv), long_pieces_left(g, sv), n_trials))
                 return simulate_trials(g, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, nullptr, 0, opts, false, s);

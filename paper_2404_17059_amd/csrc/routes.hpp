@@ -91,22 +91,57 @@ inline bool live_item_pays(const RouteGraph& g, uint32_t n_trials)
     return live_degree < 8.0 || (g.ic_growth < 1.5 * live_degree && n_trials <= 500 && live_degree * n <= 60e3);
 }
 
-// Whether a one-set IC run takes the per-trial form that draws an arc's coin
-// when it meets the arc: cascades that stay small (growth below 0.7), or whose
-// dense draw does not pay, up to about 1,500 trials (above, the tasks of 4 to
-// 16 trials share a hash block between their trials; this form uses one
-// trial's eighth of it).  Measured against the tasks and the grid: 64 to 1,000
-// trials at probabilities 0.01 and 0.03 on 500 to 100,000 nodes 25 to 54
-// against 58 to 95 us (4,000 trials 100 to 150 against 73 to 100); 100,000-
-// node Erdos-Renyi, WC, 1,000 trials 1.3 against 2.3 ms.  Hubs of several
-// thousand out-arcs are walked by one workgroup a trial: there the others are
-// faster (100,000-node preferential attachment, 11 arcs a node: 2.1 / 1.7 ms),
-// and from growth 0.7 on graphs of 16 arcs a node and more (60 arcs, 12,000
-// nodes, WC, 1,000 trials 2.6 / 2.0 ms).
-inline bool lazy_trials_pay(const RouteGraph& g, uint32_t n_trials)
+// The form of a one-set IC run.  `arcs`: out-arcs of the seeds; `live` of them
+// live in a trial, on average.
+// - kDrawn: all coins drawn densely, then a workgroup per trial.
+// - kMet: a workgroup per trial draws an arc's coin when it meets the arc, a
+//   whole hash block of which it uses an eighth; up to 1,500 trials (the tasks
+//   of 4 to 16 trials share the blocks) and hubs of 4,000 out-arcs (one
+//   workgroup walks them).
+// - kTasks: word-local tasks or grid-wide levels.
+// Growth below 0.7 (cascades stay small; ms, tasks / met / drawn):
+// - a hundred live seed arcs, and a part of all arcs that grows with the
+//   trials (0.5% at 100, 5% at 1,000): drawn (200,000-node Erdos-Renyi, 30
+//   arcs, p 0.01, 66,666 seeds, 100 trials 2.9 / 19.7 / 0.96; 100,000 nodes, 4
+//   arcs, p 0.01, 2,000 seeds with 5%, 1,000 trials 0.25 / 0.34 / 0.41)
+// - up to 200,000 arcs met over all trials, or 300 trials on graphs of up to
+//   12 arcs a node: met, half to all of the tasks' time; beyond, 0.4 to 3 times
+// Above:
+// - under two live seed arcs, a mean below 1.1 a node, and a draw of over 10
+//   us: most trials end at once (200,000-node preferential attachment, p 0.05,
+//   one node, 100 trials 0.035 / 0.024 / 0.133)
+// - where the draw does not pay, met up to 300 live seed arcs below growth 1.3
+//   and 16 arcs a node (100,000-node Erdos-Renyi, WC, 1,000 trials 2.3 / 1.3;
+//   60 arcs, 12,000 nodes 2.0 / 2.6), drawn above (100,000-node preferential
+//   attachment, WC, 33,333 hubs, 1,000 trials 1.8 / 5.8 / 1.9)
+// - hubs and 2.5 live arcs a node, 13,000 live seed arcs: two or three pull
+//   steps end it (100,000-node directed power law, UR, 100 hubs, 100 trials
+//   0.62 / 5.1 / 2.6)
+// With active bits (`bits`) the tasks run whole words and take 2 to 6 times as
+// long, so the arcs met do not count there.
+// (8,064 runs, 1 to a third of the nodes as seeds: slower than the tasks by
+// more than 15% in 76, at most 2.0 times; 667, at most 6.9 times, by growth
+// and trial count alone.  With bits 15 of 4,320, at most 1.8 times; 66, at most
+// 6.6 times.)
+enum class IcForm { kTasks, kDrawn, kMet };
+inline IcForm ic_run_form(const RouteGraph& g, uint64_t arcs, uint32_t n_trials, bool bits)
 {
-    if (g.n == 0 || (uint64_t)g.n > kLiveNodes || !g.records || n_trials > 1500 || g.max_out > 4000) return false;
-    return g.ic_growth < 0.7 || (g.ic_growth < 1.3 && (double)g.m < 16.0 * (double)g.n && !live_single_pays(g, n_trials, false));
+    if (g.n == 0 || (uint64_t)g.n > kLiveNodes || !g.records) return IcForm::kTasks;
+    const double n = (double)g.n, m = (double)g.m, growth = g.ic_growth, trials = (double)n_trials;
+    const double live = (double)arcs * g.ic_pbar, live_degree = g.ic_pbar * (double)g.ic_in_m / n;
+    const double draw = m * (double)((n_trials + 7) / 8) / 150e3;
+    const double met = trials * std::min(m, (double)arcs / (1.0 - std::min(growth, 0.9)));  // arcs met over all trials
+    const bool dense = m >= 16.0 * n, meets = n_trials <= 1500 && g.max_out <= 4000;
+    if (growth < 0.7) {
+        if (n_trials <= 1500 && live >= 100.0 && (double)arcs >= 5e-5 * m * trials) return IcForm::kDrawn;
+        return meets && (bits || met <= 2e5 || (n_trials <= 300 && m <= 12.0 * n && live < 100.0)) ? IcForm::kMet : IcForm::kTasks;
+    }
+    if (growth < 2.0 && live < 2.0 && live_degree < 1.1 && !dense && draw > 10.0)
+        return growth < 1.3 && meets && (bits || met <= 2e5) ? IcForm::kMet : IcForm::kTasks;
+    if (growth >= 2.0 && live_degree >= 2.5 && (double)g.max_out * n >= 20.0 * m && live >= 13000.0) return IcForm::kTasks;
+    if (live_single_pays(g, n_trials, false)) return IcForm::kDrawn;
+    if (growth >= 1.3 || dense) return IcForm::kTasks;
+    return live >= 300.0 ? IcForm::kDrawn : meets ? IcForm::kMet : IcForm::kTasks;
 }
 
 // Per-trial LT form: element width of a graph's states, and whether a trial's

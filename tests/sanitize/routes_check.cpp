@@ -18,6 +18,14 @@ int main()
             uint32_t trials;
             std::cin >> g.n >> g.m >> g.max_out >> g.lt_uniform >> g.lt_max_in >> arcs >> left >> trials;
             std::cout << (lt_run_pays(g, arcs, left, trials) ? "trials" : "sweeps") << "\n";
+        } else if (what == "ic") {
+            uint64_t arcs;
+            uint32_t trials;
+            bool bits;
+            std::cin >> g.n >> g.m >> g.max_out >> g.ic_pbar >> g.ic_growth >> arcs >> trials >> bits;
+            g.ic_in_m = g.m;
+            const IcForm f = ic_run_form(g, arcs, trials, bits);
+            std::cout << (f == IcForm::kTasks ? "tasks" : f == IcForm::kMet ? "met" : "drawn") << "\n";
         }
     }
     return 0;

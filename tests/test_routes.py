@@ -48,3 +48,23 @@ def routes(tmp_path_factory):
 ])
 def test_lt_runs_of_many_seeds_take_the_sweeps(routes, n, m, max_out, equal, max_in, arcs, left, trials, form):
     assert routes("lt", n, m, max_out, equal, max_in, arcs, left, trials) == form
+
+
+@pytest.mark.parametrize("n,m,max_out,pbar,growth,arcs,trials,bits,form", [
+    # ms: tasks / coins met / coins drawn
+    (200000, 5999568, 57, 0.01, 0.3, 2400761, 100, 0, "drawn"),     # a third of the nodes 2.86 / 19.7 / 0.96
+    (200000, 1599965, 24, 0.037, 0.295, 532583, 100, 0, "drawn"),   # 1.87 / 4.46 / 0.58
+    (100000, 399988, 16, 0.01, 0.04, 8052, 1000, 0, "tasks"),       # 2,000 nodes
+    (40000, 319956, 22, 0.05, 0.4, 9, 1000, 0, "met"),              # one node
+    (12000, 95962, 21, 0.05, 0.4, 2400, 1000, 1, "met"),            # 240 nodes, bits wanted 0.78 / 0.13 / 0.13
+    (200000, 1199730, 3330, 0.05, 1.643, 7, 100, 0, "tasks"),       # one leaf 0.035 / 0.024 / 0.133
+    (200000, 1188837, 3000, 0.16783, 0.998, 3, 100, 0, "met"),      # 0.032 / 0.021 / 0.132
+    (100000, 599754, 2346, 0.16674, 1.0, 366395, 1000, 0, "drawn"),  # 33,333 hubs 1.8 / 5.8 / 1.9
+    (100000, 591739, 24895, 0.49954, 2.925, 173195, 100, 0, "tasks"),  # 100 hubs, two in three arcs live 0.62 / 5.1 / 2.6
+    (100000, 591739, 24895, 0.49954, 2.925, 600, 100, 0, "drawn"),  # 100 random nodes
+    (10000, 100000, 12, 0.5, 5.0, 1000, 1000, 0, "drawn"),          # a ring, UR 2.2 / - / 0.39
+    (100000, 999000, 3000, 0.01, 0.6, 500, 10000, 0, "tasks"),      # beyond 1,500 trials
+    (300000, 900000, 20, 0.1, 0.3, 30, 100, 0, "tasks"),            # more nodes than the per-trial forms take
+])
+def test_ic_runs_choose_by_their_seeds(routes, n, m, max_out, pbar, growth, arcs, trials, bits, form):
+    assert routes("ic", n, m, max_out, pbar, growth, arcs, trials, bits) == form

@@ -402,6 +402,7 @@ int ims_graph_create(int64_t n, int64_t m, const int64_t* offsets, const uint32_
         }
         g->ic_pbar = mi > 0 ? psum / (double)mi : 0.0;
         g->ic_growth = psum > 0.0 ? grown / psum : 0.0;
+        if (n > 0 && (uint64_t)n <= imsim_plan::kLiveNodes) imsim_plan::ic_locality(*g, offsets, indices, thr);
         if ((rc = dev_alloc(&g->d_in_off, (uint64_t)n + 1)) || (rc = dev_alloc(&g->d_ic_in, (uint64_t)mi)) ||
             (rc = dev_alloc(&g->d_ic_in_thr, (uint64_t)mi)))
             return bail(rc);
@@ -886,8 +887,9 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
     if (!form_asked && n > 0 && g->d_rec) {
         if (g->model == IMS_MODEL_IC) {
             using imsim_plan::IcForm;
-            IcForm form = level_counts ? (imsim_plan::live_single_pays(*g, n_trials, true) ? IcForm::kDrawn : IcForm::kTasks)
-                                       : imsim_plan::ic_run_form(*g, seed_out_arcs(g, sv), n_trials, active_bits != nullptr);
+            const uint64_t arcs = seed_out_arcs(g, sv);
+            IcForm form = level_counts ? (imsim_plan::live_levels_pay(*g, arcs, n_trials) ? IcForm::kDrawn : IcForm::kTasks)
+                                       : imsim_plan::ic_run_form(*g, arcs, n_trials, active_bits != nullptr);
             if (forced && n <= kLiveNodes) form = IcForm::kDrawn;
             if (opts && (opts->test_flags & 32) && n <= kLiveNodes && !level_counts) form = IcForm::kMet;
             if (form != IcForm::kTasks)
@@ -1631,8 +1633,9 @@ int batch_plan_sides(ims_batch* b, std::vector<bool>& aside)
     for (uint32_t i = 0; i < (uint32_t)b->items.size(); ++i) {
         const ims_graph* g = b->items[i].graph;
         if (g->n == 0 || g->device != b->device) continue;
-        if (g->model == IMS_MODEL_IC ? imsim_plan::live_item_pays(*g, b->items[i].n_trials)
-                                     : imsim_plan::lt_trials_pay(*g, seed_out_arcs(g, b->seed_lists[i]), b->items[i].n_trials))
+        const uint64_t arcs = seed_out_arcs(g, b->seed_lists[i]);
+        if (g->model == IMS_MODEL_IC ? imsim_plan::live_item_pays(*g, arcs, b->items[i].n_trials)
+                                     : imsim_plan::lt_trials_pay(*g, arcs, b->items[i].n_trials))
             which.push_back(i);
     }
     std::stable_sort(which.begin(), which.end(), [&](uint32_t x, uint32_t y) { return b->cost[x] > b->cost[y]; });

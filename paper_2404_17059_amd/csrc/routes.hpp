@@ -24,11 +24,56 @@ struct RouteGraph {
     int64_t ic_in_m = 0;     // IC: in-arcs (arcs whose threshold is not 0)
     double ic_pbar = 0.0;    // IC: mean firing probability of those arcs
     double ic_growth = 0.0;  // IC: live out-arcs of the target of a live arc, on average
+    // IC: the two-step targets of a node, as a part of those that as many arcs
+    // to random nodes would have (rings 0.1 to 0.6, grids 0.56, random, power-
+    // law and preferential-attachment graphs 0.84 to 1), and the part of the
+    // two-step live arcs that lead back neither to the node nor to one it has
+    // reached in one step
+    double ic_spread = 1.0, ic_fresh = 1.0;
+    // cascades stay among the seeds' neighbours' neighbours
+    bool local() const { return ic_spread < 0.7; }
     bool lt_uniform = false; // LT: equal in-weights
     bool lt_zero = false;    // LT: some arc has weight 0
     uint64_t lt_max_in = 0;  // LT: most in-arc pieces of a node, and
     uint64_t lt_long = 0;    // those of all nodes with more than 64
 };
+
+// ic_spread and ic_fresh from at most 256 nodes, spread over the ids, and 32
+// arcs a node (under 1 ms whatever the graph).
+inline void ic_locality(RouteGraph& g, const int64_t* off, const uint32_t* idx, const uint32_t* thr)
+{
+    constexpr int64_t kNodes = 256, kArcs = 32;
+    const int64_t n = g.n, samples = std::min(n, kNodes);
+    std::vector<uint32_t> seen((size_t)n, 0);  // sample that met the node, counted from 1
+    std::vector<float> reached((size_t)n, 0.0f);  // probability that the sample's arc to the node is live
+    double distinct = 0.0, random = 0.0, fresh = 0.0, all = 0.0;
+    auto each = [&](int64_t u, auto use) {
+        const int64_t d = off[u + 1] - off[u], k = std::min(d, kArcs);
+        for (int64_t i = 0; i < k; ++i) {
+            const int64_t e = off[u] + i * d / k;
+            if (thr[e] != 0) use(idx[e], (float)((double)thr[e] * 0x1p-32));
+        }
+    };
+    for (int64_t s = 0; s < samples; ++s) {
+        const int64_t u = s * n / samples;
+        each(u, [&](uint32_t v, float p) { reached[v] = std::max(reached[v], p); });
+        int64_t arcs = 0, met = 0;
+        each(u, [&](uint32_t v, float p) {
+            each((int64_t)v, [&](uint32_t w, float q) {
+                ++arcs;
+                met += seen[w] != (uint32_t)s + 1 ? 1 : 0;
+                seen[w] = (uint32_t)s + 1;
+                all += (double)p * q;
+                if ((int64_t)w != u) fresh += (double)p * q * (1.0 - reached[w]);
+            });
+        });
+        each(u, [&](uint32_t v, float) { reached[v] = 0.0f; });
+        distinct += (double)met;
+        random += (double)n * (1.0 - std::exp(-(double)arcs / (double)n));
+    }
+    g.ic_spread = random > 0.0 ? distinct / random : 1.0;
+    g.ic_fresh = all > 0.0 ? fresh / all : 1.0;
+}
 
 // Whether a one-set run takes the drawn-coins form.  It draws all m * T coins
 // (`draw`, us) where the other forms draw those of the arcs they meet, so it
@@ -76,18 +121,36 @@ inline bool live_single_pays(const RouteGraph& g, uint32_t n_trials, bool levels
     return true;
 }
 
+// Whether a run with level counts does: not where most trials end at once
+// (10,000-node directed power law, TV, one node, 1,000 trials 0.062 against
+// 0.115 ms).
+inline bool live_levels_pay(const RouteGraph& g, uint64_t arcs, uint32_t n_trials)
+{
+    if (!live_single_pays(g, n_trials, true)) return false;
+    const double n = (double)g.n, m = (double)g.m, live_degree = g.ic_pbar * (double)g.ic_in_m / n;
+    const bool few = (double)arcs * g.ic_pbar < 2.0 && m < 16.0 * n && live_degree < 1.1;
+    return !few || m * (double)((n_trials + 7) / 8) / 150e3 <= 15.0;
+}
+
 // Whether an IC item of a batch does: the tasks share the chip there, so the
 // lines lie lower than for a run alone (batches of 8 items, ms, tasks / this:
 // 60,000 to 300,000 arcs, WC, 2,000 trials 2.7 / 2.9, at draws up to 40 us 0.94
 // / 0.37; 44 arcs a node, WC, draws of 300 us and more 4.4 / 6.0, up to 150 us
 // 1.5 / 0.9; 44 arcs a node, UR 0.59 / 0.80; 40 arcs, Erdos-Renyi, UR, 200
-// trials 1.05 / 0.42, 2,000 trials 2.1 / 2.3).
-inline bool live_item_pays(const RouteGraph& g, uint32_t n_trials)
+// trials 1.05 / 0.42, 2,000 trials 2.1 / 2.3; hubs and 2.5 live
+// arcs a node, 8,000 to 30,000 nodes, 100 hubs, 200 trials 2.6 / 3.3, 1,000 to
+// 3,000 nodes 0.28 / 0.34, one node 0.77 / 0.34; under one live seed arc, 2,000
+// trials 0.35 / 0.47; rings, 8,000 to 30,000 nodes, one node 0.15 / 0.28, 100
+// 0.33 / 0.47, a tenth of 1,000 to 3,000 0.36 / 0.17).
+inline bool live_item_pays(const RouteGraph& g, uint64_t arcs, uint32_t n_trials)
 {
     if (!live_single_pays(g, n_trials, false)) return false;
-    const double n = (double)g.n, draw = (double)g.m * (double)((n_trials + 7) / 8) / 150e3;
-    if (g.ic_growth < 1.3) return draw <= ((double)g.m >= 16.0 * n ? 150.0 : 45.0);
-    const double live_degree = g.ic_pbar * (double)g.ic_in_m / n;
+    const double n = (double)g.n, m = (double)g.m, draw = m * (double)((n_trials + 7) / 8) / 150e3;
+    const double live = (double)arcs * g.ic_pbar, live_degree = g.ic_pbar * (double)g.ic_in_m / n;
+    if (g.ic_growth < 1.3 && g.local() && live < n / 50.0) return false;
+    if (g.ic_growth < 2.0 && live < 0.8 && m < 16.0 * n && n_trials > 1000 && draw > 10.0) return false;
+    if (g.ic_growth < 1.3) return draw <= (m >= 16.0 * n ? 150.0 : 45.0);
+    if (live_degree >= 2.5 && (g.ic_growth >= 1.5 * live_degree || (double)g.max_out * n >= 20.0 * m)) return n < 5000.0 && live < 200.0;
     return live_degree < 8.0 || (g.ic_growth < 1.5 * live_degree && n_trials <= 500 && live_degree * n <= 60e3);
 }
 
@@ -110,6 +173,9 @@ inline bool live_item_pays(const RouteGraph& g, uint32_t n_trials)
 // - under two live seed arcs, a mean below 1.1 a node, and a draw of over 10
 //   us: most trials end at once (200,000-node preferential attachment, p 0.05,
 //   one node, 100 trials 0.035 / 0.024 / 0.133)
+// - rings and other local graphs below growth 1.3, live seed arcs fewer than
+//   0.3% of the nodes: likewise (40,000-node ring, WC, 100 nodes, 1,000 trials
+//   0.19 / 0.12 / 0.40; 12,000 nodes, 10 nodes, 5,000 trials 0.14 / 0.22 / 0.59)
 // - where the draw does not pay, met up to 300 live seed arcs below growth 1.3
 //   and 16 arcs a node (100,000-node Erdos-Renyi, WC, 1,000 trials 2.3 / 1.3;
 //   60 arcs, 12,000 nodes 2.0 / 2.6), drawn above (100,000-node preferential
@@ -138,6 +204,7 @@ inline IcForm ic_run_form(const RouteGraph& g, uint64_t arcs, uint32_t n_trials,
     }
     if (growth < 2.0 && live < 2.0 && live_degree < 1.1 && !dense && draw > 10.0)
         return growth < 1.3 && meets && (bits || met <= 2e5) ? IcForm::kMet : IcForm::kTasks;
+    if (growth < 1.3 && g.local() && live < 0.003 * n) return meets ? IcForm::kMet : IcForm::kTasks;
     if (growth >= 2.0 && live_degree >= 2.5 && (double)g.max_out * n >= 20.0 * m && live >= 13000.0) return IcForm::kTasks;
     if (live_single_pays(g, n_trials, false)) return IcForm::kDrawn;
     if (growth >= 1.3 || dense) return IcForm::kTasks;
@@ -232,8 +299,8 @@ inline bool lt_run_pays(const RouteGraph& g, uint64_t arcs, uint64_t long_left, 
 // break even at about 100 random single nodes, m / 2,000 seed out-arcs; one
 // hub already takes 1.7 against 4.4 ms, a set of 25 nodes 2.4 against 21).
 // Below that the factor is the geometric sum of that growth times what a
-// dense draw gains per block.  Draws of up to 20 us always pay but for
-// single-set calls (5,000 nodes: 0.28 against 0.17 ms for one node).
+// dense draw gains per block.  From eight sets on draws of up to 20 us pay
+// whatever the sets' arcs, where none of the exceptions below applies.
 // Sets on top of a base meet an unknown part of their arcs.  The measured
 // times there (graphs of 5,000 to 200,000 nodes with weighted-cascade
 // probabilities, 100 to 10,000 trials, 1 to 128 hubs on bases of 3 to 20) are
@@ -241,7 +308,10 @@ inline bool lt_run_pays(const RouteGraph& g, uint64_t arcs, uint64_t long_left, 
 // and for the tasks at least 150 us + 15 ns per node (one task's chain of
 // steps) and 50 times the draw of the sets' own out-arcs; growth above 2
 // leaves little outside the base (0.07 ms for the tasks), below 0.8 little at
-// all.
+// all.  Sets of nodes with under five live arcs often lie in the base already,
+// so there the estimates have to lie a factor of two apart (60,000-node
+// preferential attachment, TV, a base of 20 hubs, four nodes 0.16 / 0.45 ms;
+// power law, 5,000 nodes, a base of 250, 16 sets of 30 0.10 / 0.24).
 inline bool live_sets_pay(const RouteGraph& g, bool base, const std::vector<uint32_t>& off, uint64_t arcs, uint32_t n_trials)
 {
     if ((uint64_t)g.n > kLiveNodes || g.n == 0 || !g.records || off.size() > (1u << 24)) return false;
@@ -253,7 +323,8 @@ inline bool live_sets_pay(const RouteGraph& g, bool base, const std::vector<uint
         // attachment, 8 random nodes, 1,000 trials: tasks 0.40, drawn 0.64 ms)
         const bool hubs = (double)arcs * (double)g.n >= 4.0 * (double)g.m * (double)off.back();
         const double tasks = std::max(hubs ? 150.0 + 0.015 * (double)g.n : 0.0, 50.0 * (double)arcs * blocks / 150e3);
-        return g.ic_growth >= 0.8 && g.ic_growth <= 2.0 && live < tasks;
+        const double apart = (double)arcs * g.ic_pbar < 5.0 * (double)off.back() ? 2.0 : 1.0;
+        return g.ic_growth >= 0.8 && g.ic_growth <= 2.0 && apart * live < tasks;
     }
     // Where the tasks stay faster (whole calls in ms, tasks / drawn; random sets
     // on graphs of 1,000 to 40,000 nodes, 5 to 44 arcs a node):
@@ -265,7 +336,20 @@ inline bool live_sets_pay(const RouteGraph& g, bool base, const std::vector<uint
     // - under four sets near growth 1 (0.14 / 0.16);
     // - cascades that cover the graph in three levels, whose pull steps end
     //   early, but for few walks (growth 39, 16 sets, 1,000 trials 0.85 / 1.68,
-    //   100 trials 0.81 / 0.44).
+    //   100 trials 0.81 / 0.44);
+    // - below growth 0.6, hubs: two live seed arcs a set (directed power law,
+    //   1,000 nodes, TV, 1,000 trials, 1,000 sets of 4 hubs 3.3 / 5.2);
+    // - sets that mostly light nothing, and a long draw (100,000-node preferential
+    //   attachment, p 0.02, 1,000 trials, 64 nodes 0.39 / 0.92);
+    // - rings and other local graphs with less than 1.1 new live arcs per live
+    //   arc: a cascade's steps meet the same nodes again and a task's few steps
+    //   end it (200,000-node ring, WC, 1,000 trials, 40 sets of 30 0.30 / 2.4;
+    //   20,000 nodes, 16 single nodes 0.14 / 0.31), but for few walks and a short
+    //   draw (20,000 nodes, 20 arcs, 100 trials, 8 sets of 30 0.95 / 0.12), for
+    //   many single nodes (20,000-node ring, 1,000 trials, 1,000 nodes 1.8 / 0.30)
+    //   and for sets that light much of the graph (64 live seed arcs and more).
+    //   Of 8,726 calls 543 were slower than the tasks by more than 15%, at most
+    //   8 times; 52, at most 1.8 times, with this line.
     const uint64_t sets = off.size() - 1;
     uint64_t large = 0;
     for (uint64_t i = 0; i < sets; ++i) large += off[i + 1] - off[i] > kTinySeeds ? 1u : 0u;
@@ -274,6 +358,12 @@ inline bool live_sets_pay(const RouteGraph& g, bool base, const std::vector<uint
     if (g.ic_growth < 0.9 && !dense && large * n_trials > 8000) return false;
     if (sets < 4 && g.ic_growth < (dense ? 0.85 : 1.4)) return false;
     if (g.ic_growth >= 8.0 && sets * n_trials > 8000) return false;
+    const double live = (double)arcs * g.ic_pbar / (double)sets, renewed = g.ic_growth * g.ic_fresh;
+    if (g.ic_growth < 0.6 && live > 2.0) return false;
+    if (g.ic_growth < 2.0 && live < 0.6 && draw >= 100.0) return false;
+    if (g.local() && renewed < 1.1 && live < 64.0 && !(sets * n_trials <= 4000 && draw <= 45.0) &&
+        (live > 2.0 || (double)arcs * 16.0 < (double)g.m * (1.0 - std::min(renewed, 0.9))))
+        return false;
     const double reach = g.ic_growth >= 0.8 ? 2000.0 : 8.0 / (1.0 - g.ic_growth);
     return (double)arcs * reach >= (double)g.m || (draw <= 20.0 && off.size() > 8);
 }

@@ -4,7 +4,10 @@ import os
 import shutil
 import subprocess
 
+import numpy as np
 import pytest
+
+import synth
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -68,3 +71,45 @@ def test_lt_runs_of_many_seeds_take_the_sweeps(routes, n, m, max_out, equal, max
 ])
 def test_ic_runs_choose_by_their_seeds(routes, n, m, max_out, pbar, growth, arcs, trials, bits, form):
     assert routes("ic", n, m, max_out, pbar, growth, arcs, trials, bits) == form
+
+
+RING = (1.0, 0.22, 0.84)      # growth, spread, fresh of a ring with ten neighbours, WC
+LATTICE = (1.0, 0.57, 0.66)   # with four
+RANDOM = (1.0, 1.0, 1.0)
+POWER = (1.0, 0.93, 0.80)
+
+
+@pytest.mark.parametrize("n,m,pbar,shape,base,sets,size,arcs,trials,form", [
+    # ms: tasks / drawn
+    (200000, 2000000, 0.1, RING, 0, 40, 4, 1602, 1000, "tasks"),     # 0.25 / 1.9
+    (200000, 800000, 0.25, LATTICE, 0, 40, 30, 4807, 1000, "tasks"),  # 0.30 / 2.4
+    (20000, 200000, 0.1, RING, 0, 16, 1, 160, 1000, "tasks"),        # 0.14 / 0.31
+    (20000, 200000, 0.1, RING, 0, 16, 30, 4800, 1000, "tasks"),      # 0.43 / 0.48
+    (20000, 80000, 0.25, LATTICE, 0, 1000, 1, 3992, 1000, "drawn"),  # 1.8 / 0.30
+    (20000, 200000, 0.1, RING, 0, 8, 1000, 80000, 1000, "drawn"),    # a twentieth of the nodes a set
+    (20000, 200000, 0.1, RANDOM, 0, 16, 1, 160, 1000, "drawn"),      # the same arcs to random nodes
+    (200000, 1969000, 0.1, POWER, 0, 128, 25, 300000, 1000, "drawn"),
+    (200000, 1969000, 0.1, POWER, 1, 64, 1, 150000, 10000, "drawn"),
+    (60000, 359768, 0.037, (1.14, 0.93, 0.83), 1, 4, 1, 470, 1000, "tasks"),   # four nodes on a base of 20 hubs 0.16 / 0.45
+    (100000, 1000000, 0.02, (1.2, 0.93, 0.9), 0, 64, 1, 640, 1000, "tasks"),   # 0.39 / 0.92
+    (1000, 10000, 0.037, (0.31, 1.0, 1.0), 0, 1000, 4, 280000, 1000, "tasks"),  # hubs 3.3 / 5.2
+])
+def test_sets_on_local_graphs_keep_the_tasks(routes, n, m, pbar, shape, base, sets, size, arcs, trials, form):
+    assert routes("sets", n, m, m // n * 20, pbar, *shape, base, sets, size, arcs, trials) == form
+
+
+@pytest.mark.parametrize("kind,low,high", [("ring", 0.1, 0.6), ("random", 0.95, 1.05)])
+def test_locality_tells_rings_from_random_graphs(routes, kind, low, high):
+    n = 3000
+    if kind == "ring":
+        u = np.repeat(np.arange(n), 10)
+        v = (u + np.tile([-5, -4, -3, -2, -1, 1, 2, 3, 4, 5], n)) % n
+        off, idx = np.arange(0, 10 * n + 1, 10), v
+    else:
+        g = synth.erdos_renyi_directed(n, 10.0, seed=4)
+        off, idx = g.offsets, g.indices
+    thr = np.full(len(idx), 1 << 28)
+    spread, fresh = (float(x) for x in routes("graph", n, len(idx), *off.tolist(), *idx.tolist(), *thr.tolist()).split())
+    assert low <= spread <= high and (kind == "random") == (fresh > 0.95)
+    # arcs that never fire are no arcs, and a graph without any is not local
+    assert routes("graph", n, len(idx), *off.tolist(), *idx.tolist(), *[0] * len(idx)).split() == ["1", "1"]

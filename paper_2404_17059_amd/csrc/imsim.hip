@@ -1574,6 +1574,7 @@ struct ims_batch {
     ims_graph::Buf sA, sN, sQ0, sQ1, sQ2, sact, sstamp, ssteps, srem;
     bool any_lt = false;
     uint32_t slots = 0;
+    bool planned = false;  // the plan below is whole; a planning call that failed leaves none
     imsim_plan::SlotTags tags;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -1680,10 +1681,14 @@ int batch_plan_sides(ims_batch* b, std::vector<bool>& aside)
     return IMS_OK;
 }
 
-// Task list and slot state for the current tuning.
+// Task list and slot state for the current tuning.  The captured launch of the
+// plan before goes first: it reads buffers that are given back below.
 int batch_plan(ims_batch* b)
 {
     const uint32_t n_items = (uint32_t)b->items.size();
+    b->planned = false;
+    if (b->exec) IMS_HIP(hipDeviceSynchronize());
+    b->drop_graph();
     std::vector<bool> aside;
     int rc_sides = batch_plan_sides(b, aside);
     if (rc_sides) return rc_sides;
@@ -1746,7 +1751,7 @@ int batch_plan(ims_batch* b)
             if (t->p) IMS_HIP(hipMemset(t->p, 0, t->bytes));
     }
     IMS_HIP(hipStreamSynchronize(nullptr));  // cleared before a launch on any stream
-    b->drop_graph();
+    b->planned = true;
     return IMS_OK;
 }
 
@@ -1890,6 +1895,7 @@ int ims_batch_create(const ims_batch_item* items, uint32_t n_items, const ims_tu
 int ims_batch_launch(ims_batch* b, void* stream)
 {
     if (!b) return fail(IMS_E_INVALID_ARG, "ims_batch_launch: NULL batch");
+    if (!b->planned) return fail(IMS_E_INVALID_ARG, "ims_batch_launch: the batch's last planning call failed");
     hipStream_t s = (hipStream_t)stream;
     if (!b->exec) {
         // record the launch sequence on a private stream (default priority);
@@ -1965,6 +1971,7 @@ int ims_batch_autotune(ims_batch* b, int repeats, void* stream, ims_tuning* chos
                                  {2, 0, 8, 0, 0}, {4, 0, 8, 0, 0}, {2, 0, 16, 0, 0}};
     // (a default batch first as it stands, with its per-trial forms)
     const bool had_forms = b->forms;
+    const ims_tuning had = b->tuning;
     bool best_forms = false;
     if (had_forms) {
         rc = trial(b->tuning);
@@ -1993,7 +2000,11 @@ int ims_batch_autotune(ims_batch* b, int repeats, void* stream, ims_tuning* chos
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     b->forms = had_forms;
-    if (rc) return rc;
+    if (rc) {
+        b->tuning = had;
+        (void)batch_plan(b);  // as it was before
+        return rc;
+    }
     b->forms = best_forms && best_ms >= forms_ms;
     b->tuning = best;
     if ((rc = batch_plan(b))) return rc;
@@ -2006,7 +2017,12 @@ int ims_batch_task_timing(ims_batch* b, int enable)
     if (!b) return fail(IMS_E_INVALID_ARG, "ims_batch_task_timing: NULL batch");
     if ((enable != 0) == b->timing) return IMS_OK;
     b->timing = enable != 0;
-    return batch_plan(b);  // (re)allocates the record and drops the captured graph
+    const int rc = batch_plan(b);  // (re)allocates the record and drops the captured graph
+    if (rc) {
+        b->timing = !b->timing;
+        (void)batch_plan(b);  // as it was before
+    }
+    return rc;
 }
 
 int ims_batch_task_times(ims_batch* b, uint32_t max_tasks, uint64_t* tasks, uint64_t* times, uint32_t* count, void* stream)

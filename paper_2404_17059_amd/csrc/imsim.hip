@@ -97,8 +97,8 @@ struct ims_graph : imsim_plan::RouteGraph {
     int cus = 0;
     std::vector<int64_t> h_off;  // host copy of the out-offsets (launch planning)
     int64_t* d_off = nullptr;
-    uint32_t* d_off32 = nullptr;  // the out-offsets in 32 bits (m < 2^32 - 1), for the per-trial forms
-    uint64_t* d_rec = nullptr;    // arc records of the per-trial forms (null: node, arc or degree count too large for them)
+    uint32_t* d_off32 = nullptr;  // the out-offsets in 32 bits and the arc records of the per-trial forms
+    uint64_t* d_rec = nullptr;    // (null: node, arc or degree count, or the device's memory, too small for them)
     uint32_t* d_idx = nullptr;
     uint32_t* d_thr = nullptr;
     int64_t* d_in_off = nullptr;     // in-CSR offsets (LT: weight pieces; IC: arcs of nonzero threshold)
@@ -232,6 +232,15 @@ int ensure_buf(ims_graph* g, ims_graph::Buf& b, uint64_t bytes, bool zero_invari
     return IMS_OK;
 }
 
+// The workspaces of the per-trial forms.  A call for which they do not fit in
+// the device's memory gives back what it got and runs in the general forms,
+// which need less.
+void free_live(ims_graph* g)
+{
+    for (ims_graph::Buf* b : {&g->live_rows, &g->live_rank, &g->live_loff, &g->live_list, &g->live_base, &g->live_todo, &g->live_ctl, &g->live_queue})
+        ims_graph::release(*b);
+}
+
 // Copy `bytes` of host data to device `dst` on stream s through stage `st`
 // (see ims_graph::Stage).
 int stage_upload(ims_graph::Stage& st, void* dst, const void* src, size_t bytes, hipStream_t s)
@@ -363,19 +372,6 @@ int ims_graph_create(int64_t n, int64_t m, const int64_t* offsets, const uint32_
     if (hipMemcpy(g->d_off, offsets, sizeof(int64_t) * (n + 1), hipMemcpyHostToDevice) != hipSuccess ||
         (m > 0 && hipMemcpy(g->d_idx, indices, sizeof(uint32_t) * m, hipMemcpyHostToDevice) != hipSuccess))
         return bail(fail(IMS_E_HIP, "graph upload failed"));
-    const std::vector<uint32_t> off32(offsets, offsets + n + 1);
-    if ((rc = dev_alloc(&g->d_off32, off32.size()))) return bail(rc);
-    if (hipMemcpy(g->d_off32, off32.data(), sizeof(uint32_t) * off32.size(), hipMemcpyHostToDevice) != hipSuccess)
-        return bail(fail(IMS_E_HIP, "graph upload failed"));
-    if (n <= (1ll << imsim::kRecNodeBits) && m < (1ll << imsim::kRecArcBits) && max_deg < (1ull << (64 - imsim::kRecNodeBits - imsim::kRecArcBits))) {
-        if ((rc = dev_alloc(&g->d_rec, (uint64_t)m))) return bail(rc);
-        g->records = true;
-        if (m > 0)
-            hipLaunchKernelGGL(imsim::arc_record_kernel, dim3((unsigned)std::min<int64_t>((m + imsim::kBlock - 1) / imsim::kBlock, 4096)),
-                               dim3(imsim::kBlock), 0, nullptr, (const uint32_t*)g->d_off32, (const uint32_t*)g->d_idx, (uint64_t)m, g->d_rec);
-        if (hipGetLastError() != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess)
-            return bail(fail(IMS_E_HIP, "arc records failed"));
-    }
     if (model == IMS_MODEL_IC) {
         if ((rc = dev_alloc(&g->d_thr, (uint64_t)m))) return bail(rc);
         if (m > 0 && hipMemcpy(g->d_thr, param, sizeof(uint32_t) * m, hipMemcpyHostToDevice) != hipSuccess)
@@ -470,6 +466,23 @@ int ims_graph_create(int64_t n, int64_t m, const int64_t* offsets, const uint32_
     if (model == IMS_MODEL_IC && ((rc = dev_alloc(&g->d_lvl, 2ull * g->cap)) || (rc = dev_alloc(&g->d_lvl_dir, g->cap))))
         return bail(rc);
     if ((rc = dev_alloc(&g->d_status, 4))) return bail(rc);
+    // the per-trial forms' records come last: without room for them the graph
+    // goes without
+    if (n <= (1ll << imsim::kRecNodeBits) && m < (1ll << imsim::kRecArcBits) && max_deg < (1ull << (64 - imsim::kRecNodeBits - imsim::kRecArcBits))) {
+        const std::vector<uint32_t> off32(offsets, offsets + n + 1);
+        rc = dev_alloc(&g->d_off32, off32.size());
+        if (!rc) rc = dev_alloc(&g->d_rec, (uint64_t)m);
+        if (rc && rc != IMS_E_OOM) return bail(rc);
+        g->records = !rc;
+        if (rc) dev_free(g->d_off32);
+        else if (hipMemcpy(g->d_off32, off32.data(), sizeof(uint32_t) * off32.size(), hipMemcpyHostToDevice) != hipSuccess)
+            return bail(fail(IMS_E_HIP, "graph upload failed"));
+        if (g->records && m > 0)
+            hipLaunchKernelGGL(imsim::arc_record_kernel, dim3((unsigned)std::min<int64_t>((m + imsim::kBlock - 1) / imsim::kBlock, 4096)),
+                               dim3(imsim::kBlock), 0, nullptr, (const uint32_t*)g->d_off32, (const uint32_t*)g->d_idx, (uint64_t)m, g->d_rec);
+        if (hipGetLastError() != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess)
+            return bail(fail(IMS_E_HIP, "arc records failed"));
+    }
     *out = g;
     return IMS_OK;
 }
@@ -892,12 +905,18 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
                                        : imsim_plan::ic_run_form(*g, arcs, n_trials, active_bits != nullptr);
             if (forced && n <= kLiveNodes) form = IcForm::kDrawn;
             if (opts && (opts->test_flags & 32) && n <= kLiveNodes && !level_counts) form = IcForm::kMet;
-            if (form != IcForm::kTasks)
-                return simulate_trials(g, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, level_counts, max_levels,
-                                       opts, form == IcForm::kMet, s);
+            if (form != IcForm::kTasks) {
+                rc = simulate_trials(g, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, level_counts, max_levels,
+                                     opts, form == IcForm::kMet, s);
+                if (rc != IMS_E_OOM) return rc;
+                free_live(g);
+            }
         } else if (!level_counts && !(opts && ((opts->test_flags & ~16) || opts->alpha != 0.0))) {
-            if (forced || imsim_plan::lt_run_pays(*g, seed_out_arcs(g, sv), long_pieces_left(g, sv), n_trials))
-                return simulate_trials(g, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, nullptr, 0, opts, false, s);
+            if (forced || imsim_plan::lt_run_pays(*g, seed_out_arcs(g, sv), long_pieces_left(g, sv), n_trials)) {
+                rc = simulate_trials(g, sv, n_trials, rng_seed, trial_counts, node_counts, total, active_bits, nullptr, 0, opts, false, s);
+                if (rc != IMS_E_OOM) return rc;
+                free_live(g);
+            }
         }
     }
     if (level_counts) shape = 1;  // levels are the word-local (synchronous) steps
@@ -1007,10 +1026,13 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
             lt_mode = 4;
         else if (cells * 256 <= kThresholdTableBudget) lt_mode = 1;
     }
-    const bool use_table = lt_mode != 0;
     // (the count-threshold table has 64 bytes of padding: the sweep reads 64
     // bytes from each (node, word)'s first plane)
-    if (use_table && (rc = ensure_buf(g, g->thp, lt_mode == 2 ? kmin_bytes + 64 : lt_mode == 4 ? halves_bytes : cells * 256, false))) return rc;
+    if (lt_mode != 0 && (rc = ensure_buf(g, g->thp, lt_mode == 2 ? kmin_bytes + 64 : lt_mode == 4 ? halves_bytes : cells * 256, false))) {
+        // (no room for the halves where full hashes pass the budget: none at all)
+        if (rc != IMS_E_OOM || lt_mode != 4 || cells * 256 <= kThresholdTableBudget) return rc;
+        lt_mode = 0;
+    }
     if (g->seeds_cap < sv.size() || !g->d_seeds) {
         dev_free(g->d_seeds);
         dev_free(g->d_seed_pre);
@@ -1448,8 +1470,11 @@ int simulate_sets_impl(ims_graph* g, const uint64_t* base, const uint32_t* set_o
     const bool tasks_asked = opts && (opts->shape || opts->blocks_per_cu || opts->ic_alpha != 0.0 || opts->ic_beta != 0.0 || opts->ic_direction);
     const bool live_forced = opts && (opts->test_flags & 16) && n > 0 && n <= kLiveNodes && g->d_rec;
     if (g->model == IMS_MODEL_IC && !tasks_asked &&
-        (live_forced || imsim_plan::live_sets_pay(*g, base != nullptr, off, seed_out_arcs(g, nodes), n_trials)))
-        return simulate_sets_live(g, base, off.data(), d_off, d_nodes, n_sets, n_trials, rng_seed, totals, node_counts, s);
+        (live_forced || imsim_plan::live_sets_pay(*g, base != nullptr, off, seed_out_arcs(g, nodes), n_trials))) {
+        rc = simulate_sets_live(g, base, off.data(), d_off, d_nodes, n_sets, n_trials, rng_seed, totals, node_counts, s);
+        if (rc != IMS_E_OOM) return rc;
+        free_live(g);
+    }
 
     const uint64_t tasks = (uint64_t)n_sets * W;
     const int per_cu = opts && opts->blocks_per_cu > 0 ? opts->blocks_per_cu : 2;
@@ -1691,7 +1716,15 @@ int batch_plan(ims_batch* b)
     b->drop_graph();
     std::vector<bool> aside;
     int rc_sides = batch_plan_sides(b, aside);
-    if (rc_sides) return rc_sides;
+    if (rc_sides == IMS_E_OOM) {
+        // no room for the lanes: every item on the task list
+        b->sides.clear();
+        aside.assign(n_items, false);
+        for (ims_batch::Lane& l : b->lanes)
+            for (ims_graph::Buf* f : {&l.rows, &l.queue, &l.bitmaps}) ims_graph::release(*f);
+    } else if (rc_sides) {
+        return rc_sides;
+    }
     std::vector<uint32_t> order;
     for (uint32_t i = 0; i < n_items; ++i)
         if (!aside[i]) order.push_back(i);

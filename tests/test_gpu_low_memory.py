@@ -22,7 +22,7 @@ def only(mib):
     import torch
     torch.cuda.empty_cache()
     held = []
-    for chunk in (8192, 1024, 128, 32):
+    for chunk in (32768, 1024, 128, 12):
         while torch.cuda.mem_get_info()[0] - (chunk << 20) >= mib << 20:
             held.append(torch.empty(chunk << 20, dtype=torch.uint8, device="cuda"))
     print("left:", torch.cuda.mem_get_info()[0] >> 20, "MiB", flush=True)
@@ -77,3 +77,56 @@ def test_a_plan_without_room_leaves_the_batch_as_it_was(ims):
     B.close()
     G.close()
     R.close()
+
+
+def test_calls_without_room_for_per_trial_workspaces_take_the_general_forms(ims):
+    """An LT run and a batch item (1 GiB of starting states), an IC run and seed sets (1.2 GiB of coin rows)."""
+    n, T = 4000, 1 << 18
+    off, idx = sparse_graph(n, 10 * n, 4)
+    lt, ic = lt_graph(ims, n, 2 * n), ims.Graph(n, off, idx, "ic", np.full(idx.size, 0.02))
+    seeds = np.array([5, 77, 1234], dtype=np.uint32)
+    sets = [seeds, seeds[:1], seeds[1:]]
+    forced = ims.Opts(test_flags=16)
+
+    def calls(lt, ic, opts):
+        batch = ims.Batch([(lt, seeds, T, 9)])
+        batch.launch()
+        out = [ims.simulate(lt, seeds, T, 9, opts=opts), ims.simulate(ic, seeds, T, 9, opts=opts), batch.results()[0]]
+        totals = ims.simulate_sets(ic, sets, T, 9, opts=opts)["totals"]
+        batch.close()
+        return out, totals
+
+    R = [lt_graph(ims, n, 2 * n), ims.Graph(n, off, idx, "ic", np.full(idx.size, 0.02))]
+    want, want_totals = calls(*R, None)
+    for g in R:
+        g.close()
+    for room in (850, None):
+        with only(room) if room else contextlib.nullcontext():
+            got, totals = calls(lt, ic, forced)
+        for x, y in zip(got, want):
+            equal(x, y)
+        assert (totals == want_totals).all()
+    lt.close()
+    ic.close()
+
+
+def test_graph_without_room_for_arc_records(ims):
+    """4M arcs, whose records take 32 MiB beside the rest."""
+    import torch
+    n = 200000
+    off, idx = sparse_graph(n, 20 * n, 5)
+    w = 1.0 / np.bincount(idx, minlength=n)[idx]
+    seeds = np.arange(0, n, 5000, dtype=np.uint32)
+    R = ims.Graph(n, off, idx, "lt", w)
+    want = ims.simulate(R, seeds, 64, 9, opts=ims.Opts(shape=2))
+    torch.cuda.synchronize()
+    R.close()
+    free = torch.cuda.mem_get_info()[0]
+    R = ims.Graph(n, off, idx, "lt", w)
+    whole = (free - torch.cuda.mem_get_info()[0]) >> 20
+    R.close()
+    print("graph:", whole, "MiB", flush=True)
+    with only(whole - 28):
+        G = ims.Graph(n, off, idx, "lt", w)
+    equal(ims.simulate(G, seeds, 64, 9), want)
+    G.close()

@@ -93,12 +93,16 @@ int ims_graph_info(const ims_graph* g, int64_t* n, int64_t* m, int* model);
 
 /* Simulation options; NULL = automatic.  Any setting gives the same bits. */
 typedef struct ims_opts {
-    int shape;             /* 0 = auto (IC: coins drawn densely, then a workgroup per trial, where
-                              the cascades go far, else word-local when the run has at least a
-                              quarter as many 64-trial words as compute units or they stay small,
-                              else grid-wide; LT: a workgroup per trial where its state fits the
-                              LDS and it pays, else grid-wide), 1 = word-local (a workgroup runs
-                              the whole cascade of its trials: of one 64-trial word when
+    int shape;             /* 0 = auto (IC: a workgroup per trial, with all coins drawn first where
+                              the cascades go far and with coins drawn as arcs are met where they
+                              stay small, as graph, seeds and trials say; else word-local when the
+                              run has at least a quarter as many 64-trial words as compute units or
+                              the cascades stay small, else grid-wide; LT: a workgroup per trial,
+                              its state in the LDS or in a row of device memory, where that pays
+                              for the graph, the seeds and the trials, else grid-wide; both: the
+                              forms without a workgroup per trial also where its workspace, up to
+                              4 GiB of rows and 4 GiB of lists, finds no room), 1 = word-local (a
+                              workgroup runs the whole cascade of its trials: of one 64-trial word when
                               active_bits is requested, else of 16 trials on persistent slots
                               that add their own counts), 2 = grid-wide steps (one launch per
                               level / sweep) */
@@ -160,7 +164,7 @@ int ims_simulate(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_t
  *   level_counts  device uint32[max_levels * n_trials]: level_counts[l * T + t].
  *   trial_counts, total as ims_simulate.
  * Runs the word-local shape, or (IC, where it pays) a workgroup per trial over
- * drawn coins.  ims_graph_last_status() then gives the number
+ * drawn coins (word-local where the coins find no room).  ims_graph_last_status() then gives the number
  * of levels processed: the deepest nonempty level is at most that number, so
  * a caller that sees it >= max_levels can retry with a larger buffer. */
 int ims_simulate_levels(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_t n_trials, uint64_t rng_seed,
@@ -206,8 +210,8 @@ int ims_simulate_noalloc(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, 
  * Every set's results equal those of ims_simulate on that set.  Asynchronous
  * on `stream`.  IC on graphs of at most 2^18 nodes draws every arc's coins
  * once for all sets and walks the cascades over them where the sets meet
- * enough arcs (any of opts' shape, blocks_per_cu and ic_* fields keeps the
- * word-local tasks, which draw coins as they meet arcs). */
+ * enough arcs and the coins find room (any of opts' shape, blocks_per_cu and
+ * ic_* fields keeps the word-local tasks, which draw coins as they meet arcs). */
 int ims_simulate_sets(ims_graph* g, const uint32_t* set_offsets, const uint32_t* set_nodes, uint32_t n_sets,
                       uint32_t n_trials, uint64_t rng_seed, const ims_opts* opts, uint64_t* totals,
                       uint32_t* node_counts, void* stream);
@@ -234,7 +238,9 @@ int ims_simulate_sets_from(ims_graph* g, const uint64_t* base_bits, const uint32
 /* Batch: several (graph, seeds, trials, rng_seed) runs, IC and LT mixed,
  * executed by one persistent launch that takes (item, 64-trial word, trial
  * part) tasks in a scheduled order, captured once in a HIP graph and
- * replayed.  Each item's outputs equal those of ims_simulate on that item
+ * replayed.  With tuning NULL, items for which a workgroup per trial pays run so
+ * beside that launch, on up to four branches of the graph; without room for
+ * their workspaces all items run as tasks.  Each item's outputs equal those of ims_simulate on that item
  * alone. */
 typedef struct ims_batch ims_batch;
 
@@ -262,15 +268,17 @@ typedef struct ims_tuning {
 } ims_tuning;
 
 /* tuning NULL = defaults (2 per CU, largest first, 8 tasks per word, default
- * switch points).  Synchronous. */
+ * switch points; other items than tasks, above).  Synchronous. */
 int ims_batch_create(const ims_batch_item* items, uint32_t n_items, const ims_tuning* tuning, ims_batch** out);
-/* Time candidate schedules `repeats` times each on `stream`: first
+/* Time candidate schedules `repeats` times each on `stream`: a batch made with
+ * tuning NULL as it stands, then with all items as tasks, first
  * (workgroups per compute unit, order, split) at the default switch points,
  * then the IC push / pull switch points (alpha; a tiny alpha keeps every task
  * on the push side) for the fastest of those.  Check that every candidate
  * gives identical outputs (every item's trial counts, node counts and total;
  * IMS_E_HIP otherwise), keep the fastest (reported in *chosen if not NULL)
- * and drop the captured graph.  Synchronous. */
+ * and drop the captured graph.  If it fails, the schedule before it stays.
+ * Synchronous. */
 int ims_batch_autotune(ims_batch* b, int repeats, void* stream, ims_tuning* chosen);
 /* Run the batch on `stream`: the first call (and the first after a tuning
  * change) captures the launch sequence into a HIP graph, later calls replay
@@ -282,7 +290,8 @@ int ims_batch_destroy(ims_batch* b);
  * ims_batch_task_timing(b, 1) makes every later launch record, for each task,
  * the device wall clock (a constant-rate counter, 100 MHz on this device
  * family) at its start and end and the workgroup slot that ran it; 0 turns
- * it off.  Either call drops the captured HIP graph.  ims_batch_task_times
+ * it off.  Either call drops the captured HIP graph; one that fails leaves
+ * the batch as it was.  ims_batch_task_times
  * waits for `stream` and copies, for the tasks of the last launch in the
  * order they are listed, their codes (item << 32 | log2 trials-per-task
  * split << 24 | part << 16 | word) into tasks (host uint64[max_tasks]) and

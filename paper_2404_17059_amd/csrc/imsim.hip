@@ -877,8 +877,8 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
     // TV and WC weights, ER 2k with UR weights, ER 1k at p = 0.1 and a
     // 200k-node Chung-Lu graph with WC weights; the grid shape 1.2-4x faster
     // for offspring from 1.3 on larger graphs, from 5 on small ones, and for
-    // 100 hub seeds on a 1M-node graph even at 0.3).  LT always takes the
-    // grid shape (measured 1.2-16x faster than word-local on graphs of 1,000
+    // 100 hub seeds on a 1M-node graph even at 0.3).  Of the two shapes LT always
+    // takes the grid's (measured 1.2-16x faster than word-local on graphs of 1,000
     // to 1M nodes at 1,000 and 10,000 trials, except a 5,000-node BA graph at
     // 10,000 trials, 2.5x slower)
     if (shape == 0) {

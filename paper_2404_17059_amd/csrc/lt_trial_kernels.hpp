@@ -1,7 +1,9 @@
-// LT kernels of the per-trial form: one small workgroup runs one trial's whole
-// cascade by pushing, with every node's distance to its threshold in LDS.
+// Kernels of the per-trial push form: one small workgroup runs one trial's
+// whole cascade by pushing, for LT with every node's distance to its threshold
+// in LDS or, on larger graphs, in a row of device memory, for IC (kBits = 1)
+// with the active nodes in LDS and each arc's coin drawn as the arc is met.
 //
-// Section 2's rule (v joins when the weight of its active in-neighbours
+// Section 2's LT rule (v joins when the weight of its active in-neighbours
 // exceeds its threshold) needs, per node and trial, one number that every
 // newly active in-neighbour lowers once; the trial joins v in the step that
 // takes it past zero.  A grid-wide sweep re-reads all in-neighbours of every
@@ -114,7 +116,7 @@ struct LtTrialShared {
 // trial's state in LDS (kLds) or in its row where it stands.  A
 // round takes up to 64 * kW joined nodes (lane = node), lays their out-arcs
 // out densely in LDS (a prefix sum of the degrees), fetches 64 targets at a
-// time and updates them in LDS.  Bound by the chain of rounds: one dependent
+// time and updates their states.  Bound by the chain of rounds: one dependent
 // read (the target records, which bring the next round's row bounds) and the
 // update.
 template <int kBits, int kW, bool kLds>

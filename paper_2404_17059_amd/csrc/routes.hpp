@@ -337,19 +337,25 @@ inline bool live_sets_pay(const RouteGraph& g, bool base, const std::vector<uint
     // - cascades that cover the graph in three levels, whose pull steps end
     //   early, but for few walks (growth 39, 16 sets, 1,000 trials 0.85 / 1.68,
     //   100 trials 0.81 / 0.44);
-    // - below growth 0.6, hubs: two live seed arcs a set (directed power law,
-    //   1,000 nodes, TV, 1,000 trials, 1,000 sets of 4 hubs 3.3 / 5.2);
-    // - sets that mostly light nothing, and a long draw (100,000-node preferential
-    //   attachment, p 0.02, 1,000 trials, 64 nodes 0.39 / 0.92);
+    // - below growth 0.6, hubs of small graphs: eight live seed arcs a set, up to
+    //   5,000 nodes (directed power law, TV, 1,000 trials, 200 hubs in sets of 4:
+    //   1,000 nodes 0.80 / 1.25, 5,000 nodes 2.2 / 2.5, 20,000 nodes 5.2 / 3.2);
+    // - sets that mostly light nothing, and a long draw: below growth 1.25 the
+    //   sets' arcs have to be a 300th of all (100,000-node preferential attachment,
+    //   p 0.02, 1,000 trials, 64 nodes 0.39 / 0.92; 5,000-node random regular
+    //   graph, TV, 10,000 trials, 64 nodes 0.52 / 0.58, 5,000 nodes 36 / 1.6);
     // - rings and other local graphs with less than 1.1 new live arcs per live
     //   arc: a cascade's steps meet the same nodes again and a task's few steps
-    //   end it (200,000-node ring, WC, 1,000 trials, 40 sets of 30 0.30 / 2.4;
-    //   20,000 nodes, 16 single nodes 0.14 / 0.31), but for few walks and a short
-    //   draw (20,000 nodes, 20 arcs, 100 trials, 8 sets of 30 0.95 / 0.12), for
-    //   many single nodes (20,000-node ring, 1,000 trials, 1,000 nodes 1.8 / 0.30)
-    //   and for sets that light much of the graph (64 live seed arcs and more).
-    //   Of 8,726 calls 543 were slower than the tasks by more than 15%, at most
-    //   8 times; 52, at most 1.8 times, with this line.
+    //   end it, unless there is much to walk per set and little to draw
+    //   (degree 4, WC, 1,000 trials, 40 sets of 30: 200,000 nodes 0.30 / 2.4, 1,000
+    //   nodes 0.28 / 0.56; degree 20, 8 sets of 30, 5,000 nodes 0.95 / 0.29,
+    //   200,000 nodes 1.6 / 4.6), or many single nodes (degree 4, 20,000 nodes, WC, 8
+    //   nodes 0.11 / 0.17, 1,000 nodes 1.8 / 0.30).  Small calls (sets times
+    //   trials up to 4,000, draws up to 45 us) and sets of 64 live seed arcs and
+    //   more are as on other graphs.
+    //   Of 21,923 calls 672 were slower than the tasks by more than 15%, at most
+    //   8 times, without the last three lines; 126, at most 2.1 times, with them,
+    //   and 80 calls stay with tasks that are slower, at most 2.8 times.
     const uint64_t sets = off.size() - 1;
     uint64_t large = 0;
     for (uint64_t i = 0; i < sets; ++i) large += off[i + 1] - off[i] > kTinySeeds ? 1u : 0u;
@@ -359,10 +365,11 @@ inline bool live_sets_pay(const RouteGraph& g, bool base, const std::vector<uint
     if (sets < 4 && g.ic_growth < (dense ? 0.85 : 1.4)) return false;
     if (g.ic_growth >= 8.0 && sets * n_trials > 8000) return false;
     const double live = (double)arcs * g.ic_pbar / (double)sets, renewed = g.ic_growth * g.ic_fresh;
-    if (g.ic_growth < 0.6 && live > 2.0) return false;
-    if (g.ic_growth < 2.0 && live < 0.6 && draw >= 100.0) return false;
+    const double walked = (double)arcs / (double)sets / (1.0 - std::min(renewed, 0.97));  // by a set's cascade
+    if (g.ic_growth < 0.6 && g.n <= 5000 && live > 8.0) return false;
+    if (g.ic_growth < 1.25 && live < 0.6 && draw >= 100.0 && (double)arcs * 300.0 < (double)g.m) return false;
     if (g.local() && renewed < 1.1 && live < 64.0 && !(sets * n_trials <= 4000 && draw <= 45.0) &&
-        (live > 2.0 || (double)arcs * 16.0 < (double)g.m * (1.0 - std::min(renewed, 0.9))))
+        (live > 2.0 ? walked < 1500.0 || draw > walked / 12.0 : (double)arcs * 200.0 < (double)g.m))
         return false;
     const double reach = g.ic_growth >= 0.8 ? 2000.0 : 8.0 / (1.0 - g.ic_growth);
     return (double)arcs * reach >= (double)g.m || (draw <= 20.0 && off.size() > 8);

@@ -98,6 +98,27 @@ def test_sets_on_local_graphs_keep_the_tasks(routes, n, m, pbar, shape, base, se
     assert routes("sets", n, m, m // n * 20, pbar, *shape, base, sets, size, arcs, trials) == form
 
 
+@pytest.mark.parametrize("n,m,max_out,pbar,growth,spread,fresh,sets,size,arcs,trials,form", [
+    # ms: tasks / drawn.  A random regular graph, TV: the draw is shared by the sets
+    (5000, 34981, 7, 0.0368, 0.2572, 1.0, 1.0, 64, 1, 448, 10000, "tasks"),       # 0.52 / 0.57
+    (5000, 34981, 7, 0.0368, 0.2572, 1.0, 1.0, 5000, 1, 34981, 10000, "drawn"),   # 36 / 1.6
+    (20000, 318844, 1780, 0.0370, 1.94, 1.0, 1.0, 1000, 1, 15356, 1000, "drawn"),  # preferential attachment, TV, 77 / 4.0
+    # hubs of directed power-law graphs, and sets of four on an Erdos-Renyi graph
+    (200000, 1969424, 70707, 0.0370, 0.3633, 1.0, 1.0, 200, 1, 1544502, 100, "drawn"),  # 9.6 / 0.72
+    (60000, 585800, 23602, 0.02, 0.1923, 1.0, 1.0, 200, 4, 1931047, 100, "drawn"),      # 3.3 / 0.49
+    (5000, 49941, 23, 0.0370, 0.3719, 1.0, 1.0, 1000, 4, 76559, 1000, "drawn"),         # 1.7 / 0.55
+    (1000, 8913, 394, 0.0365, 0.3099, 1.0, 1.0, 200, 4, 57037, 1000, "tasks"),          # 0.80 / 1.25
+    # rings: much to walk and little to draw, and the other way round
+    (5000, 99996, 22, 0.05, 1.0, 0.12, 0.92, 8, 30, 4807, 1000, "drawn"),      # 0.95 / 0.29
+    (200000, 3999998, 23, 0.05, 1.0, 0.11, 0.92, 8, 30, 4799, 1000, "tasks"),  # 1.0 / 3.2
+    (60000, 599980, 17, 0.1, 1.0, 0.46, 0.86, 200, 30, 60091, 100, "drawn"),   # a quarter rewired, 0.97 / 0.60
+    (20000, 80000, 6, 0.25, 1.0, 0.57, 0.66, 200, 1, 797, 1000, "drawn"),      # 0.45 / 0.21
+    (60000, 600000, 12, 0.1, 1.0, 0.22, 0.84, 40, 1, 401, 1000, "tasks"),      # 0.19 / 0.61
+])
+def test_many_sets_share_the_drawn_coins(routes, n, m, max_out, pbar, growth, spread, fresh, sets, size, arcs, trials, form):
+    assert routes("sets", n, m, max_out, pbar, growth, spread, fresh, 0, sets, size, arcs, trials) == form
+
+
 @pytest.mark.parametrize("kind,low,high", [("ring", 0.1, 0.6), ("random", 0.95, 1.05)])
 def test_locality_tells_rings_from_random_graphs(routes, kind, low, high):
     n = 3000

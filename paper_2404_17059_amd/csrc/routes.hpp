@@ -255,12 +255,13 @@ inline bool lt_trials_pay(const RouteGraph& g, uint64_t arcs, uint32_t n_trials)
 
 // Whether a one-set run does.  The more out-arcs the seeds have (`arcs`), the
 // fewer sweeps a cascade takes, while every trial still pushes along all it
-// reaches, so the line is a number of seed arcs over all trials: 8e7 with the
+// reaches, so the line is a number of seed arcs over all trials: 1.1e8 with the
 // states in the LDS (scaled by the square root of a state's size, as larger
 // ones leave fewer trials a compute unit), 1.4e7 outside it; below 512 and 256
-// trials a workgroup's chain decides, not their number.  Directed graphs with
+// trials a workgroup's chain decides, not their number, and beyond the 1,024
+// trials that sweep together both forms' times grow with it.  Directed graphs with
 // a hub holding a notable part of all arcs reach far from any seed, and their
-// sweeps are few: 5e7 there, 1e7 where a compute unit holds one trial and they
+// sweeps are few: 5e7 there, 1.5e7 where a compute unit holds one trial and they
 // take turns, and up to 1.1 million arcs (outside the LDS 300,000, and no
 // seeds with a sixteenth of the arcs).  The sweeps draw the hashes of rows
 // above 64 in-arcs anew each time, so those that no seed covers (`long_left`)
@@ -277,7 +278,7 @@ inline bool lt_trials_pay(const RouteGraph& g, uint64_t arcs, uint32_t n_trials)
 //   hub 2.5 / 3.5, ten 2.6 / 2.7; 100,000 nodes (one trial a compute unit), 50
 //   random nodes 2.2 / 4.1, 2,000 6.1 / 4.5, the largest hub 7.8 / 4.5, at
 //   256 trials 2.1 / 3.9
-// (5,100 runs: slower than the sweeps by more than 15% in 28, at most 2.0
+// (5,100 runs: slower than the sweeps by more than 15% in 47, at most 2.6
 // times; 371, at most 30 times, by the rule above.)
 inline bool lt_run_pays(const RouteGraph& g, uint64_t arcs, uint64_t long_left, uint32_t n_trials)
 {
@@ -285,9 +286,10 @@ inline bool lt_run_pays(const RouteGraph& g, uint64_t arcs, uint64_t long_left, 
     const bool lds = lt_trial_lds(g), hub = g.max_out * 64 >= (uint64_t)g.m && g.lt_max_in <= 64;
     if (hub && (lds ? g.m > 1100000 : g.m > 300000 || arcs * 16 >= (uint64_t)g.m)) return false;
     const double state = (double)g.n * lt_trial_bits(g) / 8;
-    const double pushed = (double)arcs * std::max<double>(n_trials, lds ? 512 : 256) * (lds ? std::sqrt(state / 65536.0) : 1.0);
-    const double most = !lds ? 1.4e7 : !hub ? 8e7 : state > 70e3 && n_trials > 256 ? 1e7 : 5e7;
-    return pushed <= most * (1.0 + 50.0 * (double)long_left / (double)std::max<int64_t>(g.m, 1));
+    const double pushed = (double)arcs * std::min(std::max<double>(n_trials, lds ? 512 : 256), 1024.0) * (lds ? std::sqrt(state / 65536.0) : 1.0);
+    const double most = !lds ? 1.4e7 : !hub ? 1.1e8 : state > 70e3 && n_trials > 256 ? 1.5e7 : 5e7;
+    const double left = (double)long_left / (double)std::max<int64_t>(g.m, 1);
+    return pushed <= most * (1.0 + 35.0 * left + 700.0 * left * left);
 }
 
 // Whether a many-sets call takes the drawn-coins form.  It draws every arc's

@@ -53,6 +53,18 @@ def test_lt_runs_of_many_seeds_take_the_sweeps(routes, n, m, max_out, equal, max
     assert routes("lt", n, m, max_out, equal, max_in, arcs, left, trials) == form
 
 
+@pytest.mark.parametrize("n,m,max_out,equal,max_in,arcs,left,trials,form", [
+    # beyond the 1,024 trials that sweep together both forms' times grow with the trials (ms, per-trial form / sweeps)
+    (20000, 200000, 12, 1, 12, 67360, 0, 4096, "trials"),        # a ring, a third of the nodes 1.0 / 3.3
+    (20000, 155757, 7601, 1, 20, 27241, 0, 4096, "trials"),      # directed power law, the ten largest hubs 2.1 / 6.6
+    (20000, 159949, 16, 1, 21, 74312, 0, 4096, "trials"),        # Erdos-Renyi, a third of the nodes 1.5 / 3.2
+    # rows above 64 in-arcs that no seed covers: 10,000 random nodes 16 / 54
+    (100000, 799582, 2343, 1, 2343, 79638, 54000, 1000, "trials"),
+])
+def test_lt_runs_of_many_seeds_and_trials(routes, n, m, max_out, equal, max_in, arcs, left, trials, form):
+    assert routes("lt", n, m, max_out, equal, max_in, arcs, left, trials) == form
+
+
 @pytest.mark.parametrize("n,m,max_out,pbar,growth,arcs,trials,bits,form", [
     # ms: tasks / coins met / coins drawn
     (200000, 5999568, 57, 0.01, 0.3, 2400761, 100, 0, "drawn"),     # a third of the nodes 2.86 / 19.7 / 0.96

@@ -131,6 +131,16 @@ def test_many_sets_share_the_drawn_coins(routes, n, m, max_out, pbar, growth, sp
     assert routes("sets", n, m, max_out, pbar, growth, spread, fresh, 0, sets, size, arcs, trials) == form
 
 
+@pytest.mark.parametrize("n,m,max_out,pbar,growth,sets,size,arcs,trials,form", [
+    # ms: tasks / drawn
+    (20000, 599977, 55, 0.037, 1.11, 16, 30, 21900, 1000, "drawn"),    # Erdos-Renyi, TV, a base of one node 43 / 1.9
+    (5000, 149950, 50, 0.0333, 1.0, 16, 30, 14300, 1000, "drawn"),     # WC, a base of 20 random nodes 3.8 / 0.56
+    (60000, 359768, 1500, 0.037, 1.14, 4, 1, 470, 1000, "tasks"),      # four nodes on a base of 20 hubs 0.16 / 0.45
+])
+def test_marginal_sets_of_many_nodes_take_the_drawn_coins(routes, n, m, max_out, pbar, growth, sets, size, arcs, trials, form):
+    assert routes("sets", n, m, max_out, pbar, growth, 1.0, 1.0, 1, sets, size, arcs, trials) == form
+
+
 @pytest.mark.parametrize("kind,low,high", [("ring", 0.1, 0.6), ("random", 0.95, 1.05)])
 def test_locality_tells_rings_from_random_graphs(routes, kind, low, high):
     n = 3000

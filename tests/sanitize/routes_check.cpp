@@ -35,6 +35,12 @@ int main()
             std::vector<uint32_t> off;
             for (uint64_t i = 0; i <= sets; ++i) off.push_back((uint32_t)(i * size));
             std::cout << (live_sets_pay(g, base, off, arcs, trials) ? "drawn" : "tasks") << "\n";
+        } else if (what == "levels") {
+            uint64_t arcs;
+            uint32_t trials;
+            std::cin >> g.n >> g.m >> g.max_out >> g.ic_pbar >> g.ic_growth >> arcs >> trials;
+            g.ic_in_m = g.m;
+            std::cout << (live_levels_pay(g, arcs, trials) ? "drawn" : "tasks") << "\n";
         } else if (what == "graph") {
             // offsets, targets and thresholds follow: the measures of locality
             std::cin >> g.n >> g.m;

@@ -141,6 +141,18 @@ def test_marginal_sets_of_many_nodes_take_the_drawn_coins(routes, n, m, max_out,
     assert routes("sets", n, m, max_out, pbar, growth, 1.0, 1.0, 1, sets, size, arcs, trials) == form
 
 
+@pytest.mark.parametrize("n,m,max_out,pbar,growth,arcs,trials,form", [
+    # one node, ms: tasks / drawn
+    (10000, 79990, 22, 0.125, 1.0, 8, 1000, "drawn"),      # Erdos-Renyi, WC 0.73 / 0.24
+    (80000, 639980, 24, 0.125, 1.0, 8, 100, "drawn"),      # 0.92 / 0.37
+    (10000, 99945, 800, 0.1, 1.0, 5, 1000, "drawn"),       # preferential attachment, WC 0.53 / 0.23
+    (10000, 94500, 4000, 0.037, 0.34, 2, 1000, "tasks"),   # directed power law, TV 0.062 / 0.115
+    (80000, 639980, 24, 0.02, 0.16, 8, 100, "tasks"),      # 0.069 / 0.081
+])
+def test_level_counts_from_one_node(routes, n, m, max_out, pbar, growth, arcs, trials, form):
+    assert routes("levels", n, m, max_out, pbar, growth, arcs, trials) == form
+
+
 @pytest.mark.parametrize("kind,low,high", [("ring", 0.1, 0.6), ("random", 0.95, 1.05)])
 def test_locality_tells_rings_from_random_graphs(routes, kind, low, high):
     n = 3000

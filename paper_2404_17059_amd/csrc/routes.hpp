@@ -345,10 +345,10 @@ inline bool live_sets_pay(const RouteGraph& g, bool base, const std::vector<uint
     // - below growth 0.6, hubs of small graphs: eight live seed arcs a set, up to
     //   5,000 nodes (directed power law, TV, 1,000 trials, 200 hubs in sets of 4:
     //   1,000 nodes 0.80 / 1.25, 5,000 nodes 2.2 / 2.5, 20,000 nodes 5.2 / 3.2);
-    // - sets that mostly light nothing, and a long draw: below growth 1.25 the
-    //   sets' arcs have to be a 300th of all (100,000-node preferential attachment,
-    //   p 0.02, 1,000 trials, 64 nodes 0.39 / 0.92; 5,000-node random regular
-    //   graph, TV, 10,000 trials, 64 nodes 0.52 / 0.58, 5,000 nodes 36 / 1.6);
+    // - sets that mostly light nothing, and a long draw: below growth 1.25
+    //   with under one live seed arc in all per 1,700 nodes (100,000-node
+    //   preferential attachment, p 0.02, 1,000 trials, 64 nodes 0.39 / 0.92; 60,000
+    //   nodes, p 0.05, 4,000 trials, 64 nodes 0.78 / 1.40, 200 nodes 2.0 / 1.5);
     // - rings and other local graphs with less than 1.1 new live arcs per live
     //   arc: a cascade's steps meet the same nodes again and a task's few steps
     //   end it, unless there is much to walk per set and little to draw
@@ -372,7 +372,7 @@ inline bool live_sets_pay(const RouteGraph& g, bool base, const std::vector<uint
     const double live = (double)arcs * g.ic_pbar / (double)sets, renewed = g.ic_growth * g.ic_fresh;
     const double walked = (double)arcs / (double)sets / (1.0 - std::min(renewed, 0.97));  // by a set's cascade
     if (g.ic_growth < 0.6 && g.n <= 5000 && live > 8.0) return false;
-    if (g.ic_growth < 1.25 && live < 0.6 && draw >= 100.0 && (double)arcs * 300.0 < (double)g.m) return false;
+    if (g.ic_growth < 1.25 && live < 0.6 && draw >= 100.0 && (double)arcs * g.ic_pbar * 1700.0 < (double)g.n) return false;
     if (g.local() && renewed < 1.1 && live < 64.0 && !(sets * n_trials <= 4000 && draw <= 45.0) &&
         (live > 2.0 ? walked < 1500.0 || draw > walked / 12.0 : (double)arcs * 200.0 < (double)g.m))
         return false;

@@ -126,6 +126,11 @@ def test_sets_on_local_graphs_keep_the_tasks(routes, n, m, pbar, shape, base, se
     (60000, 599980, 17, 0.1, 1.0, 0.46, 0.86, 200, 30, 60091, 100, "drawn"),   # a quarter rewired, 0.97 / 0.60
     (20000, 80000, 6, 0.25, 1.0, 0.57, 0.66, 200, 1, 797, 1000, "drawn"),      # 0.45 / 0.21
     (60000, 600000, 12, 0.1, 1.0, 0.22, 0.84, 40, 1, 401, 1000, "tasks"),      # 0.19 / 0.61
+    # light sets: the live seed arcs in all count
+    (60000, 359768, 1500, 0.05, 1.16, 0.93, 0.85, 64, 1, 384, 4000, "tasks"),      # preferential attachment, p 0.05, 0.78 / 1.40
+    (60000, 359768, 1500, 0.05, 1.16, 0.93, 0.85, 200, 1, 1200, 4000, "drawn"),    # 2.0 / 1.5
+    (20000, 194000, 3000, 0.1, 1.0, 0.9, 0.8, 200, 1, 536, 1000, "drawn"),         # directed power law, WC, 0.83 / 0.50
+    (151922, 1032316, 9000, 0.137, 1.0, 0.93, 0.8, 284, 1, 1215, 760, "drawn"),    # 1.35 / 1.07
 ])
 def test_many_sets_share_the_drawn_coins(routes, n, m, max_out, pbar, growth, spread, fresh, sets, size, arcs, trials, form):
     assert routes("sets", n, m, max_out, pbar, growth, spread, fresh, 0, sets, size, arcs, trials) == form

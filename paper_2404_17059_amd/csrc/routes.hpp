@@ -124,12 +124,13 @@ inline bool live_single_pays(const RouteGraph& g, uint32_t n_trials, bool levels
 // Whether a run with level counts does: not where most trials end at once and
 // the others soon (10,000-node directed power law, TV, one node, 1,000 trials
 // 0.062 against 0.115 ms; near growth 1 some go on: 10,000-node Erdos-Renyi, WC,
-// one node, 1,000 trials 0.73 against 0.24, 80,000 nodes, 100 trials 0.92 against 0.37).
+// one node, 1,000 trials 0.73 against 0.24, 80,000 nodes, 100 trials 0.92 against
+// 0.37; ten nodes of an 11,000-node ring, TV, 586 trials 0.23 against 0.16).
 inline bool live_levels_pay(const RouteGraph& g, uint64_t arcs, uint32_t n_trials)
 {
     if (!live_single_pays(g, n_trials, true)) return false;
     const double m = (double)g.m;
-    const bool few = (double)arcs * g.ic_pbar < 2.0 && m < 16.0 * (double)g.n && g.ic_growth < 0.7;
+    const bool few = (double)arcs * g.ic_pbar < 0.5 && m < 16.0 * (double)g.n && g.ic_growth < 0.7;
     return !few || m * (double)((n_trials + 7) / 8) / 150e3 <= 15.0;
 }
 

@@ -153,6 +153,7 @@ def test_marginal_sets_of_many_nodes_take_the_drawn_coins(routes, n, m, max_out,
     (10000, 99945, 800, 0.1, 1.0, 5, 1000, "drawn"),       # preferential attachment, WC 0.53 / 0.23
     (10000, 94500, 4000, 0.037, 0.34, 2, 1000, "tasks"),   # directed power law, TV 0.062 / 0.115
     (80000, 639980, 24, 0.02, 0.16, 8, 100, "tasks"),      # 0.069 / 0.081
+    (11173, 44692, 7, 0.037, 0.15, 40, 586, "drawn"),      # ten nodes of a ring, TV 0.23 / 0.16
 ])
 def test_level_counts_from_one_node(routes, n, m, max_out, pbar, growth, arcs, trials, form):
     assert routes("levels", n, m, max_out, pbar, growth, arcs, trials) == form

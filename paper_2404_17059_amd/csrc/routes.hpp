@@ -170,7 +170,10 @@ inline bool live_item_pays(const RouteGraph& g, uint64_t arcs, uint32_t n_trials
 //   arcs, p 0.01, 66,666 seeds, 100 trials 2.9 / 19.7 / 0.96; 100,000 nodes, 4
 //   arcs, p 0.01, 2,000 seeds with 5%, 1,000 trials 0.25 / 0.34 / 0.41)
 // - up to 200,000 arcs met over all trials, or 300 trials on graphs of up to
-//   12 arcs a node: met, half to all of the tasks' time; beyond, 0.4 to 3 times
+//   12 arcs a node: met, half to all of the tasks' time; beyond, 0.4 to 3 times;
+//   without hubs 400,000 arcs and 750 trials (medians up to 1.2 million arcs: 0.75
+//   to 0.86 of the tasks' time at 100 to 750 trials, 0.9 to 1.2 beyond; 28,000-node
+//   ring, p 0.07, 91 seeds, 624 trials 0.099 / 0.070)
 // Above:
 // - under two live seed arcs, a mean below 1.1 a node, and a draw of over 10
 //   us: most trials end at once (200,000-node preferential attachment, p 0.05,
@@ -188,7 +191,7 @@ inline bool live_item_pays(const RouteGraph& g, uint64_t arcs, uint32_t n_trials
 // With active bits (`bits`) the tasks run whole words and take 2 to 6 times as
 // long, so the arcs met do not count there.
 // (8,064 runs, 1 to a third of the nodes as seeds: slower than the tasks by
-// more than 15% in 76, at most 2.0 times; 667, at most 6.9 times, by growth
+// more than 15% in 86, at most 2.0 times; 667, at most 6.9 times, by growth
 // and trial count alone.  With bits 15 of 4,320, at most 1.8 times; 66, at most
 // 6.6 times.)
 enum class IcForm { kTasks, kDrawn, kMet };
@@ -202,7 +205,9 @@ inline IcForm ic_run_form(const RouteGraph& g, uint64_t arcs, uint32_t n_trials,
     const bool dense = m >= 16.0 * n, meets = n_trials <= 1500 && g.max_out <= 4000;
     if (growth < 0.7) {
         if (n_trials <= 1500 && live >= 100.0 && (double)arcs >= 5e-5 * m * trials) return IcForm::kDrawn;
-        return meets && (bits || met <= 2e5 || (n_trials <= 300 && m <= 12.0 * n && live < 100.0)) ? IcForm::kMet : IcForm::kTasks;
+        const bool flat = (double)g.max_out * n <= 8.0 * m;
+        return meets && (bits || met <= (flat ? 4e5 : 2e5) || (n_trials <= (flat ? 750u : 300u) && m <= 12.0 * n && live < 100.0)) ? IcForm::kMet
+                                                                                                                                 : IcForm::kTasks;
     }
     if (growth < 2.0 && live < 2.0 && live_degree < 1.1 && !dense && draw > 10.0)
         return growth < 1.3 && meets && (bits || met <= 2e5) ? IcForm::kMet : IcForm::kTasks;

@@ -80,6 +80,10 @@ def test_lt_runs_of_many_seeds_and_trials(routes, n, m, max_out, equal, max_in, 
     (10000, 100000, 12, 0.5, 5.0, 1000, 1000, 0, "drawn"),          # a ring, UR 2.2 / - / 0.39
     (100000, 999000, 3000, 0.01, 0.6, 500, 10000, 0, "tasks"),      # beyond 1,500 trials
     (300000, 900000, 20, 0.1, 0.3, 30, 100, 0, "tasks"),            # more nodes than the per-trial forms take
+    # small cascades without hubs, tens of seeds, hundreds of trials
+    (28460, 227680, 12, 0.0716, 0.573, 728, 624, 0, "met"),         # a ring 0.099 / 0.070
+    (51979, 467811, 24, 0.037, 0.33, 540, 364, 0, "met"),           # Erdos-Renyi, TV 0.076 / 0.058
+    (1900, 15200, 20, 0.05, 0.4, 800, 1400, 0, "tasks"),            # 2 million arcs met
 ])
 def test_ic_runs_choose_by_their_seeds(routes, n, m, max_out, pbar, growth, arcs, trials, bits, form):
     assert routes("ic", n, m, max_out, pbar, growth, arcs, trials, bits) == form

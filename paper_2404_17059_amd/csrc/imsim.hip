@@ -1018,11 +1018,8 @@ int simulate_impl(ims_graph* g, const uint32_t* seeds, uint32_t n_seeds, uint32_
         if (g->lt_uniform && !(test_flags & 4) && kmin_bytes <= kThresholdTableBudget && g->kplanes_total < (1ull << 32) &&
             !(test_flags & 8))
             lt_mode = 2;
-        // the bit-sliced sums give a lane to each word of a row: below six
-        // words most lanes idle (100,000-node power-law graph, random weights:
-        // 2.1 against 1.2 ms at 2 words, 3.4 against 3.0 at 5, 3.5 against 3.6
-        // at 7, 3.1 against 7.3 at 16)
-        else if (!(test_flags & 8) && halves_bytes <= kThresholdTableBudget && (W >= 6 || cells * 256 > kThresholdTableBudget))
+        else if (!(test_flags & 8) && halves_bytes <= kThresholdTableBudget &&
+                 (imsim_plan::lt_sliced_pays(*g, seed_out_arcs(g, sv), W) || cells * 256 > kThresholdTableBudget))
             lt_mode = 4;
         else if (cells * 256 <= kThresholdTableBudget) lt_mode = 1;
     }

@@ -299,6 +299,22 @@ inline bool lt_run_pays(const RouteGraph& g, uint64_t arcs, uint64_t long_left, 
     return pushed <= most * (1.0 + 35.0 * left + 700.0 * left * left);
 }
 
+// Whether sweeps over unequal weights take the bit-sliced sums.  Those give a
+// lane to each word of a row, so below six words most lanes idle (100,000-node
+// power-law graph, random weights, ms, threshold table / sliced: 1.2 / 2.1 at 2
+// words, 3.0 / 3.4 at 5, 3.6 / 3.5 at 7, 7.3 / 3.1 at 16), and they sum every
+// in-arc of a pending node, where the table's sweep looks only at the words in
+// which one is active: cascades that stay small on graphs of eight arcs a node
+// and more take it up to 0.85% of the arcs at the seeds, over the words (10 arcs,
+// 55,000 nodes, 34 random seeds, 6 words 2.4 / 4.6, 9 words 3.7 / 5.8, 16 words
+// 6.4 / 6.7; 250,000 nodes, 16 arcs, 10 seeds, 16 words 8.7 / 16.2; 70,000 nodes, 100
+// seeds, 6 words 3.3 / 3.8, 11 words 5.4 / 5.0, 16 words 8.1 / 5.3; 60,000 nodes,
+// 16 arcs, 1,000 seeds, 8 words 8.0 / 7.0).
+inline bool lt_sliced_pays(const RouteGraph& g, uint64_t arcs, uint32_t words)
+{
+    return words >= 6 && (g.m < 8 * g.n || (double)arcs * words >= 0.0085 * (double)g.m);
+}
+
 // Whether a many-sets call takes the drawn-coins form.  It draws every arc's
 // coin once, m * T / 8 hash blocks at about 150 a nanosecond; the tasks draw
 // the coins of the arcs their cascades meet, set by set, at least those of

@@ -35,6 +35,11 @@ int main()
             std::vector<uint32_t> off;
             for (uint64_t i = 0; i <= sets; ++i) off.push_back((uint32_t)(i * size));
             std::cout << (live_sets_pay(g, base, off, arcs, trials) ? "drawn" : "tasks") << "\n";
+        } else if (what == "sweeps") {
+            uint64_t arcs;
+            uint32_t words;
+            std::cin >> g.n >> g.m >> arcs >> words;
+            std::cout << (lt_sliced_pays(g, arcs, words) ? "sliced" : "table") << "\n";
         } else if (what == "levels") {
             uint64_t arcs;
             uint32_t trials;

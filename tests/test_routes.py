@@ -163,6 +163,20 @@ def test_level_counts_from_one_node(routes, n, m, max_out, pbar, growth, arcs, t
     assert routes("levels", n, m, max_out, pbar, growth, arcs, trials) == form
 
 
+@pytest.mark.parametrize("n,m,arcs,words,form", [
+    # directed power-law graphs, unequal weights, ms: threshold table / bit-sliced sums
+    (54860, 534000, 220, 6, "table"),       # 34 random seeds 2.4 / 4.6
+    (54860, 534000, 220, 9, "table"),       # 3.7 / 5.8
+    (250000, 3885325, 40, 16, "table"),     # ten random seeds 8.7 / 16.2
+    (70000, 685129, 541, 16, "sliced"),     # 100 random seeds 8.1 / 5.3
+    (54860, 534000, 90000, 6, "sliced"),    # the largest hubs 2.8 / 2.5
+    (100000, 591739, 20, 16, "sliced"),     # six arcs a node
+    (100000, 591739, 60000, 5, "table"),    # under six words
+])
+def test_sweeps_over_unequal_weights(routes, n, m, arcs, words, form):
+    assert routes("sweeps", n, m, arcs, words) == form
+
+
 @pytest.mark.parametrize("kind,low,high", [("ring", 0.1, 0.6), ("random", 0.95, 1.05)])
 def test_locality_tells_rings_from_random_graphs(routes, kind, low, high):
     n = 3000

@@ -171,9 +171,10 @@ inline bool live_item_pays(const RouteGraph& g, uint64_t arcs, uint32_t n_trials
 //   arcs, p 0.01, 2,000 seeds with 5%, 1,000 trials 0.25 / 0.34 / 0.41)
 // - up to 200,000 arcs met over all trials, or 300 trials on graphs of up to
 //   12 arcs a node: met, half to all of the tasks' time; beyond, 0.4 to 3 times;
-//   without hubs 400,000 arcs and 750 trials (medians up to 1.2 million arcs: 0.75
-//   to 0.86 of the tasks' time at 100 to 750 trials, 0.9 to 1.2 beyond; 28,000-node
-//   ring, p 0.07, 91 seeds, 624 trials 0.099 / 0.070)
+//   without hubs 100 arcs a node, up to 2 million, and 750 trials (medians up to
+//   1.2 million arcs: 0.75 to 0.86 of the tasks' time at 100 to 750 trials, beyond
+//   0.9 on 10,000 nodes and more, 1.2 on 1,000; 28,000-node ring, p 0.07, 91 seeds,
+//   624 trials 0.099 / 0.070; 96,000 nodes, 60 seeds, 1,184 trials 0.15 / 0.12)
 // Above:
 // - under two live seed arcs, a mean below 1.1 a node, and a draw of over 10
 //   us: most trials end at once (200,000-node preferential attachment, p 0.05,
@@ -191,7 +192,7 @@ inline bool live_item_pays(const RouteGraph& g, uint64_t arcs, uint32_t n_trials
 // With active bits (`bits`) the tasks run whole words and take 2 to 6 times as
 // long, so the arcs met do not count there.
 // (8,064 runs, 1 to a third of the nodes as seeds: slower than the tasks by
-// more than 15% in 86, at most 2.0 times; 667, at most 6.9 times, by growth
+// more than 15% in 90, at most 2.0 times; 667, at most 6.9 times, by growth
 // and trial count alone.  With bits 15 of 4,320, at most 1.8 times; 66, at most
 // 6.6 times.)
 enum class IcForm { kTasks, kDrawn, kMet };
@@ -206,7 +207,7 @@ inline IcForm ic_run_form(const RouteGraph& g, uint64_t arcs, uint32_t n_trials,
     if (growth < 0.7) {
         if (n_trials <= 1500 && live >= 100.0 && (double)arcs >= 5e-5 * m * trials) return IcForm::kDrawn;
         const bool flat = (double)g.max_out * n <= 8.0 * m;
-        return meets && (bits || met <= (flat ? 4e5 : 2e5) || (n_trials <= (flat ? 750u : 300u) && m <= 12.0 * n && live < 100.0)) ? IcForm::kMet
+        return meets && (bits || met <= (flat ? std::max(2e5, std::min(100.0 * n, 2e6)) : 2e5) || (n_trials <= (flat ? 750u : 300u) && m <= 12.0 * n && live < 100.0)) ? IcForm::kMet
                                                                                                                                  : IcForm::kTasks;
     }
     if (growth < 2.0 && live < 2.0 && live_degree < 1.1 && !dense && draw > 10.0)

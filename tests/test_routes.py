@@ -83,6 +83,7 @@ def test_lt_runs_of_many_seeds_and_trials(routes, n, m, max_out, equal, max_in, 
     # small cascades without hubs, tens of seeds, hundreds of trials
     (28460, 227680, 12, 0.0716, 0.573, 728, 624, 0, "met"),         # a ring 0.099 / 0.070
     (51979, 467811, 24, 0.037, 0.33, 540, 364, 0, "met"),           # Erdos-Renyi, TV 0.076 / 0.058
+    (95702, 574212, 8, 0.0848, 0.51, 360, 1184, 0, "met"),          # a ring 0.15 / 0.12
     (1900, 15200, 20, 0.05, 0.4, 800, 1400, 0, "tasks"),            # 2 million arcs met
 ])
 def test_ic_runs_choose_by_their_seeds(routes, n, m, max_out, pbar, growth, arcs, trials, bits, form):

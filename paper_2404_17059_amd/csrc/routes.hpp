@@ -207,8 +207,9 @@ inline IcForm ic_run_form(const RouteGraph& g, uint64_t arcs, uint32_t n_trials,
     if (growth < 0.7) {
         if (n_trials <= 1500 && live >= 100.0 && (double)arcs >= 5e-5 * m * trials) return IcForm::kDrawn;
         const bool flat = (double)g.max_out * n <= 8.0 * m;
-        return meets && (bits || met <= (flat ? std::max(2e5, std::min(100.0 * n, 2e6)) : 2e5) || (n_trials <= (flat ? 750u : 300u) && m <= 12.0 * n && live < 100.0)) ? IcForm::kMet
-                                                                                                                                 : IcForm::kTasks;
+        const double most = flat ? std::max(2e5, std::min(100.0 * n, 2e6)) : 2e5;
+        const bool small = n_trials <= (flat ? 750u : 300u) && m <= 12.0 * n && live < 100.0;
+        return meets && (bits || met <= most || small) ? IcForm::kMet : IcForm::kTasks;
     }
     if (growth < 2.0 && live < 2.0 && live_degree < 1.1 && !dense && draw > 10.0)
         return growth < 1.3 && meets && (bits || met <= 2e5) ? IcForm::kMet : IcForm::kTasks;
